@@ -540,40 +540,50 @@ __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmA
             float* C = (float*)g.C;
             const bf16_t* bias = (const bf16_t*)g.bias;
             const int rr = lane >> 3, c4 = (lane & 7) * 4;    // read-back: row rr + 8 it, columns c4..
+            // every bias value ahead of the first store: loads and stores share one counter, so a
+            // load between the blocks would wait for all the stores before it
+            float bv[NB][4];
 #pragma unroll
-            for (int b = 0; b < MB * NB; ++b) {
-                const int mb = b % MB, nb = b / MB;
-                const int wr = lane & 31;
-#pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4) {
-                    const int slot = (2 * j4 + (lane >> 5)) ^ ((wr >> 1) & 7);
-                    *(float4*)&cst[wr * 32 + slot * 4] =
-                        make_float4(acc[nb][mb][4 * j4], acc[nb][mb][4 * j4 + 1], acc[nb][mb][4 * j4 + 2],
-                                    acc[nb][mb][4 * j4 + 3]);
-                }
+            for (int nb = 0; nb < NB; ++nb) {
                 const int n = n0 + wn * S::WN + nb * 32 + c4;
-                float bv[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n + e < g.N) bv[e] = bf16_to_f32(bias[n + e]);
+                for (int e = 0; e < 4; ++e) bv[nb][e] = bf16_to_f32(bias[min(n + e, g.N - 1)]);
+            }
+            auto blocks = [&](auto whole_c) {
+                constexpr bool whole = decltype(whole_c)::value;
 #pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int r = rr + 8 * it;
-                    const float4 v = *(const float4*)&cst[r * 32 + (((c4 >> 2) ^ ((r >> 1) & 7)) * 4)];
-                    const int m = tm0 + wm * S::WM + mb * 32 + r;
-                    if (m >= M) continue;
-                    float* dst = C + (int64_t)m * g.ldc + n;
-                    if (n + 3 < g.N) {
-                        // an ordinary store: the normalisation reads the row next and finds it in
-                        // the Infinity Cache (12.9 -> 11.9 us per LayerNorm at B16 L1024)
-                        *(f32x4*)dst = f32x4{v.x + bv[0], v.y + bv[1], v.z + bv[2], v.w + bv[3]};
-                    } else {
-                        const float o[4] = {v.x + bv[0], v.y + bv[1], v.z + bv[2], v.w + bv[3]};
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < g.N) dst[e] = o[e];
+                for (int b = 0; b < MB * NB; ++b) {
+                    const int mb = b % MB, nb = b / MB;
+                    const int wr = lane & 31;
+#pragma unroll
+                    for (int j4 = 0; j4 < 4; ++j4) {
+                        const int slot = (2 * j4 + (lane >> 5)) ^ ((wr >> 1) & 7);
+                        *(float4*)&cst[wr * 32 + slot * 4] =
+                            make_float4(acc[nb][mb][4 * j4], acc[nb][mb][4 * j4 + 1], acc[nb][mb][4 * j4 + 2],
+                                        acc[nb][mb][4 * j4 + 3]);
+                    }
+                    const int n = n0 + wn * S::WN + nb * 32 + c4;
+#pragma unroll
+                    for (int it = 0; it < 4; ++it) {
+                        const int r = rr + 8 * it;
+                        const float4 v = *(const float4*)&cst[r * 32 + (((c4 >> 2) ^ ((r >> 1) & 7)) * 4)];
+                        const int m = tm0 + wm * S::WM + mb * 32 + r;
+                        if (!whole && m >= M) continue;
+                        float* dst = C + (int64_t)m * g.ldc + n;
+                        const float o[4] = {v.x + bv[nb][0], v.y + bv[nb][1], v.z + bv[nb][2], v.w + bv[nb][3]};
+                        if (whole || n + 3 < g.N) {
+                            // an ordinary store: the normalisation reads the row next and finds it in
+                            // the Infinity Cache (12.9 -> 11.9 us per LayerNorm at B16 L1024)
+                            *(f32x4*)dst = f32x4{o[0], o[1], o[2], o[3]};
+                        } else {
+                            for (int e = 0; e < 4; ++e)
+                                if (n + e < g.N) dst[e] = o[e];
+                        }
                     }
                 }
-            }
+            };
+            if (tm0 + DM <= M && n0 + S::TBN <= g.N) blocks(std::true_type{});
+            else blocks(std::false_type{});
         } else {
             // bf16 outputs: each wave stages half of its WM x WN sub-tile at a time in LDS (rows
             // padded by 16 B, above stage 0), then writes whole row segments with 16-byte stores.
@@ -836,28 +846,47 @@ __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmA
             if constexpr (!RING) {
                 if (g.c_in) C = g.c_in;
             }
+            // a whole tile issues all its loads before anything waits for one; with the bounds tests
+            // of a ragged tile between them each load was waited for before the next went out
+            if (m0 + DM <= M && n0 + S::TBN <= g.N) {
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
+                for (int i = 0; i < NB; ++i)
 #pragma unroll
-                for (int j = 0; j < MB; ++j)
+                    for (int j = 0; j < MB; ++j) {
+                        const float* hp = C + hrow[j] * g.ldc + (n0 + wn * S::WN + i * 32 + 4 * (lane >> 5));
 #pragma unroll
-                    for (int j4 = 0; j4 < 4; ++j4) {
-                        const int m = m0 + wm * S::WM + j * 32 + (lane & 31);
-                        const int n = n0 + wn * S::WN + i * 32 + 8 * j4 + 4 * (lane >> 5);
-                        float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (m < M && n + 3 < g.N) {
-                            h = *(const float4*)(C + hrow[j] * g.ldc + n);
-                        } else if (m < M) {
-                            float t[4] = {0.f, 0.f, 0.f, 0.f};
-                            for (int e = 0; e < 4; ++e)
-                                if (n + e < g.N) t[e] = C[hrow[j] * g.ldc + n + e];
-                            h = make_float4(t[0], t[1], t[2], t[3]);
+                        for (int j4 = 0; j4 < 4; ++j4) {
+                            const float4 h = *(const float4*)(hp + 8 * j4);
+                            acc[i][j][4 * j4] = h.x;
+                            acc[i][j][4 * j4 + 1] = h.y;
+                            acc[i][j][4 * j4 + 2] = h.z;
+                            acc[i][j][4 * j4 + 3] = h.w;
                         }
-                        acc[i][j][4 * j4] = h.x;
-                        acc[i][j][4 * j4 + 1] = h.y;
-                        acc[i][j][4 * j4 + 2] = h.z;
-                        acc[i][j][4 * j4 + 3] = h.w;
                     }
+            } else {
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int j = 0; j < MB; ++j)
+#pragma unroll
+                        for (int j4 = 0; j4 < 4; ++j4) {
+                            const int m = m0 + wm * S::WM + j * 32 + (lane & 31);
+                            const int n = n0 + wn * S::WN + i * 32 + 8 * j4 + 4 * (lane >> 5);
+                            float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+                            if (m < M && n + 3 < g.N) {
+                                h = *(const float4*)(C + hrow[j] * g.ldc + n);
+                            } else if (m < M) {
+                                float t[4] = {0.f, 0.f, 0.f, 0.f};
+                                for (int e = 0; e < 4; ++e)
+                                    if (n + e < g.N) t[e] = C[hrow[j] * g.ldc + n + e];
+                                h = make_float4(t[0], t[1], t[2], t[3]);
+                            }
+                            acc[i][j][4 * j4] = h.x;
+                            acc[i][j][4 * j4 + 1] = h.y;
+                            acc[i][j][4 * j4 + 2] = h.z;
+                            acc[i][j][4 * j4 + 3] = h.w;
+                        }
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < NB; ++i)
