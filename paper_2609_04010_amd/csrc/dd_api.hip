@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <initializer_list>
 #include <mutex>
 #include <vector>
 
@@ -286,6 +287,27 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         return launch_gemm(dt, EPI_GATE, KC_GEMM_LORA, g, s);
     };
 
+    // Splits a residual projection over K (launch_gemm's choice, or `forced` ways where given) as far
+    // as the free regions of the workspace hold its partials ([rows][d] fp32 each), and describes
+    // them to the normalisation that reads the row next.
+    struct Region {
+        char *begin, *end;
+    };
+    auto split_k = [&](GemmArgs& g, LnSlabs& add, int64_t rows, int forced, std::initializer_list<Region> free_ws) {
+        g.k_base = g.K - r;
+        const size_t need = (size_t)rows * d * sizeof(float);
+        add = LnSlabs{};
+        g.splits = 1;
+        if (dt != DD_BF16) return;
+        int n = 0;
+        for (const Region& f : free_ws)
+            for (char* p = f.begin; n < MAX_SPLITS - 1 && p + need <= f.end; p += need) g.slab[n++] = (float*)p;
+        g.splits = forced ? std::min(forced, n + 1) : gemm_splits(dt, EPI_BIAS_RESID, g, n + 1);
+        g.splits = std::max(1, std::min(g.splits, g.k_base / 128));
+        add.n = g.splits - 1;
+        for (int i = 0; i < add.n; ++i) add.slab[i] = g.slab[i];
+    };
+
     // With vocab_rows only the listed rows get logits.  In the last layer only the attention's keys
     // and values mix rows, so from its queries on that layer runs on the listed rows alone,
     // compacted (row j is token row vocab_rows[j]; vocab_seq gives each sequence's first list
@@ -315,44 +337,62 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         DD_TRY(launch_attn(dt, aa, s));
         if (tail) {
             // The listed rows are few in most steps (about M / T from an all-mask start), where the
-            // 256-row tiles leave most CUs idle through a whole K loop.  Each of these GEMMs is
-            // launched twice, gated on the device-side count: the shape's usual tiles above
-            // TAIL_ROWS rows, 64 x 32 tiles of one wavefront up to it (several workgroups per CU;
-            // 4.172 -> 4.159 ms per reverse step against 64 x 128 tiles of four wavefronts).
+            // 256-row tiles leave most CUs idle through a whole K loop.  Up to TAIL_ROWS rows the ring
+            // kernel's 64 x 64 tiles do these GEMMs, the residual ones split over K; for larger M each
+            // is launched twice, gated on the device-side count, with the shape's usual tiles above.
             constexpr int TAIL_ROWS = 2048;
+            const int64_t cap = std::min<int64_t>(M, TAIL_ROWS);
             auto gated = [&](GemmArgs ga, int epi, int cls) -> dd_status {
-                ga.m_gate = TAIL_ROWS;
-                ga.m_side = 0;
-                DD_TRY(launch_gemm(dt, epi, cls, ga, s));
-                ga.m_side = 1;
-                ga.tile_hint = 10 + 1;
+                if (M > TAIL_ROWS) {
+                    GemmArgs big = ga;
+                    big.m_gate = TAIL_ROWS;
+                    big.m_side = 0;
+                    big.splits = 1;
+                    DD_TRY(launch_gemm(dt, epi, cls, big, s));
+                    ga.m_gate = TAIL_ROWS;
+                    ga.m_side = 1;
+                }
+                ga.m_rows = (int)cap;
+                ga.tile_hint = TILE_TAIL + 1;
                 return launch_gemm(dt, epi, cls, ga, s);
             };
             float* hc = (float*)qkv;
+            LnSlabs add;
             g = {att, dr, tp(b + 4), dr, tp(b + 5), hc, d, (int)M, d, dr, nullptr, vocab_count};
             g.c_in = h;
             g.c_rows = vocab_rows;
+            split_k(g, add, cap, MAX_SPLITS, {{(char*)mlp, (char*)ws + w.total_fwd}});
+            add.gate = M > TAIL_ROWS ? TAIL_ROWS : 0;
+            add.h_out = hc;
             DD_TRY(gated(g, EPI_BIAS_RESID, KC_GEMM_O));
-            DD_TRY(launch_ln(dt, c->norm, hc, M, d, tp(b + 6), tp(b + 7), c->norm_eps, xln, dr, s, vocab_count));
+            DD_TRY(launch_ln(dt, c->norm, hc, M, d, tp(b + 6), tp(b + 7), c->norm_eps, xln, dr, s, vocab_count, &add));
             g = {xln, dr, tp(b + 8), dr, tp(b + 9), mlp, Fr, (int)M, F, dr, nullptr, vocab_count};
             DD_TRY(gated(g, EPI_BIAS_GELU, KC_GEMM_MLP1));
+            // (the residual rows h have been read for the last time)
             g = {mlp, Fr, tp(b + 10), Fr, tp(b + 11), hc, d, (int)M, d, Fr, nullptr, vocab_count};
+            split_k(g, add, cap, MAX_SPLITS, {{(char*)h, (char*)xln}, {(char*)(hc + M * d), (char*)mlp}});
+            add.gate = M > TAIL_ROWS ? TAIL_ROWS : 0;
             DD_TRY(gated(g, EPI_BIAS_RESID, KC_GEMM_MLP2));
-            DD_TRY(launch_ln(dt, c->norm, hc, M, d, tp(lnf), tp(lnf + 1), c->norm_eps, xln, dr, s, vocab_count));
+            DD_TRY(launch_ln(dt, c->norm, hc, M, d, tp(lnf), tp(lnf + 1), c->norm_eps, xln, dr, s, vocab_count, &add));
             break;
         }
         if (r > 0) DD_TRY(lora_down(att, dr, d, a0 + 1));
+        LnSlabs add;
         g = {att, dr, tp(b + 4), dr, tp(b + 5), h, d, (int)M, d, dr, nullptr, nullptr};
+        split_k(g, add, M, 0, {{(char*)mlp, (char*)ws + w.total_fwd}, {(char*)qkv, (char*)att}});
+        add.h_out = h;
         DD_TRY(launch_gemm(dt, EPI_BIAS_RESID, KC_GEMM_O, g, s));
-        DD_TRY(launch_ln(dt, c->norm, h, M, d, tp(b + 6), tp(b + 7), c->norm_eps, xln, dr, s));
+        DD_TRY(launch_ln(dt, c->norm, h, M, d, tp(b + 6), tp(b + 7), c->norm_eps, xln, dr, s, nullptr, &add));
         if (r > 0) DD_TRY(lora_down(xln, dr, d, a0 + 2));
         g = {xln, dr, tp(b + 8), dr, tp(b + 9), mlp, Fr, (int)M, F, dr, nullptr, nullptr};
         DD_TRY(launch_gemm(dt, EPI_BIAS_GELU, KC_GEMM_MLP1, g, s));
         if (r > 0) DD_TRY(lora_down(mlp, Fr, F, a0 + 3));
         g = {mlp, Fr, tp(b + 10), Fr, tp(b + 11), h, d, (int)M, d, Fr, nullptr, nullptr};
+        split_k(g, add, M, 0, {{(char*)qkv, (char*)mlp}});
+        add.h_out = l + 1 < nl ? h : nullptr;   // after the last layer only the normalised row is read
         DD_TRY(launch_gemm(dt, EPI_BIAS_RESID, KC_GEMM_MLP2, g, s));
         const int gn = (l + 1 < nl) ? b + 12 : lnf;
-        DD_TRY(launch_ln(dt, c->norm, h, M, d, tp(gn), tp(gn + 1), c->norm_eps, xln, dr, s));
+        DD_TRY(launch_ln(dt, c->norm, h, M, d, tp(gn), tp(gn + 1), c->norm_eps, xln, dr, s, nullptr, &add));
     }
     // with vocab_rows only the listed rows (count on the device) get logits, compacted; after the
     // compacted last layer the normalised rows are already in list order

@@ -1,0 +1,39 @@
+// Types and device helpers shared by the bf16 GEMM kernels.
+#pragma once
+
+#include "kernels.h"
+
+namespace dd {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// gelu_tanh(x) = 0.5 x (1 + tanh(y)) = x / (1 + exp(-2y)), y = sqrt(2/pi) (x + 0.044715 x^3), with
+// exp(-2y) = 2^(x (a + b x^2)), a = -2 sqrt(2/pi) log2(e), b = 0.044715 a: five VALU operations plus
+// v_exp_f32 and v_rcp_f32 (about 1 ulp each; the result is rounded to bf16 afterwards)
+DD_DEV float gelu_tanh(float x) {
+    const float e = __builtin_amdgcn_exp2f(x * fmaf(x * x, -0.1029432395800235f, -2.302208198144325f));
+    return x * __builtin_amdgcn_rcpf(1.0f + e);
+}
+
+constexpr int BK = 64;   // K depth of an operand tile
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) const void gbl_void;
+
+// EPI_GATE row factor of output row m (m % gate_period is in range for any m, clamped rows too)
+DD_DEV float gate_row_scale(const GemmArgs& g, int m) {
+    if (!g.gate) return g.gate_scale;
+    return g.gate[m % g.gate_period] != 0 ? g.gate_scale : 0.f;
+}
+
+// Tiles of the ring kernel (k_gemm_ring.hip): 128 x 128 (four stages, one workgroup of eight
+// wavefronts per CU), 64 x 64 with four stages (two workgroups of four wavefronts per CU) or three
+// stages (three per CU)
+enum RingTile { RING_128 = 0, RING_64_DEEP = 1, RING_64 = 2 };
+void launch_gemm_ring(RingTile tile, int epi, const GemmArgs& g, hipStream_t s);
+double gemm_ring_us(RingTile tile, int64_t M, int64_t N, int64_t K, int splits, int cus);
+
+}  // namespace dd

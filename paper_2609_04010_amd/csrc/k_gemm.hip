@@ -1,12 +1,10 @@
 // Dense layers of the denoiser: C = A W^T (+ epilogue), A [M][K] row-major, W [N][K] row-major
 // (weights stored [out][in]), so both operands are contiguous along K.
 //
-// bf16 path: workgroup tiles of 128 or 256 rows/columns by 64 along K, 4 wavefronts each owning a
-// quarter of the tile, computed with v_mfma_f32_32x32x16_bf16 (fp32 accumulation).  Global -> register prefetch of the next K-tile
-// overlaps the MFMAs on the current one; tiles are double-buffered in padded LDS rows (144 B) so
-// the 16-byte fragment reads are bank-conflict free.  The MFMA's first operand is the weight
-// fragment, so each lane ends with four consecutive output columns of one row, which the
-// epilogue writes as 8-byte (bf16) or 16-byte (fp32 residual) accesses.
+// bf16 path: workgroup tiles of 256 rows by 256 or 192 columns by 64 along K, computed with
+// v_mfma_f32_32x32x16_bf16 (fp32 accumulation).  The MFMA's first operand is the weight fragment, so
+// each lane ends with four consecutive output columns of one row.  Products on few rows, or with K
+// not a multiple of 128, take the ring kernel of k_gemm_ring.hip (plan_tile below chooses).
 //
 // Tile order: workgroups are dispatched round-robin over the 8 XCDs; each XCD is given a
 // contiguous run of tile ids, walked in groups of 8 M-tiles so concurrent tiles share A and W
@@ -27,23 +25,11 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gemm_common.h"
 #include "kernels.h"
 #include "rng.h"
 
 namespace dd {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-// gelu_tanh(x) = 0.5 x (1 + tanh(y)) = x / (1 + exp(-2y)), y = sqrt(2/pi) (x + 0.044715 x^3), with
-// exp(-2y) = 2^(x (a + b x^2)), a = -2 sqrt(2/pi) log2(e), b = 0.044715 a: five VALU operations plus
-// v_exp_f32 and v_rcp_f32 (about 1 ulp each; the result is rounded to bf16 afterwards)
-DD_DEV float gelu_tanh(float x) {
-    const float e = __builtin_amdgcn_exp2f(x * fmaf(x * x, -0.1029432395800235f, -2.302208198144325f));
-    return x * __builtin_amdgcn_rcpf(1.0f + e);
-}
 
 // M-tiles per group of the tile order (map_tile) of the body projections other than QKV (4; QKV
 // takes 2, the vocabulary projection 8: see the kernel).  Measured: QKV 69.6 -> 66.0 us with 4
@@ -64,7 +50,6 @@ DD_DEV void map_tile(int bid, int nblocks, int tiles_m, int tiles_n, int& tm, in
 }
 
 // ------------------------------------------------------------------------------ bf16 MFMA
-constexpr int BK = 64, LSTR = BK + 8;
 constexpr float LOG2E_F = 1.4426950408889634f;
 
 // x rounded to bf16 (round to nearest even, like the stores), as an fp32 value: one conversion that
@@ -73,149 +58,6 @@ DD_DEV float round_bf16(float x) {
     uint32_t r;
     asm("v_cvt_pk_bf16_f32 %0, 0, %1" : "=v"(r) : "v"(x));
     return __uint_as_float(r);
-}
-
-// EPI_GATE row factor of output row m (m % gate_period is in range for any m, clamped rows too)
-DD_DEV float gate_row_scale(const GemmArgs& g, int m) {
-    if (!g.gate) return g.gate_scale;
-    return g.gate[m % g.gate_period] != 0 ? g.gate_scale : 0.f;
-}
-
-template <int EPI>
-DD_DEV void epilogue_bf16(const GemmArgs& g, int m, int n, const float* v, const float* bias4) {
-    float o[4];
-    const float rs = EPI == EPI_GATE ? gate_row_scale(g, m) : 1.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float x = v[e] + bias4[e];
-        if (EPI == EPI_BIAS_GELU) x = gelu_tanh(x);
-        if (EPI == EPI_GATE) x = v[e] * rs;
-        o[e] = x;
-    }
-    if (EPI == EPI_BIAS_RESID) {
-        float* c = (float*)g.C + (int64_t)m * g.ldc + n;
-        if (n + 3 < g.N) {
-            float4 h = *(float4*)c;
-            h.x += o[0]; h.y += o[1]; h.z += o[2]; h.w += o[3];
-            *(float4*)c = h;
-        } else {
-            for (int e = 0; e < 4; ++e) if (n + e < g.N) c[e] += o[e];
-        }
-    } else {
-        bf16_t* c = (bf16_t*)g.C + (int64_t)m * g.ldc + n;
-        if (n + 3 < g.N) {
-            uint2 p;
-            p.x = pack_bf16x2(o[0], o[1]);
-            p.y = pack_bf16x2(o[2], o[3]);
-            *(uint2*)c = p;
-        } else {
-            for (int e = 0; e < 4; ++e) if (n + e < g.N) c[e] = f32_to_bf16(o[e]);
-        }
-    }
-}
-
-// Workgroup tile TBM x TBN (x BK): 4 wavefronts in a 2 x 2 grid, each owning a (TBM/2) x (TBN/2)
-// sub-tile of MB x NB 32x32 MFMA blocks.  Larger wave tiles read fewer LDS bytes per MFMA flop
-// (64x64: 32 flop/B, 128x128: 64 flop/B).
-template <int TBM, int TBN, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    constexpr int MB = TBM / 64, NB = TBN / 64;       // 32x32 blocks per wave along M and N
-    constexpr int RA = TBM / 32, RW = TBN / 32;       // 16-byte chunks per thread per K-tile
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    bf16_t* As = smem;                        // [2][TBM * LSTR]
-    bf16_t* Ws = smem + 2 * TBM * LSTR;       // [2][TBN * LSTR]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    int tm, tn;
-    map_tile(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
-    const int m0 = tm * TBM, n0 = tn * TBN;
-    const bf16_t* A = (const bf16_t*)g.A;
-    const bf16_t* W = (const bf16_t*)g.W;
-
-    f32x16 acc[NB][MB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    uint4 ra[RA], rw[RW];
-    const int lrow = tid >> 3, lk = (tid & 7) * 8;
-    auto gload = [&](int k0) {
-        const int gk = k0 + lk;
-#pragma unroll
-        for (int r = 0; r < RA; ++r) {
-            const int gm = m0 + lrow + 32 * r;
-            ra[r] = (gm < g.M && gk < g.K) ? *(const uint4*)(A + (int64_t)gm * g.lda + gk)
-                                           : make_uint4(0u, 0u, 0u, 0u);
-        }
-#pragma unroll
-        for (int r = 0; r < RW; ++r) {
-            const int gn = n0 + lrow + 32 * r;
-            rw[r] = (gn < g.N && gk < g.K) ? *(const uint4*)(W + (int64_t)gn * g.ldw + gk)
-                                           : make_uint4(0u, 0u, 0u, 0u);
-        }
-    };
-    auto sstore = [&](int buf) {
-#pragma unroll
-        for (int r = 0; r < RA; ++r)
-            *(uint4*)&As[buf * TBM * LSTR + (lrow + 32 * r) * LSTR + lk] = ra[r];
-#pragma unroll
-        for (int r = 0; r < RW; ++r)
-            *(uint4*)&Ws[buf * TBN * LSTR + (lrow + 32 * r) * LSTR + lk] = rw[r];
-    };
-    auto compute = [&](int buf) {
-        const bf16_t* Ab = As + buf * TBM * LSTR + (wm * (TBM / 2) + (lane & 31)) * LSTR;
-        const bf16_t* Wb = Ws + buf * TBN * LSTR + (wn * (TBN / 2) + (lane & 31)) * LSTR;
-#pragma unroll
-        for (int kk = 0; kk < BK / 16; ++kk) {
-            const int koff = kk * 16 + (lane >> 5) * 8;
-            bf16x8 af[MB], wf[NB];
-#pragma unroll
-            for (int i = 0; i < MB; ++i) af[i] = *(const bf16x8*)&Ab[i * 32 * LSTR + koff];
-#pragma unroll
-            for (int i = 0; i < NB; ++i) wf[i] = *(const bf16x8*)&Wb[i * 32 * LSTR + koff];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[nb], af[mb], acc[nb][mb], 0, 0, 0);
-        }
-    };
-
-    const int nk = (g.K + BK - 1) / BK;
-    gload(0);
-    sstore(0);
-    __syncthreads();
-    for (int t = 0; t < nk; ++t) {
-        if (t + 1 < nk) gload((t + 1) * BK);
-        compute(t & 1);
-        if (t + 1 < nk) sstore((t + 1) & 1);
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-            const int n = n0 + wn * (TBN / 2) + nb * 32 + 8 * j4 + 4 * (lane >> 5);
-            if (n >= g.N) continue;
-            float b4[4] = {0.f, 0.f, 0.f, 0.f};
-            if (EPI != EPI_PLAIN && EPI != EPI_GATE)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n + e < g.N) b4[e] = bf16_to_f32(((const bf16_t*)g.bias)[n + e]);
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int m = m0 + wm * (TBM / 2) + mb * 32 + (lane & 31);
-                if (m >= g.M) continue;
-                float v[4] = {acc[nb][mb][4 * j4], acc[nb][mb][4 * j4 + 1], acc[nb][mb][4 * j4 + 2],
-                              acc[nb][mb][4 * j4 + 3]};
-                epilogue_bf16<EPI>(g, m, n, v, b4);
-            }
-        }
 }
 
 // ------------------------------------------------------------------------------ bf16, direct to LDS
@@ -285,9 +127,6 @@ template <int EPI, class S> constexpr size_t dl_lds_bytes() {
     return S::LDS + (EPI == EPI_LSE || EPI == EPI_LSE_CDF ? (size_t)S::DM * S::WGN * sizeof(float2) : 0) +
            (EPI == EPI_LSE_CDF ? (size_t)S::DM * sizeof(float2) : 0);
 }
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_void;
 
 // ROLE (the profiler class of the layer) only separates the symbols of layers sharing an epilogue.
 // Persistent: workgroup b takes tiles b, b + G, b + 2G, ... (G = grid size).  The number of K-tiles
@@ -945,9 +784,6 @@ __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmA
     __builtin_amdgcn_s_waitcnt(0x3F70);           // vmcnt(0): no LDS write in flight at exit
 }
 
-template <int TBM, int TBN>
-constexpr size_t gemm_lds_bytes() { return (size_t)2 * (TBM + TBN) * LSTR * sizeof(bf16_t); }
-
 // ------------------------------------------------------------------------------ fp32 (validation)
 constexpr int FT = 64, FK = 16;
 
@@ -1001,31 +837,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_m, 
     }
 }
 
-template <int TBM, int TBN, int EPI>
-static void launch_tile(const GemmArgs& g, hipStream_t s) {
-    const int tm = (g.M + TBM - 1) / TBM, tn = (g.N + TBN - 1) / TBN;
-    constexpr size_t lds = gemm_lds_bytes<TBM, TBN>();
-    static bool attr = false;   // one-time opt-in to more than 64 KB of LDS per workgroup
-    if (!attr) {
-        (void)hipFuncSetAttribute((const void*)gemm_bf16_kernel<TBM, TBN, EPI>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        attr = true;
-    }
-    launch_k((gemm_bf16_kernel<TBM, TBN, EPI>), dim3(tm * tn), dim3(256), lds, s, g, tm, tn);
-}
-
-// Tile choice for the direct-to-LDS kernel: the N width (256 or 192) with the smaller estimated time,
-// counting whole rounds of workgroups over the CUs (a round of 192-wide tiles takes about 0.85 of a
-// round of 256-wide ones on MI355X), in the 8-wavefront form (two wavefronts per SIMD, measured 2-6%
-// faster than four wavefronts of twice the sub-tile).  K % 128 != 0 falls back to the 128 x 128
-// register-staged kernel.  Skinny products (N <= 128, e.g. an adapter down-projection to rank r)
-// would leave most CUs idle with 256-row tiles (M / 256 workgroups): with K % 128 == 0 they take
-// 64 x 32 direct-to-LDS tiles of one wavefront, up to eight workgroups per CU (their K loop is
-// latency-bound, so more independent loops per CU pay: 12 % faster than one 64 x 128 workgroup of
-// four wavefronts per CU), else 64 x 128 register-staged tiles.  DD_GEMM_TILE (0..10) forces a
-// variant for tuning and tests (4: 256 x 256 / 4 waves, 5: 256 x 192 / 4 waves, 6: 256 x 256 /
-// 8 waves, 7: 256 x 192 / 8 waves, 8: 64 x 128 register-staged, 9: 64 x 128 direct-to-LDS,
-// 10: 64 x 32 direct-to-LDS / 1 wave).
 static int num_cus() {
     static int n = 0;
     if (n == 0) {
@@ -1036,19 +847,67 @@ static int num_cus() {
     return n;
 }
 
-static int pick_tile(const GemmArgs& g) {
+// The tile of a bf16 product: one of the ring kernel's (0 .. 2) or a 256-row tile of this file (4 .. 7),
+// and over how many workgroups K is split (residual epilogue on a ring tile only).
+struct Plan {
+    int tile, splits;
+};
+
+// Splits of a residual projection on ring tiles: 4 ways up to 512 rows, 2 up to 2048 (attention output,
+// K 768, N 768: 4.5 / 5.0 / 8.1 us with 4 / 2 / 1 at M 64, 7.6 / 7.4 with 2 / 1 at M 1024; MLP down,
+// K 3072: 7.0 / 10.5 / 16 at M 64, 13.6 with 2 against 13.7 with 4 at M 1024, 20.6 with 2 against 21.9
+// with 1 at M 2000; a split more costs the normalisation 0.5 to 2 us).  Steps of M, not the best per M,
+// and cut by the model's own K, so that a row's sums are the same in calls of similar size and with
+// adapters switched off.
+static int ring_splits(const GemmArgs& g, int max_splits) {
+    const int want = g.M <= 512 ? 4 : g.M <= 2048 ? 2 : 1;
+    const int k = g.k_base > 0 ? g.k_base : g.K;
+    return std::max(1, std::min(std::min(want, max_splits), k / (2 * BK)));   // at least two K-tiles each
+}
+
+// The smallest estimated time.  The 256-row tiles (K % 128 == 0) in whole rounds of workgroups over
+// the CUs: the N width (256 or 192) with the smaller time (a round of 192-wide tiles takes about 0.85
+// of a round of 256-wide ones), in the 8-wavefront form (two wavefronts per SIMD, 2-6 % faster than
+// four wavefronts of twice the sub-tile), per K-tile 1.08 us (192) or 1.79 us (256) and 9 us besides,
+// fitted like the ring tiles' (10 % rms).  Measured at K 768, N 2304 / 3072: ring 11.1 / 11.6 us against
+// 20.3 / 21.0 at M 1024, 29.4 / 37.4 against 21.5 / 24.5 at M 4096; MLP down (K 3072, N 768): 13.6
+// against 57.6 at M 1024, 35.9 against 57.8 at M 4096, 103.7 against 76.8 at M 16384.  Products with
+// N <= 128 (adapter down-projections) leave the 256-row tiles one workgroup per 256 rows: ring tiles
+// only.  A split costs the next normalisation one more slab to read.
+static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
     const char* e = getenv("DD_GEMM_TILE");
     const int forced = e ? atoi(e) : -1;
-    if (((forced >= 4 && forced <= 7) || forced >= 9) && g.K % (2 * BK) != 0) return 0;
-    const bool gathered = g.a_rows || g.m_count || g.c_in;   // only the direct-to-LDS kernels
-    if (forced >= 0 && forced <= 10 && !(gathered && (forced < 4 || forced == 8))) return forced;
-    if (g.N <= 128) return g.K % (2 * BK) == 0 ? 10 : (gathered ? 0 : 8);
-    if (g.K % (2 * BK) != 0) return 0;
-    const int64_t ncu = num_cus();
-    const int64_t tm = (g.M + DM - 1) / DM;
-    const int64_t r256 = (tm * ((g.N + 255) / 256) + ncu - 1) / ncu;
-    const int64_t r192 = (tm * ((g.N + 191) / 192) + ncu - 1) / ncu;
-    return (17 * r192 < 20 * r256) ? 7 : 6;
+    const bool wide_ok = g.K % (2 * BK) == 0;
+    if (g.a_rows) return {forced >= 4 && forced <= 7 ? forced : 6, 1};   // row gather: 256-row tiles only
+    if (forced >= 0 && forced <= 10) {
+        if (forced >= 4 && forced <= 7) return {wide_ok ? forced : 0, 1};
+        return {forced <= 2 ? forced : forced == 3 ? 0 : 1, 1};
+    }
+    const int cus = num_cus();
+    Plan best = {-1, 1};
+    double t_best = 0.0;
+    if (wide_ok && g.N > 128) {
+        const int64_t tm = (g.M + DM - 1) / DM;
+        const int64_t r256 = (tm * ((g.N + 255) / 256) + cus - 1) / cus;
+        const int64_t r192 = (tm * ((g.N + 191) / 192) + cus - 1) / cus;
+        const bool narrow = 17 * r192 < 20 * r256;
+        best.tile = narrow ? 7 : 6;
+        t_best = 9.0 + (double)(g.K / BK) * (narrow ? r192 * 1.08 : r256 * 1.79);
+    }
+    const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits) : 1;
+    const double slab_us = 0.4 + (double)g.M * g.N * 4 / 5e6;
+    for (int tile = 0; tile < 3; ++tile) {
+        const double t = gemm_ring_us((RingTile)tile, g.M, g.N, g.K, sp, cus) + (sp - 1) * slab_us;
+        if (best.tile < 0 || t < t_best) {
+            best = {tile, sp};
+            t_best = t;
+        }
+    }
+    return best;
+}
+
+int gemm_splits(int dtype, int epi, const GemmArgs& g, int max_splits) {
+    return dtype == DD_BF16 ? plan_tile(g, epi, max_splits).splits : 1;
 }
 
 template <int EPI, int ROLE, int TBN, int WGM, int WGN, int DMR = DM>
@@ -1072,7 +931,7 @@ static void launch_dl(const GemmArgs& g, hipStream_t s) {
 template <int EPI, int ROLE>
 static void launch_epi(int dtype, const GemmArgs& g, hipStream_t s) {
     if (dtype == DD_BF16) {
-        int tile = g.tile_hint > 0 ? g.tile_hint - 1 : pick_tile(g);
+        int tile = g.tile_hint > 0 ? g.tile_hint - 1 : plan_tile(g, EPI, std::max(g.splits, 1)).tile;
         // the ring instance of the 256 x 192 tile takes no gathered rows and no separate residual
         // input: the four-wavefront form
         if (tile == 7 && (g.a_rows || g.c_in) && dl_ring<EPI, DLShape<192, 4, 2>>()) tile = 5;
@@ -1081,13 +940,7 @@ static void launch_epi(int dtype, const GemmArgs& g, hipStream_t s) {
             case 6: launch_dl<EPI, ROLE, 256, 2, 4>(g, s); break;
             case 5: launch_dl<EPI, ROLE, 192, 2, 2>(g, s); break;
             case 4: launch_dl<EPI, ROLE, 256, 2, 2>(g, s); break;
-            case 9: launch_dl<EPI, ROLE, 128, 1, 4, 64>(g, s); break;
-            case 10: launch_dl<EPI, ROLE, 32, 1, 1, 64>(g, s); break;
-            case 8: launch_tile<64, 128, EPI>(g, s); break;
-            case 3: launch_tile<256, 256, EPI>(g, s); break;
-            case 2: launch_tile<256, 128, EPI>(g, s); break;
-            case 1: launch_tile<128, 256, EPI>(g, s); break;
-            default: launch_tile<128, 128, EPI>(g, s); break;
+            default: launch_gemm_ring((RingTile)tile, EPI, g, s); break;
         }
     } else {
         const int tm = (g.M + FT - 1) / FT, tn = (g.N + FT - 1) / FT;

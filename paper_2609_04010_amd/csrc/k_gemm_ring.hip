@@ -1,0 +1,392 @@
+// Dense layers on few rows, or with K not a multiple of 128: C = A W^T (+ epilogue), bf16 operands,
+// the operand layouts of k_gemm.hip.
+//
+// The 256-row tiles of k_gemm.hip leave most CUs idle when M is small (M = 1024, N = 768: 16 tiles
+// for 256 CUs), and each tile then walks its whole K loop alone.  Here the tiles are 128 x 128 to
+// 64 x 64, so the same product makes 48 to 192 of them, and the residual layers (attention output,
+// MLP down) also split K over workgroups: split 0 adds its part and the bias to the residual row in
+// place, the others write fp32 partials into slabs of free workspace, which the normalisation that
+// reads the row next adds first (in slab order, so results do not depend on timing).
+//
+// With so little work per CU the K loop is bound by the latency of its loads, not by the matrix
+// cores: operand K-tiles of 64 go global -> LDS (global_load_lds_dwordx4, XOR-swizzled 128-byte rows
+// as in k_gemm.hip) through a ring of NST stages, so NST - 1 K-tiles are in flight while one is
+// computed; each K-tile waits for its own loads by count and costs one barrier.
+//
+// Measured (MI355X, weights of 12 layers in turn; 256-row tiles -> ring): M 1024, d 768: QKV 20.3 ->
+// 11.1 us, attention output 22.5 -> 7.6, MLP up 21.0 -> 11.6, MLP down 57.6 -> 13.6; M 64: 19.7 -> 6.4,
+// 19.5 -> 4.5, 19.5 -> 6.4, 53.4 -> 7.5.  What bounds it now: at M 64 the K loop, 0.21 us per K-tile
+// (fragment reads, loads into LDS and four dependent MFMAs); at M 1024 the operand stream through
+// L2, 16 TB/s.  Against the register-staged 128 x 128 tiles this kernel replaced for K % 128 != 0:
+// M 1320, N 3072, K 832 24.0 -> 13.3 us, M 16384 143.5 -> 134.4.
+//
+// K needs only K % 8 == 0: the chunks of the last K-tile past K are loaded from the row's first chunk
+// (in bounds) and their fragments are replaced by zeros.
+#include <math.h>
+
+#include <algorithm>
+#include <mutex>
+#include <type_traits>
+
+#include "gemm_common.h"
+#include "kernels.h"
+
+namespace dd {
+
+// BM x BN x 64 tiles over WGM x WGN wavefronts of MB x NB 32x32 MFMA blocks, NST stages
+template <int BM_, int BN_, int WGM_, int WGN_, int NST_> struct RingShape {
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NST = NST_;
+    static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
+    static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
+    static constexpr int NA = BM / 8 / NW, NWL = BN / 8 / NW, NL = NA + NWL;   // 1 KB loads per wave and K-tile
+    static constexpr int STAGE = (BM + BN) * BK;
+    static constexpr size_t LDS = (size_t)NST * STAGE * sizeof(bf16_t);
+    static constexpr int WG_PER_CU = LDS * 2 <= 160 * 1024 ? 2 : 1;
+    static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && WM % 32 == 0 && WN % 32 == 0, "split");
+    static_assert(LDS <= 160 * 1024 && NST >= 2 && (NST - 2) * NL < 64, "stages; the wait counts the loads");
+    static_assert((size_t)NW * 32 * 32 * 4 <= LDS, "epilogue staging");
+};
+
+// s_waitcnt vmcnt(N) alone
+template <int N> DD_DEV void wait_vm() { __builtin_amdgcn_s_waitcnt(0x3F70 | (N & 15) | ((N >> 4) << 14)); }
+
+template <int EPI, class S>
+__global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_CU * S::NW / 4 : 1) void gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+    constexpr int MB = S::MB, NB = S::NB, NA = S::NA, NWL = S::NWL, NST = S::NST;
+    constexpr int AROWS = S::BM / S::NW, WROWS = S::BN / S::NW;
+    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / S::WGN, wn = wave % S::WGN;
+    int M = g.M;
+    if (g.m_count) {
+        M = *g.m_count;
+        tiles_m = (M + S::BM - 1) / S::BM;
+        if (g.m_gate > 0 && ((M > g.m_gate) == (g.m_side != 0))) return;   // the other launch's rows
+    }
+    // splits outermost: an XCD's run of work indices then covers one K range of neighbouring tiles
+    const int tiles = tiles_m * tiles_n, nsplit = g.splits > 1 ? g.splits : 1, work = tiles * nsplit;
+    if ((int)blockIdx.x >= work) return;
+    const int id = xcd_linear(blockIdx.x, work);
+    const int split = id / tiles;
+    int tm, tn;
+    {
+        const int t = id - split * tiles, in_group = 8 * tiles_n, grp = t / in_group, first = grp * 8;
+        const int gsz = min(tiles_m - first, 8), r = t - grp * in_group;
+        tm = first + r % gsz;
+        tn = r / gsz;
+    }
+    const int m0 = tm * S::BM, n0 = tn * S::BN;
+    const bf16_t* A = (const bf16_t*)g.A;
+    const bf16_t* W = (const bf16_t*)g.W;
+    const int nkt = (g.K + BK - 1) / BK, klast = g.K - (nkt - 1) * BK;   // valid k of the last K-tile
+    const int nkb = g.k_base > 0 ? (g.k_base + BK - 1) / BK : nkt;   // K-tiles that are cut evenly
+    const int kt0 = split * nkb / nsplit, kt1 = split + 1 == nsplit ? nkt : (split + 1) * nkb / nsplit;
+
+    // This lane's 16-byte slot of row r holds K-chunk (lane % 8) ^ ((r >> 1) & 7).  Byte offsets from
+    // the tile's first row (under 256 rows, so 32 bits), and the chunk's first k in the K-tile.
+    const char* Ab = (const char*)(A + (int64_t)m0 * g.lda);
+    const char* Wb = (const char*)(W + (int64_t)n0 * g.ldw);
+    uint32_t offA[NA], offW[NWL];
+    int chA[NA], chW[NWL];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int rl = AROWS * wave + 8 * i + (lane >> 3);
+        chA[i] = ((lane & 7) ^ ((rl >> 1) & 7)) * 8;
+        offA[i] = (uint32_t)(min(rl, M - 1 - m0) * (int)g.lda + chA[i]) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < NWL; ++i) {
+        const int rl = WROWS * wave + 8 * i + (lane >> 3);
+        chW[i] = ((lane & 7) ^ ((rl >> 1) & 7)) * 8;
+        offW[i] = (uint32_t)(min(rl, g.N - 1 - n0) * (int)g.ldw + chW[i]) * 2u;
+    }
+    auto load = [&](int t, int stage, auto whole_c) {
+        bf16_t* st = smem + stage * S::STAGE;
+        const char* ap = Ab + (int64_t)t * (BK * 2);
+        const char* wp = Wb + (int64_t)t * (BK * 2);
+        if (!decltype(whole_c)::value && t == nkt - 1 && klast < BK) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                __builtin_amdgcn_global_load_lds((gbl_void*)(ap + (offA[i] - (chA[i] < klast ? 0 : chA[i] * 2))),
+                                                 (lds_void*)(st + (AROWS * wave + 8 * i) * BK), 16, 0, 0);
+#pragma unroll
+            for (int i = 0; i < NWL; ++i)
+                __builtin_amdgcn_global_load_lds((gbl_void*)(wp + (offW[i] - (chW[i] < klast ? 0 : chW[i] * 2))),
+                                                 (lds_void*)(st + (S::BM + WROWS * wave + 8 * i) * BK), 16, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                __builtin_amdgcn_global_load_lds((gbl_void*)(ap + offA[i]),
+                                                 (lds_void*)(st + (AROWS * wave + 8 * i) * BK), 16, 0, 0);
+#pragma unroll
+            for (int i = 0; i < NWL; ++i)
+                __builtin_amdgcn_global_load_lds((gbl_void*)(wp + offW[i]),
+                                                 (lds_void*)(st + (S::BM + WROWS * wave + 8 * i) * BK), 16, 0, 0);
+        }
+    };
+
+    f32x16 acc[NB][MB];
+    if constexpr (EPI == EPI_BIAS_RESID) {
+        // split 0 starts from the residual row: h is C itself, or the rows of c_in that c_rows lists
+        const float* C = g.c_in ? g.c_in : (const float*)g.C;
+        int64_t hrow[MB];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            hrow[j] = min(m0 + wm * S::WM + j * 32 + (lane & 31), M - 1);
+            if (g.c_in && g.c_rows) hrow[j] = g.c_rows[hrow[j]];
+        }
+        // rows past M and columns past N (N % 4 == 0) read a neighbour inside the matrix and are not
+        // stored: no test between the loads, so that all are in flight together
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int j4 = 0; j4 < 4; ++j4) {
+                    const int n = min(n0 + wn * S::WN + i * 32 + 8 * j4 + 4 * (lane >> 5), g.N - 4);
+                    float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (split == 0) h = *(const float4*)(C + hrow[j] * g.ldc + n);
+                    acc[i][j][4 * j4] = h.x;
+                    acc[i][j][4 * j4 + 1] = h.y;
+                    acc[i][j][4 * j4 + 2] = h.z;
+                    acc[i][j][4 * j4 + 3] = h.w;
+                }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    }
+
+    // Two sets of fragments: a K-tile's are read while the MFMAs of the one before run (one set, read
+    // after the barrier, left the LDS reads, the LDS writes of the loads and the MFMAs one after the
+    // other: the wavefronts of a workgroup pass the barrier together).
+    constexpr int KS = BK / 16;
+    struct Frags {
+        bf16x8 a[KS][MB], w[KS][NB];
+    };
+    const int frow = lane & 31, fsw = (lane >> 1) & 7, fhalf = lane >> 5;
+    auto read = [&](Frags& f, int stage) {
+        const bf16_t* sA = smem + stage * S::STAGE + (wm * S::WM + frow) * BK;
+        const bf16_t* sW = smem + stage * S::STAGE + (S::BM + wn * S::WN + frow) * BK;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const int slot = ((2 * kk + fhalf) ^ fsw) * 8;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) f.a[kk][i] = *(const bf16x8*)&sA[32 * i * BK + slot];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) f.w[kk][i] = *(const bf16x8*)&sW[32 * i * BK + slot];
+        }
+    };
+    auto mfmas = [&](const Frags& f) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[kk][nb], f.a[kk][mb], acc[nb][mb], 0, 0, 0);
+    };
+    auto clear_past = [&](Frags& f) {   // the last K-tile's fragments past K
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const bool past = (2 * kk + fhalf) * 8 >= klast;
+            const bf16x8 z = {};
+#pragma unroll
+            for (int i = 0; i < MB; ++i) f.a[kk][i] = past ? z : f.a[kk][i];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) f.w[kk][i] = past ? z : f.w[kk][i];
+        }
+    };
+    // this lane's loads of K-tile t landed (`ahead` K-tiles after it may be in flight), then everyone's
+    auto publish = [&](int ahead) {
+        if (ahead >= NST - 2) wait_vm<(NST - 2) * S::NL>();
+        else if (NST > 3 && ahead == NST - 3) wait_vm<(NST > 3 ? NST - 3 : 0) * S::NL>();
+        else if (NST > 4 && ahead == NST - 4) wait_vm<(NST > 4 ? NST - 4 : 0) * S::NL>();
+        else if (NST > 5 && ahead == NST - 5) wait_vm<(NST > 5 ? NST - 5 : 0) * S::NL>();
+        else wait_vm<0>();
+        asm volatile("s_barrier" ::: "memory");
+    };
+
+    const int nt = kt1 - kt0;
+#pragma unroll
+    for (int p = 0; p < NST - 1; ++p)
+        if (p < nt) load(kt0 + p, p, std::false_type{});
+    Frags f0, f1;
+    publish(min(nt - 1, NST - 2));
+    read(f0, 0);
+    int rd = 1, ld = NST - 1;   // stages of K-tile t + 1 and of K-tile t + NST - 1
+    // K-tile t from `cur`; K-tile t + 1 is read into `nxt` and K-tile t + NST - 1 loaded into the
+    // stage of K-tile t - 1, whose fragments every wavefront had waited for before this barrier.
+    // `steady`: both exist, and nothing branches, so that the compiler's waits before the MFMAs count
+    // the reads of `nxt` as still in flight.
+    auto step = [&](int t, Frags& cur, Frags& nxt, auto steady_c) {
+        constexpr bool steady = decltype(steady_c)::value;
+        if (steady || t + 1 < nt) {
+            if constexpr (steady) {
+                wait_vm<(NST - 3) * S::NL>();
+                asm volatile("s_barrier" ::: "memory");
+            } else {
+                publish(min(nt - 2 - t, NST - 3));
+            }
+            read(nxt, rd);
+            if (steady || t + NST - 1 < nt) load(kt0 + t + NST - 1, ld, steady_c);
+            rd = rd + 1 == NST ? 0 : rd + 1;
+            ld = ld + 1 == NST ? 0 : ld + 1;
+            __builtin_amdgcn_sched_barrier(0);
+        } else if (kt1 == nkt && klast < BK) {
+            clear_past(cur);
+        }
+        mfmas(cur);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int t = 0;
+    for (; t + NST + 1 < nt; t += 2) {   // the last K-tile, which may be ragged, is loaded below
+        step(t, f0, f1, std::true_type{});
+        step(t + 1, f1, f0, std::true_type{});
+    }
+    for (; t < nt; t += 2) {
+        step(t, f0, f1, std::false_type{});
+        if (t + 1 < nt) step(t + 1, f1, f0, std::false_type{});
+    }
+    __syncthreads();   // the stages become the epilogue's staging area
+
+    if constexpr (EPI == EPI_BIAS_RESID) {
+        float* cst = (float*)smem + wave * (32 * 32);
+        float* C = split == 0 ? (float*)g.C : g.slab[split - 1];
+        const bf16_t* bias = (const bf16_t*)g.bias;
+        const int rr = lane >> 3, c4 = (lane & 7) * 4;
+        float bv[NB][4];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                bv[nb][e] = split == 0 ? bf16_to_f32(bias[min(n0 + wn * S::WN + nb * 32 + c4 + e, g.N - 1)]) : 0.f;
+#pragma unroll
+        for (int b = 0; b < MB * NB; ++b) {
+            const int mb = b % MB, nb = b / MB;
+            const int wr = lane & 31;
+#pragma unroll
+            for (int j4 = 0; j4 < 4; ++j4) {
+                const int slot = (2 * j4 + (lane >> 5)) ^ ((wr >> 1) & 7);
+                *(float4*)&cst[wr * 32 + slot * 4] = make_float4(acc[nb][mb][4 * j4], acc[nb][mb][4 * j4 + 1],
+                                                                 acc[nb][mb][4 * j4 + 2], acc[nb][mb][4 * j4 + 3]);
+            }
+            const int n = n0 + wn * S::WN + nb * 32 + c4;
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int r = rr + 8 * it;
+                const float4 v = *(const float4*)&cst[r * 32 + (((c4 >> 2) ^ ((r >> 1) & 7)) * 4)];
+                const int m = m0 + wm * S::WM + mb * 32 + r;
+                if (m < M && n < g.N)
+                    *(f32x4*)(C + (int64_t)m * g.ldc + n) =
+                        f32x4{v.x + bv[nb][0], v.y + bv[nb][1], v.z + bv[nb][2], v.w + bv[nb][3]};
+            }
+        }
+    } else {
+        // one 32 x 32 block at a time through this wavefront's staging rows (80 bytes), then 16-byte
+        // pieces of 64-byte row segments
+        constexpr int CSTR = 40;
+        bf16_t* cst = smem + wave * (32 * CSTR);
+        bf16_t* C = (bf16_t*)g.C;
+        const bf16_t* bias = (const bf16_t*)g.bias;
+        float b4[EPI == EPI_BIAS || EPI == EPI_BIAS_GELU ? NB : 1][16];
+        if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    b4[nb][e] = bf16_to_f32(bias[min(n0 + wn * S::WN + nb * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3), g.N - 1)]);
+        }
+#pragma unroll
+        for (int b = 0; b < MB * NB; ++b) {
+            const int mb = b % MB, nb = b / MB;
+            float rs = 1.f;
+            if constexpr (EPI == EPI_GATE) rs = gate_row_scale(g, m0 + wm * S::WM + mb * 32 + (lane & 31));
+#pragma unroll
+            for (int j4 = 0; j4 < 4; ++j4) {
+                float o[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float x = acc[nb][mb][4 * j4 + e];
+                    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) x += b4[nb][4 * j4 + e];
+                    if constexpr (EPI == EPI_BIAS_GELU) x = gelu_tanh(x);
+                    if constexpr (EPI == EPI_GATE) x *= rs;
+                    o[e] = x;
+                }
+                uint2 pk;
+                pk.x = pack_bf16x2(o[0], o[1]);
+                pk.y = pack_bf16x2(o[2], o[3]);
+                *(uint2*)&cst[(lane & 31) * CSTR + 8 * j4 + 4 * (lane >> 5)] = pk;
+            }
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int r = 16 * it + (lane >> 2), c = (lane & 3) * 8;
+                const uint4 v = *(const uint4*)&cst[r * CSTR + c];
+                const int m = m0 + wm * S::WM + mb * 32 + r, n = n0 + wn * S::WN + nb * 32 + c;
+                if (m >= M || n >= g.N) continue;
+                bf16_t* dst = C + (int64_t)m * g.ldc + n;
+                if (n + 7 < g.N) {
+                    *(u32x4*)dst = u32x4{v.x, v.y, v.z, v.w};
+                } else {
+                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+                    for (int e = 0; n + e < g.N; ++e) dst[e] = (bf16_t)((w[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
+                }
+            }
+        }
+    }
+}
+
+
+template <int EPI, class S>
+static void launch_shape(const GemmArgs& g, hipStream_t s) {
+    const int tm = ((g.m_rows > 0 ? g.m_rows : g.M) + S::BM - 1) / S::BM, tn = (g.N + S::BN - 1) / S::BN;
+    static std::once_flag once;   // opt-in to more than 64 KB of LDS per workgroup
+    std::call_once(once, [] {
+        (void)hipFuncSetAttribute((const void*)gemm_ring_kernel<EPI, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)S::LDS);
+    });
+    launch_k((gemm_ring_kernel<EPI, S>), dim3(tm * tn * std::max(g.splits, 1)), dim3(S::THREADS), S::LDS, s, g, tm, tn);
+}
+
+template <int EPI>
+static void launch_epi(RingTile tile, const GemmArgs& g, hipStream_t s) {
+    switch (tile) {
+        case RING_128: launch_shape<EPI, RingShape<128, 128, 4, 2, 4>>(g, s); break;
+        case RING_64_DEEP: launch_shape<EPI, RingShape<64, 64, 2, 2, 4>>(g, s); break;
+        default: launch_shape<EPI, RingShape<64, 64, 2, 2, 3>>(g, s); break;
+    }
+}
+
+void launch_gemm_ring(RingTile tile, int epi, const GemmArgs& g, hipStream_t s) {
+    switch (epi) {
+        case EPI_BIAS: launch_epi<EPI_BIAS>(tile, g, s); break;
+        case EPI_BIAS_GELU: launch_epi<EPI_BIAS_GELU>(tile, g, s); break;
+        case EPI_BIAS_RESID: launch_epi<EPI_BIAS_RESID>(tile, g, s); break;
+        case EPI_GATE: launch_epi<EPI_GATE>(tile, g, s); break;
+        default: launch_epi<EPI_PLAIN>(tile, g, s); break;
+    }
+}
+
+// Estimated time (us) of C [M][N] = A W^T over K on a ring tile.  Rounds of up to P workgroups per CU,
+// each a fixed part and per K-tile the larger of its own latency and the share of the CU that its
+// co-residents leave it.  Fitted to 17 products (N 64..4096, K 256..4096) at 16 row counts from 64 to
+// 16384, 1 to 4 splits, the weights rotating as the layers of a model do: 9 to 13 % rms.
+double gemm_ring_us(RingTile tile, int64_t M, int64_t N, int64_t K, int splits, int cus) {
+    const int b = tile == RING_128 ? 128 : 64;
+    const int P = tile == RING_128 ? 1 : tile == RING_64_DEEP ? 2 : 3;
+    const double t0 = tile == RING_128 ? 0.0 : tile == RING_64_DEEP ? 1.3 : 0.5;
+    const double tw = tile == RING_128 ? 6.3 : tile == RING_64_DEEP ? 2.9 : 3.3;
+    const double lat = tile == RING_128 ? 0.49 : tile == RING_64_DEEP ? 0.21 : 0.41;
+    const double share = tile == RING_128 ? 0.49 : tile == RING_64_DEEP ? 0.214 : 0.241;
+    const int64_t wg = ((M + b - 1) / b) * ((N + b - 1) / b) * splits;
+    const int64_t kt = ((K + BK - 1) / BK + splits - 1) / splits;
+    const int64_t full = wg / ((int64_t)cus * P), rest = wg - full * cus * P;
+    double t = t0 + (double)full * (tw + (double)kt * std::max(lat, P * share));
+    if (rest > 0) t += tw + (double)kt * std::max(lat, (double)((rest + cus - 1) / cus) * share);
+    return t;
+}
+
+}  // namespace dd

@@ -88,15 +88,29 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* z, int64_t
 template <typename W, int NPL, bool RMS>
 __global__ __launch_bounds__(256) void ln_kernel(const float* h, int64_t rows, const W* g,
                                                  const W* b, float eps, W* out, int64_t ldo,
-                                                 const int32_t* m_count) {
+                                                 const int32_t* m_count, LnSlabs add) {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (m_count) rows = min(rows, (int64_t)*m_count);
+    if (m_count) {
+        if (add.gate > 0 && *m_count > add.gate) add.n = 0;
+        rows = min(rows, (int64_t)*m_count);
+    }
     if (row >= rows) return;
     constexpr int d = NPL * 64;
     float x[NPL];
 #pragma unroll
     for (int k = 0; k < NPL; ++k) x[k] = h[row * d + lane + 64 * k];
+    if (add.n > 0) {   // partials of a split projection, in slab order
+#pragma unroll
+        for (int i = 0; i < MAX_SPLITS - 1; ++i) {
+            if (i >= add.n) break;
+#pragma unroll
+            for (int k = 0; k < NPL; ++k) x[k] += add.slab[i][row * d + lane + 64 * k];
+        }
+        if (add.h_out)
+#pragma unroll
+            for (int k = 0; k < NPL; ++k) add.h_out[row * d + lane + 64 * k] = x[k];
+    }
     ln_row<W, NPL, RMS>(x, lane, d, g, b, eps, out + row * ldo);
 }
 
@@ -161,10 +175,13 @@ template <int NV, bool RMS>
 __global__ __launch_bounds__(256) void ln_bf16_v4_kernel(const float* h, int64_t rows,
                                                          const bf16_t* g, const bf16_t* b,
                                                          float eps, bf16_t* out, int64_t ldo,
-                                                         const int32_t* m_count) {
+                                                         const int32_t* m_count, LnSlabs add) {
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * LN_RPW;
     const int lane = threadIdx.x & 63;
-    if (m_count) rows = min(rows, (int64_t)*m_count);
+    if (m_count) {
+        if (add.gate > 0 && *m_count > add.gate) add.n = 0;
+        rows = min(rows, (int64_t)*m_count);
+    }
     if (row0 >= rows) return;
     constexpr int d = NV * 256;
     float4 x[LN_RPW][NV];
@@ -174,6 +191,28 @@ __global__ __launch_bounds__(256) void ln_bf16_v4_kernel(const float* h, int64_t
         const float4* hr = (const float4*)(h + (row0 + r) * d);
 #pragma unroll
         for (int k = 0; k < NV; ++k) x[r][k] = hr[lane + 64 * k];
+        if (add.n > 0) {   // partials of a split projection, in slab order
+            float4 p[MAX_SPLITS - 1][NV];
+#pragma unroll
+            for (int i = 0; i < MAX_SPLITS - 1; ++i)
+                if (i < add.n) {
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) p[i][k] = ((const float4*)(add.slab[i] + (row0 + r) * d))[lane + 64 * k];
+                }
+#pragma unroll
+            for (int i = 0; i < MAX_SPLITS - 1; ++i)
+                if (i < add.n) {
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) {
+                        x[r][k].x += p[i][k].x; x[r][k].y += p[i][k].y; x[r][k].z += p[i][k].z; x[r][k].w += p[i][k].w;
+                    }
+                }
+            if (add.h_out) {
+                float4* ho = (float4*)(add.h_out + (row0 + r) * d);
+#pragma unroll
+                for (int k = 0; k < NV; ++k) ho[lane + 64 * k] = x[r][k];
+            }
+        }
     }
     uint2 gg[NV], bb[NV];
     load_gain_shift<NV, RMS>(g, b, lane, gg, bb);
@@ -283,13 +322,13 @@ dd_status launch_embed_ln(int dtype, int norm, const int32_t* z, int64_t rows, i
 
 template <typename W, bool RMS>
 dd_status launch_ln_t(const float* h, int64_t rows, int d, const void* g, const void* b, float eps,
-                      void* out, int64_t ldo, hipStream_t s, const int32_t* m_count) {
+                      void* out, int64_t ldo, hipStream_t s, const int32_t* m_count, const LnSlabs& add) {
     const dim3 grid((unsigned)ceil_div(rows, 4)), blk(256);
     switch (d / 64) {
 #define X(n)                                                                                     \
     case n:                                                                                      \
         launch_k((ln_kernel<W, n, RMS>), grid, blk, 0, s, h, rows, (const W*)g,       \
-                           (const W*)b, eps, (W*)out, ldo, m_count);                             \
+                           (const W*)b, eps, (W*)out, ldo, m_count, add);                        \
         break;
         DD_NPL_CASES(X)
 #undef X
@@ -300,15 +339,16 @@ dd_status launch_ln_t(const float* h, int64_t rows, int d, const void* g, const 
 
 template <bool RMS>
 void launch_ln_v4(int d, dim3 grid, const float* h, int64_t rows, const bf16_t* g, const bf16_t* b,
-                  float eps, bf16_t* o, int64_t ldo, hipStream_t s, const int32_t* mc) {
+                  float eps, bf16_t* o, int64_t ldo, hipStream_t s, const int32_t* mc, const LnSlabs& add) {
     const dim3 blk(256);
-    if (d == 768) launch_k((ln_bf16_v4_kernel<3, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc);
-    else if (d == 1024) launch_k((ln_bf16_v4_kernel<4, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc);
-    else launch_k((ln_bf16_v4_kernel<8, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc);
+    if (d == 768) launch_k((ln_bf16_v4_kernel<3, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc, add);
+    else if (d == 1024) launch_k((ln_bf16_v4_kernel<4, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc, add);
+    else launch_k((ln_bf16_v4_kernel<8, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc, add);
 }
 
 dd_status launch_ln(int dtype, int norm, const float* h, int64_t rows, int d, const void* g, const void* b,
-                    float eps, void* out, int64_t ldo, hipStream_t s, const int32_t* m_count) {
+                    float eps, void* out, int64_t ldo, hipStream_t s, const int32_t* m_count, const LnSlabs* slabs) {
+    const LnSlabs add = slabs ? *slabs : LnSlabs{};
     const bool rms = norm == DD_NORM_RMS;
     ProfScope ps(KC_LN, s);
     if (dtype == DD_BF16 && (d == 768 || d == 1024 || d == 2048) && ldo % 4 == 0) {
@@ -316,15 +356,15 @@ dd_status launch_ln(int dtype, int norm, const float* h, int64_t rows, int d, co
         const bf16_t* gg = (const bf16_t*)g;
         const bf16_t* bb = (const bf16_t*)b;
         bf16_t* o = (bf16_t*)out;
-        if (rms) launch_ln_v4<true>(d, grid, h, rows, gg, bb, eps, o, ldo, s, m_count);
-        else launch_ln_v4<false>(d, grid, h, rows, gg, bb, eps, o, ldo, s, m_count);
+        if (rms) launch_ln_v4<true>(d, grid, h, rows, gg, bb, eps, o, ldo, s, m_count, add);
+        else launch_ln_v4<false>(d, grid, h, rows, gg, bb, eps, o, ldo, s, m_count, add);
         return launch_status("layernorm");
     }
     if (dtype == DD_BF16)
-        return rms ? launch_ln_t<bf16_t, true>(h, rows, d, g, b, eps, out, ldo, s, m_count)
-                   : launch_ln_t<bf16_t, false>(h, rows, d, g, b, eps, out, ldo, s, m_count);
-    return rms ? launch_ln_t<float, true>(h, rows, d, g, b, eps, out, ldo, s, m_count)
-               : launch_ln_t<float, false>(h, rows, d, g, b, eps, out, ldo, s, m_count);
+        return rms ? launch_ln_t<bf16_t, true>(h, rows, d, g, b, eps, out, ldo, s, m_count, add)
+                   : launch_ln_t<bf16_t, false>(h, rows, d, g, b, eps, out, ldo, s, m_count, add);
+    return rms ? launch_ln_t<float, true>(h, rows, d, g, b, eps, out, ldo, s, m_count, add)
+               : launch_ln_t<float, false>(h, rows, d, g, b, eps, out, ldo, s, m_count, add);
 }
 
 bool ln_supported(int d) {

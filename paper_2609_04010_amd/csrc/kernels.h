@@ -54,6 +54,10 @@ struct PostArgs {
 enum Epi { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESID = 2, EPI_PLAIN = 3, EPI_GATE = 4, EPI_LSE = 5,
            EPI_LSE_CDF = 6 };
 
+constexpr int MAX_SPLITS = 4;
+// the ring kernel's 64 x 64 tile with four stages, as a GemmArgs::tile_hint (+ 1) for few listed rows
+constexpr int TILE_TAIL = 1;
+
 struct GemmArgs {
     const void* A;   // [M][K], row stride lda
     int64_t lda;
@@ -92,6 +96,17 @@ struct GemmArgs {
     // or *m_count <= m_gate (m_side 1); two launches with the two sides pick a tile shape by the
     // device-side row count
     int m_gate, m_side;
+    // m_rows > 0 (with m_count): the caller's bound on *m_count where the launch does its work (the
+    // grid is sized for it instead of M)
+    int m_rows;
+    // EPI_BIAS_RESID on the ring kernel: K is split over `splits` workgroups per tile (0 or 1: not
+    // split).  Split 0 updates C; split s > 0 writes its fp32 partial to slab[s - 1] ([M][ldc]),
+    // which the normalisation reading C next has to add.
+    int splits;
+    float* slab[MAX_SPLITS - 1];
+    // the split cuts the first k_base of K (0: all of it) evenly; the last split takes the rest
+    // (adapter columns)
+    int k_base;
 };
 
 struct AttnArgs {
@@ -149,10 +164,19 @@ dd_status launch_embed_ln(int dtype, int norm, const int32_t* z, int64_t rows, i
                           const void* tok, const void* pos, const float* temb, const void* g,
                           const void* b, float eps, float* h, void* xln, int64_t ldo, int32_t* err,
                           hipStream_t s);
+// Partials of a split residual projection: a row is h + slab[0] + .. + slab[n - 1] (each [rows][d]),
+// written back to h_out (nullable) and normalised.  With m_count, only while *m_count <= gate
+// (gate 0: always): above it the projection was not split.
+struct LnSlabs {
+    const float* slab[MAX_SPLITS - 1];
+    int n, gate;
+    float* h_out;
+};
 // out rows have stride ldo (elements) >= d
 // m_count (device, nullable): only rows < *m_count are normalised (rows bounds the grid)
 dd_status launch_ln(int dtype, int norm, const float* h, int64_t rows, int d, const void* g, const void* b,
-                    float eps, void* out, int64_t ldo, hipStream_t s, const int32_t* m_count = nullptr);
+                    float eps, void* out, int64_t ldo, hipStream_t s, const int32_t* m_count = nullptr,
+                    const LnSlabs* add = nullptr);
 bool ln_supported(int d);
 dd_status launch_gemm(int dtype, int epi, int cls, const GemmArgs& g, hipStream_t s);
 dd_status launch_attn(int dtype, const AttnArgs& a, hipStream_t s);
@@ -162,6 +186,9 @@ bool attn_supported(int dtype, int dh);
 // by *pre unmasks (the others stay masked and need no logits)
 dd_status launch_compact(const int32_t* z, int64_t M, int32_t mask_id, int32_t* idx, int32_t* count,
                          hipStream_t s, int L = 0, int32_t* seq = nullptr, const PostArgs* pre = nullptr);
+// Over how many workgroups launch_gemm would split K for this product, at most max_splits (1: not
+// split; a caller that takes more sets g.splits and g.slab and adds the slabs afterwards).
+int gemm_splits(int dtype, int epi, const GemmArgs& g, int max_splits);
 bool gemm_gather_supported(int dtype, int K);
 // the EPI_LSE epilogue (group log-sum-exps beside the logits) runs for this dtype and K
 bool gemm_lse_supported(int dtype, int K);

@@ -1,0 +1,67 @@
+"""Products on few rows (64 x 64 and 128 x 128 ring tiles, K split over workgroups): the forward pass
+against the oracle at the row counts where the tile or the split changes (1, 64 and 65 rows, 512 and
+513, 2048 and 2049), at K-tiles that are ragged (d_mlp and adapter ranks that are no multiple of 64),
+and the loop's listed rows against the full path.
+
+Bar: as for every forward pass, max |dlogit| <= 5e-2 in bf16 (measured here up to 1.3e-2)."""
+import numpy as np
+import pytest
+
+import workloads
+from oracle import forward as oforward, params as oparams
+from tests.gpu_util import dev_i32, say, torch_or_skip
+
+from paper_2609_04010_amd import _lib as dd
+
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-2
+
+CASES = [
+    # overrides of the GPT-2-small shape, B, L
+    (dict(n_layers=2, vocab=300), 1, 1),
+    (dict(n_layers=2, vocab=300), 1, 64),
+    (dict(n_layers=2, vocab=300), 5, 13),
+    (dict(n_layers=1, vocab=300), 2, 256),
+    (dict(n_layers=1, vocab=300), 3, 171),
+    (dict(n_layers=1, vocab=300), 8, 256),
+    (dict(n_layers=1, vocab=300), 3, 683),
+    # one ragged K-tile (40, 8 and 56 of 64), split four and two ways and not split
+    (dict(n_layers=1, vocab=300, d_mlp=1000), 1, 70),
+    (dict(n_layers=1, vocab=300, d_mlp=520), 3, 200),
+    (dict(n_layers=1, vocab=300, d_mlp=120), 5, 500),
+    (dict(n_layers=2, vocab=300, lora_rank=8, lora_alpha=16.0), 1, 90),
+    (dict(n_layers=1, vocab=300, lora_rank=72, lora_alpha=144.0), 3, 250),
+    # other widths (normalisation by the row-per-wavefront kernels), K of one to eight K-tiles
+    (dict(n_layers=2, vocab=300, d_model=64, n_heads=1, d_mlp=256), 2, 40),
+    (dict(n_layers=2, vocab=300, d_model=256, n_heads=4, d_mlp=256), 2, 100),
+    (dict(n_layers=2, vocab=300, d_model=512, n_heads=8, d_mlp=2048, norm="rms"), 2, 150),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"B{c[1]}-L{c[2]}-" + "-".join(f"{k}{v}" for k, v in c[0].items()))
+def test_forward_on_few_rows_matches_oracle(case):
+    torch = torch_or_skip()
+    over, B, L = case
+    say("few rows", case)
+    cfg = workloads.model_cfg(2, max_len=L, **over)
+    P = oparams.init_params(cfg, 41)
+    blob = dd.pack_params(cfg, oparams.storage_tensors(cfg, P))
+    buf = torch.zeros(blob.size, dtype=torch.uint8, device="cuda")
+    dd.init_params(cfg, buf, host_blob=blob)
+    z = workloads.masked_state(77, B, L, cfg["vocab"], 0.5)
+    ld = int(dd.logits_ld(cfg["vocab"]))
+    logits = torch.zeros((B * L, ld), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((dd.workspace_bytes(cfg, B, L),), 0xFF, dtype=torch.uint8, device="cuda")   # NaN bits
+    dd.workspace_reset(ws)
+    zd = dev_i32(torch, z.reshape(-1))
+    dd.denoise_forward(cfg, buf, zd, B, L, 0.5, logits, ld, ws)
+    first = logits.clone()
+    dd.denoise_forward(cfg, buf, zd, B, L, 0.5, logits, ld, ws)
+    assert torch.equal(first, logits)          # sums in a fixed order
+    got = first[:, :cfg["vocab"]].float().cpu().numpy().reshape(B, L, -1)
+    assert dd.read_device_error(ws[:4].view(torch.int32)) == 0
+    ref = oforward.forward(cfg, P, z, 0.5)
+    err = float(np.abs(got - ref).max())
+    say(f"max |dlogit| = {err:.3e}")
+    assert err <= TOL
