@@ -298,12 +298,10 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         const size_t need = (size_t)rows * d * sizeof(float);
         add = LnSlabs{};
         g.splits = 1;
-        if (dt != DD_BF16) return;
         int n = 0;
         for (const Region& f : free_ws)
             for (char* p = f.begin; n < MAX_SPLITS - 1 && p + need <= f.end; p += need) g.slab[n++] = (float*)p;
-        g.splits = forced ? std::min(forced, n + 1) : gemm_splits(dt, EPI_BIAS_RESID, g, n + 1);
-        g.splits = std::max(1, std::min(g.splits, g.k_base / 128));
+        g.splits = forced ? std::max(1, std::min({forced, n + 1, g.k_base / 128})) : gemm_splits(dt, EPI_BIAS_RESID, g, n + 1);
         add.n = g.splits - 1;
         for (int i = 0; i < add.n; ++i) add.slab[i] = g.slab[i];
     };

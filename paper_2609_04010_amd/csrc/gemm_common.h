@@ -18,6 +18,11 @@ DD_DEV float gelu_tanh(float x) {
     return x * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
+// the same for fp32 results
+DD_DEV float gelu_tanh_f32(float x) {
+    return 0.5f * x * (1.0f + tanhf(0.7978845608028654f * (x + 0.044715f * x * x * x)));
+}
+
 constexpr int BK = 64;   // K depth of an operand tile
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -33,7 +38,7 @@ DD_DEV float gate_row_scale(const GemmArgs& g, int m) {
 // wavefronts per CU), 64 x 64 with four stages (two workgroups of four wavefronts per CU) or three
 // stages (three per CU)
 enum RingTile { RING_128 = 0, RING_64_DEEP = 1, RING_64 = 2 };
-void launch_gemm_ring(RingTile tile, int epi, const GemmArgs& g, hipStream_t s);
+void launch_gemm_ring(int dtype, RingTile tile, int epi, const GemmArgs& g, hipStream_t s);
 double gemm_ring_us(RingTile tile, int64_t M, int64_t N, int64_t K, int splits, int cus);
 
 }  // namespace dd

@@ -25,7 +25,7 @@
 // nothing of a tile skips its arithmetic; a tile that every query of the wavefront sees whole takes
 // no per-element test.  Rows that have seen no visible key yet keep mref = -inf and use exponent
 // reference 0, so their probabilities are exactly 0 until their first visible key.
-// fp32 path (validation): one thread per (batch, head, query), fp32 online softmax.
+// fp32 path (validation): attn_f32_kernel, fp32 throughout.
 #include <limits.h>
 #include <math.h>
 
@@ -38,6 +38,7 @@ namespace dd {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int AQ = 128;  // queries per workgroup
 constexpr int AK = 64;   // keys per tile
@@ -380,40 +381,122 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
     }
 }
 
+// fp32: a workgroup of four wavefronts owns 32 queries of one (batch, head), and wavefront w the key
+// tiles (32 keys) w, w + 4, ..: at the sizes of a validation run the query blocks alone would leave
+// most of the chip idle (B 1, 12 heads, L 256: 96 of them).  S^T = K Q^T and O^T += V^T P^T with
+// v_mfma_f32_32x32x2_f32, operands straight from global memory: a lane's K chunk (4 head columns of
+// one key, the lane halves neighbouring chunks) and its Q chunk pair up element by element, and the
+// scores a lane ends with (keys 8 (j / 4) + 4 (lane / 32) + j % 4 of query lane % 32) are the P operand
+// of product j, whose V operand is one head column of those two keys.  Online softmax per lane; the
+// four partial results meet in LDS.  One thread per query, which this replaced, took 409 us at B 1,
+// 12 heads of 64, L 256, and 34 us at B 4, 2 heads of 32, L 32.
 template <int D, bool MASKED>
-__global__ __launch_bounds__(128) void attn_f32_kernel(AttnArgs a) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int L = a.L, H = a.H, d = a.d;
-    if (idx >= (int64_t)a.B * H * L) return;
-    const int q = (int)(idx % L);
-    const int h = (int)((idx / L) % H);
-    const int b = (int)(idx / ((int64_t)L * H));
-    const float* base = (const float*)a.qkv + (int64_t)b * L * a.ld;
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
+    constexpr int FQ = 32, FK = 32;
+    constexpr int NC = D / 8;              // chunk pairs of a head row
+    constexpr int DB = (D + 31) / 32;      // 32-wide blocks of head columns (D 16: half a block)
+    __shared__ float sh_o[4][DB * 32][FQ + 1];
+    __shared__ float sh_m[4][FQ], sh_l[4][FQ];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 5;
+    const int L = a.L, d = a.d;
+    const int nqb = (L + FQ - 1) / FQ;
+    const int qb = blockIdx.x % nqb, bh = blockIdx.x / nqb;
+    const int h = bh % a.H, b = bh / a.H;
+    const float* base = (const float*)a.qkv + (int64_t)b * L * a.ld + h * D;
     const float scale = 1.0f / sqrtf((float)D);
-    float qv[D], acc[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) { qv[c] = base[(int64_t)q * a.ld + h * D + c]; acc[c] = 0.f; }
+    const int qi = qb * FQ + (lane & 31);
     int pre = L, lo = 0, hi = 0;
-    if (MASKED) query_window(a, q, pre, lo, hi);
-    float m = -INFINITY, l = 0.f;
-    for (int t = 0; t < L; ++t) {
-        if (MASKED && !(t < pre || (t >= lo && t < hi))) continue;
-        const float* kr = base + (int64_t)t * a.ld + d + h * D;
-        float sdot = 0.f;
+    if (MASKED) {
+        pre = 0;
+        if (qi < L) query_window(a, qi, pre, lo, hi);
+    }
+    // union of the queries' visible sets
+    const bool win = hi > lo;
+    const int pmax = MASKED ? wave_max_i(pre) : L;
+    const int wlo = MASKED ? wave_min_i(win ? lo : INT_MAX) : 0, whi = MASKED ? wave_max_i(win ? hi : 0) : 0;
+    f32x4 qf[NC];
 #pragma unroll
-        for (int c = 0; c < D; ++c) sdot = fmaf(qv[c], kr[c], sdot);
-        sdot *= scale;
-        const float mn = fmaxf(m, sdot);
-        const float corr = expf(m - mn), p = expf(sdot - mn);
-        l = l * corr + p;
-        const float* vr = kr + d;
+    for (int c = 0; c < NC; ++c) qf[c] = *(const f32x4*)(base + (int64_t)min(qi, L - 1) * a.ld + 8 * c + 4 * grp);
+    f32x16 o[DB];
 #pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] = fmaf(p, vr[c], acc[c] * corr);
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[i][e] = 0.f;
+    float m = -INFINITY, l = 0.f;   // l: this lane's keys only
+    for (int kb0 = wave * FK; kb0 < L; kb0 += 4 * FK) {
+        if (MASKED && !(kb0 < pmax || (kb0 < whi && kb0 + FK > wlo))) continue;
+        const float* kr = base + d + (int64_t)min(kb0 + (lane & 31), L - 1) * a.ld + 4 * grp;
+        f32x4 kf[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) kf[c] = *(const f32x4*)(kr + 8 * c);
+        float vf[DB][16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int key = min(kb0 + 8 * (j >> 2) + 4 * grp + (j & 3), L - 1);
+            const float* vr = base + 2 * d + (int64_t)key * a.ld;
+#pragma unroll
+            for (int i = 0; i < DB; ++i) vf[i][j] = D >= 32 || (lane & 31) < D ? vr[32 * i + (lane & 31)] : 0.f;
+        }
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], qf[c][e], s, 0, 0, 0);
+        float mt = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int key = kb0 + 8 * (j >> 2) + 4 * grp + (j & 3);
+            const bool vis = MASKED ? (key < pre || (key >= lo && key < hi)) : key < L;
+            s[j] = vis ? s[j] * scale : -INFINITY;
+            mt = fmaxf(mt, s[j]);
+        }
+        const float mn = fmaxf(m, fmaxf(mt, __shfl_xor(mt, 32, 64)));
+        const float ref = mn == -INFINITY ? 0.f : mn;   // no visible key yet: every probability is 0
+        const float corr = expf(m - ref);
+        float lt = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            s[j] = expf(s[j] - ref);
+            lt += s[j];
+        }
+        l = fmaf(l, corr, lt);
+        // the tile's sums from zero, then added by the VALU (see the ring GEMM's fp32 sums)
+#pragma unroll
+        for (int i = 0; i < DB; ++i) {
+            f32x16 part = {};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) part = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[i][j], s[j], part, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[i][e] = fmaf(o[i][e], corr, part[e]);
+        }
         m = mn;
     }
-    float* out = (float*)a.out + ((int64_t)b * L + q) * a.ldo + h * D;
+    l += __shfl_xor(l, 32, 64);
+    if (lane < 32) {
+        sh_m[wave][lane] = m;
+        sh_l[wave][lane] = l;
+    }
 #pragma unroll
-    for (int c = 0; c < D; ++c) out[c] = acc[c] / l;
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sh_o[wave][32 * i + 8 * (e >> 2) + 4 * grp + (e & 3)][lane & 31] = o[i][e];
+    __syncthreads();
+    for (int x = tid; x < FQ * D; x += 256) {
+        const int q = x / D, c = x % D;
+        if (qb * FQ + q >= L) continue;
+        const float M = fmaxf(fmaxf(sh_m[0][q], sh_m[1][q]), fmaxf(sh_m[2][q], sh_m[3][q]));
+        const float ref = M == -INFINITY ? 0.f : M;
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float f = expf(sh_m[w][q] - ref);
+            num += f * sh_o[w][c][q];
+            den += f * sh_l[w][q];
+        }
+        ((float*)a.out)[((int64_t)b * L + qb * FQ + q) * a.ldo + h * D + c] = num / den;
+    }
 }
 
 bool attn_supported(int dtype, int dh) {
@@ -449,11 +532,10 @@ dd_status launch_attn(int dtype, const AttnArgs& a0, hipStream_t s) {
         else if (a.qrows) launch_k((attn_bf16_kernel<false, true>), grid, dim3(256), 0, s, a);
         else launch_k(attn_bf16_kernel<false>, grid, dim3(256), 0, s, a);
     } else {
-        const int64_t n = (int64_t)a.B * a.H * a.L;
-        const dim3 grid((unsigned)ceil_div(n, 128));
+        const dim3 grid((unsigned)(ceil_div(a.L, 32) * a.H * a.B));
 #define DD_ATTN_F32(DV)                                                                         \
-    if (a.mask) launch_k((attn_f32_kernel<DV, true>), grid, dim3(128), 0, s, a);      \
-    else launch_k((attn_f32_kernel<DV, false>), grid, dim3(128), 0, s, a);
+    if (a.mask) launch_k((attn_f32_kernel<DV, true>), grid, dim3(256), 0, s, a);      \
+    else launch_k((attn_f32_kernel<DV, false>), grid, dim3(256), 0, s, a);
         switch (dh) {
             case 16: DD_ATTN_F32(16) break;
             case 32: DD_ATTN_F32(32) break;

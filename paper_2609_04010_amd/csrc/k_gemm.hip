@@ -784,59 +784,6 @@ __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmA
     __builtin_amdgcn_s_waitcnt(0x3F70);           // vmcnt(0): no LDS write in flight at exit
 }
 
-// ------------------------------------------------------------------------------ fp32 (validation)
-constexpr int FT = 64, FK = 16;
-
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    __shared__ float As[FK][FT + 4];
-    __shared__ float Ws[FK][FT + 4];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
-    const int m0 = tm * FT, n0 = tn * FT;
-    const float* A = (const float*)g.A;
-    const float* W = (const float*)g.W;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < g.K; k0 += FK) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int idx = tid + 256 * r, row = idx / FK, k = idx % FK;
-            const int gk = k0 + k;
-            As[k][row] = (m0 + row < g.M && gk < g.K) ? A[(int64_t)(m0 + row) * g.lda + gk] : 0.f;
-            Ws[k][row] = (n0 + row < g.N && gk < g.K) ? W[(int64_t)(n0 + row) * g.ldw + gk] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < FK; ++k) {
-            float a[4], w[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = As[k][ty * 4 + i]; w[i] = Ws[k][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= g.M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= g.N) continue;
-            float x = acc[i][j];
-            if (EPI == EPI_GATE) x *= gate_row_scale(g, m);
-            else if (EPI != EPI_PLAIN) x += ((const float*)g.bias)[n];
-            if (EPI == EPI_BIAS_GELU) x = 0.5f * x * (1.0f + tanhf(0.7978845608028654f * (x + 0.044715f * x * x * x)));
-            float* c = (float*)g.C + (int64_t)m * g.ldc + n;
-            if (EPI == EPI_BIAS_RESID) *c += x;
-            else *c = x;
-        }
-    }
-}
-
 static int num_cus() {
     static int n = 0;
     if (n == 0) {
@@ -856,13 +803,13 @@ struct Plan {
 // Splits of a residual projection on ring tiles: 4 ways up to 512 rows, 2 up to 2048 (attention output,
 // K 768, N 768: 4.5 / 5.0 / 8.1 us with 4 / 2 / 1 at M 64, 7.6 / 7.4 with 2 / 1 at M 1024; MLP down,
 // K 3072: 7.0 / 10.5 / 16 at M 64, 13.6 with 2 against 13.7 with 4 at M 1024, 20.6 with 2 against 21.9
-// with 1 at M 2000; a split more costs the normalisation 0.5 to 2 us).  Steps of M, not the best per M,
+// with 1 at M 2000; a split more costs the normalisation 0.5 to 2 us), at least k_min of K each.  Steps of M, not the best per M,
 // and cut by the model's own K, so that a row's sums are the same in calls of similar size and with
 // adapters switched off.
-static int ring_splits(const GemmArgs& g, int max_splits) {
+static int ring_splits(const GemmArgs& g, int max_splits, int k_min) {
     const int want = g.M <= 512 ? 4 : g.M <= 2048 ? 2 : 1;
     const int k = g.k_base > 0 ? g.k_base : g.K;
-    return std::max(1, std::min(std::min(want, max_splits), k / (2 * BK)));   // at least two K-tiles each
+    return std::max(1, std::min(std::min(want, max_splits), k / k_min));
 }
 
 // The smallest estimated time.  The 256-row tiles (K % 128 == 0) in whole rounds of workgroups over
@@ -894,7 +841,7 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
         best.tile = narrow ? 7 : 6;
         t_best = 9.0 + (double)(g.K / BK) * (narrow ? r192 * 1.08 : r256 * 1.79);
     }
-    const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits) : 1;
+    const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits, 2 * BK) : 1;   // two K-tiles each
     const double slab_us = 0.4 + (double)g.M * g.N * 4 / 5e6;
     for (int tile = 0; tile < 3; ++tile) {
         const double t = gemm_ring_us((RingTile)tile, g.M, g.N, g.K, sp, cus) + (sp - 1) * slab_us;
@@ -907,7 +854,7 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
 }
 
 int gemm_splits(int dtype, int epi, const GemmArgs& g, int max_splits) {
-    return dtype == DD_BF16 ? plan_tile(g, epi, max_splits).splits : 1;
+    return dtype == DD_BF16 ? plan_tile(g, epi, max_splits).splits : ring_splits(g, max_splits, BK);
 }
 
 template <int EPI, int ROLE, int TBN, int WGM, int WGN, int DMR = DM>
@@ -930,21 +877,17 @@ static void launch_dl(const GemmArgs& g, hipStream_t s) {
 
 template <int EPI, int ROLE>
 static void launch_epi(int dtype, const GemmArgs& g, hipStream_t s) {
-    if (dtype == DD_BF16) {
-        int tile = g.tile_hint > 0 ? g.tile_hint - 1 : plan_tile(g, EPI, std::max(g.splits, 1)).tile;
-        // the ring instance of the 256 x 192 tile takes no gathered rows and no separate residual
-        // input: the four-wavefront form
-        if (tile == 7 && (g.a_rows || g.c_in) && dl_ring<EPI, DLShape<192, 4, 2>>()) tile = 5;
-        switch (tile) {
-            case 7: launch_dl<EPI, ROLE, 192, 4, 2>(g, s); break;
-            case 6: launch_dl<EPI, ROLE, 256, 2, 4>(g, s); break;
-            case 5: launch_dl<EPI, ROLE, 192, 2, 2>(g, s); break;
-            case 4: launch_dl<EPI, ROLE, 256, 2, 2>(g, s); break;
-            default: launch_gemm_ring((RingTile)tile, EPI, g, s); break;
-        }
-    } else {
-        const int tm = (g.M + FT - 1) / FT, tn = (g.N + FT - 1) / FT;
-        launch_k(gemm_f32_kernel<EPI>, dim3(tm * tn), dim3(256), 0, s, g, tm, tn);
+    if (dtype == DD_FP32) return launch_gemm_ring(dtype, RING_64_DEEP, EPI, g, s);
+    int tile = g.tile_hint > 0 ? g.tile_hint - 1 : plan_tile(g, EPI, std::max(g.splits, 1)).tile;
+    // the ring instance of the 256 x 192 tile takes no gathered rows and no separate residual
+    // input: the four-wavefront form
+    if (tile == 7 && (g.a_rows || g.c_in) && dl_ring<EPI, DLShape<192, 4, 2>>()) tile = 5;
+    switch (tile) {
+        case 7: launch_dl<EPI, ROLE, 192, 4, 2>(g, s); break;
+        case 6: launch_dl<EPI, ROLE, 256, 2, 4>(g, s); break;
+        case 5: launch_dl<EPI, ROLE, 192, 2, 2>(g, s); break;
+        case 4: launch_dl<EPI, ROLE, 256, 2, 2>(g, s); break;
+        default: launch_gemm_ring(dtype, (RingTile)tile, EPI, g, s); break;
     }
 }
 

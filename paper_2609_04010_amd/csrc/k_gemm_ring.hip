@@ -20,6 +20,10 @@
 // L2, 16 TB/s.  Against the register-staged 128 x 128 tiles this kernel replaced for K % 128 != 0:
 // M 1320, N 3072, K 832 24.0 -> 13.3 us, M 16384 143.5 -> 134.4.
 //
+// fp32 (the validation build) takes the same kernel with v_mfma_f32_32x32x2_f32, 64 x 64 tiles, bound by
+// the matrix cores: 12 layers d 768 on 256 rows 15.3 -> 1.47 ms per forward pass against the VALU
+// kernel it replaced (with the attention of k_attn.hip), error against float64 1.2e-6 -> 0.6e-6.
+//
 // K needs only K % 8 == 0: the chunks of the last K-tile past K are loaded from the row's first chunk
 // (in bounds) and their fragments are replaced by zeros.
 #include <math.h>
@@ -33,14 +37,37 @@
 
 namespace dd {
 
-// BM x BN x 64 tiles over WGM x WGN wavefronts of MB x NB 32x32 MFMA blocks, NST stages
+constexpr int ROWB = 128;   // bytes of an operand row in a K-tile: 64 bf16 or 32 fp32
+
+// The operand types: a K-tile is KT deep, a 16-byte chunk holds CH elements, and the two lane halves
+// of a fragment read hold neighbouring chunks.
+template <typename T> struct RingOp;
+template <> struct RingOp<bf16_t> {
+    static constexpr int KT = 64, CH = 8;
+    typedef bf16x8 frag;
+    DD_DEV static f32x16 mfma(frag w, frag a, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, c, 0, 0, 0); }
+};
+template <> struct RingOp<float> {
+    static constexpr int KT = 32, CH = 4;
+    typedef f32x4 frag;
+    // element e of the lanes 0..31 and of the lanes 32..63 are the two k of one 32x32x2 product
+    DD_DEV static f32x16 mfma(frag w, frag a, f32x16 c) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], a[e], c, 0, 0, 0);
+        return c;
+    }
+};
+DD_DEV float ring_bias(const bf16_t* b, int i) { return bf16_to_f32(b[i]); }
+DD_DEV float ring_bias(const float* b, int i) { return b[i]; }
+
+// BM x BN x one K-tile tiles over WGM x WGN wavefronts of MB x NB 32x32 MFMA blocks, NST stages
 template <int BM_, int BN_, int WGM_, int WGN_, int NST_> struct RingShape {
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NST = NST_;
     static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
     static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
     static constexpr int NA = BM / 8 / NW, NWL = BN / 8 / NW, NL = NA + NWL;   // 1 KB loads per wave and K-tile
-    static constexpr int STAGE = (BM + BN) * BK;
-    static constexpr size_t LDS = (size_t)NST * STAGE * sizeof(bf16_t);
+    static constexpr int STAGE = (BM + BN) * ROWB;   // bytes
+    static constexpr size_t LDS = (size_t)NST * STAGE;
     static constexpr int WG_PER_CU = LDS * 2 <= 160 * 1024 ? 2 : 1;
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && WM % 32 == 0 && WN % 32 == 0, "split");
     static_assert(LDS <= 160 * 1024 && NST >= 2 && (NST - 2) * NL < 64, "stages; the wait counts the loads");
@@ -50,11 +77,14 @@ template <int BM_, int BN_, int WGM_, int WGN_, int NST_> struct RingShape {
 // s_waitcnt vmcnt(N) alone
 template <int N> DD_DEV void wait_vm() { __builtin_amdgcn_s_waitcnt(0x3F70 | (N & 15) | ((N >> 4) << 14)); }
 
-template <int EPI, class S>
+template <typename T, int EPI, class S>
 __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_CU * S::NW / 4 : 1) void gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     constexpr int MB = S::MB, NB = S::NB, NA = S::NA, NWL = S::NWL, NST = S::NST;
     constexpr int AROWS = S::BM / S::NW, WROWS = S::BN / S::NW;
-    extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+    using Op = RingOp<T>;
+    constexpr int KT = Op::KT, CH = Op::CH, ES = sizeof(T);
+    extern __shared__ __attribute__((aligned(1024))) char ring_smem[];
+    char* smem = ring_smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / S::WGN, wn = wave % S::WGN;
     int M = g.M;
@@ -76,52 +106,50 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
         tn = r / gsz;
     }
     const int m0 = tm * S::BM, n0 = tn * S::BN;
-    const bf16_t* A = (const bf16_t*)g.A;
-    const bf16_t* W = (const bf16_t*)g.W;
-    const int nkt = (g.K + BK - 1) / BK, klast = g.K - (nkt - 1) * BK;   // valid k of the last K-tile
-    const int nkb = g.k_base > 0 ? (g.k_base + BK - 1) / BK : nkt;   // K-tiles that are cut evenly
+    const int nkt = (g.K + KT - 1) / KT, klast = g.K - (nkt - 1) * KT;   // valid k of the last K-tile
+    const int nkb = g.k_base > 0 ? (g.k_base + KT - 1) / KT : nkt;   // K-tiles that are cut evenly
     const int kt0 = split * nkb / nsplit, kt1 = split + 1 == nsplit ? nkt : (split + 1) * nkb / nsplit;
 
     // This lane's 16-byte slot of row r holds K-chunk (lane % 8) ^ ((r >> 1) & 7).  Byte offsets from
     // the tile's first row (under 256 rows, so 32 bits), and the chunk's first k in the K-tile.
-    const char* Ab = (const char*)(A + (int64_t)m0 * g.lda);
-    const char* Wb = (const char*)(W + (int64_t)n0 * g.ldw);
+    const char* Ab = (const char*)g.A + (int64_t)m0 * g.lda * ES;
+    const char* Wb = (const char*)g.W + (int64_t)n0 * g.ldw * ES;
     uint32_t offA[NA], offW[NWL];
     int chA[NA], chW[NWL];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int rl = AROWS * wave + 8 * i + (lane >> 3);
-        chA[i] = ((lane & 7) ^ ((rl >> 1) & 7)) * 8;
-        offA[i] = (uint32_t)(min(rl, M - 1 - m0) * (int)g.lda + chA[i]) * 2u;
+        chA[i] = ((lane & 7) ^ ((rl >> 1) & 7)) * CH;
+        offA[i] = (uint32_t)(min(rl, M - 1 - m0) * (int)g.lda + chA[i]) * (uint32_t)ES;
     }
 #pragma unroll
     for (int i = 0; i < NWL; ++i) {
         const int rl = WROWS * wave + 8 * i + (lane >> 3);
-        chW[i] = ((lane & 7) ^ ((rl >> 1) & 7)) * 8;
-        offW[i] = (uint32_t)(min(rl, g.N - 1 - n0) * (int)g.ldw + chW[i]) * 2u;
+        chW[i] = ((lane & 7) ^ ((rl >> 1) & 7)) * CH;
+        offW[i] = (uint32_t)(min(rl, g.N - 1 - n0) * (int)g.ldw + chW[i]) * (uint32_t)ES;
     }
     auto load = [&](int t, int stage, auto whole_c) {
-        bf16_t* st = smem + stage * S::STAGE;
-        const char* ap = Ab + (int64_t)t * (BK * 2);
-        const char* wp = Wb + (int64_t)t * (BK * 2);
-        if (!decltype(whole_c)::value && t == nkt - 1 && klast < BK) {
+        char* st = smem + stage * S::STAGE;
+        const char* ap = Ab + (int64_t)t * ROWB;
+        const char* wp = Wb + (int64_t)t * ROWB;
+        if (!decltype(whole_c)::value && t == nkt - 1 && klast < KT) {
 #pragma unroll
             for (int i = 0; i < NA; ++i)
-                __builtin_amdgcn_global_load_lds((gbl_void*)(ap + (offA[i] - (chA[i] < klast ? 0 : chA[i] * 2))),
-                                                 (lds_void*)(st + (AROWS * wave + 8 * i) * BK), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gbl_void*)(ap + (offA[i] - (chA[i] < klast ? 0 : chA[i] * ES))),
+                                                 (lds_void*)(st + (AROWS * wave + 8 * i) * ROWB), 16, 0, 0);
 #pragma unroll
             for (int i = 0; i < NWL; ++i)
-                __builtin_amdgcn_global_load_lds((gbl_void*)(wp + (offW[i] - (chW[i] < klast ? 0 : chW[i] * 2))),
-                                                 (lds_void*)(st + (S::BM + WROWS * wave + 8 * i) * BK), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gbl_void*)(wp + (offW[i] - (chW[i] < klast ? 0 : chW[i] * ES))),
+                                                 (lds_void*)(st + (S::BM + WROWS * wave + 8 * i) * ROWB), 16, 0, 0);
         } else {
 #pragma unroll
             for (int i = 0; i < NA; ++i)
                 __builtin_amdgcn_global_load_lds((gbl_void*)(ap + offA[i]),
-                                                 (lds_void*)(st + (AROWS * wave + 8 * i) * BK), 16, 0, 0);
+                                                 (lds_void*)(st + (AROWS * wave + 8 * i) * ROWB), 16, 0, 0);
 #pragma unroll
             for (int i = 0; i < NWL; ++i)
                 __builtin_amdgcn_global_load_lds((gbl_void*)(wp + offW[i]),
-                                                 (lds_void*)(st + (S::BM + WROWS * wave + 8 * i) * BK), 16, 0, 0);
+                                                 (lds_void*)(st + (S::BM + WROWS * wave + 8 * i) * ROWB), 16, 0, 0);
         }
     };
 
@@ -163,37 +191,54 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
     // Two sets of fragments: a K-tile's are read while the MFMAs of the one before run (one set, read
     // after the barrier, left the LDS reads, the LDS writes of the loads and the MFMAs one after the
     // other: the wavefronts of a workgroup pass the barrier together).
-    constexpr int KS = BK / 16;
+    constexpr int KS = ROWB / 32;   // fragment steps of a K-tile: two chunks each
+    typedef typename Op::frag frag;
     struct Frags {
-        bf16x8 a[KS][MB], w[KS][NB];
+        frag a[KS][MB], w[KS][NB];
     };
     const int frow = lane & 31, fsw = (lane >> 1) & 7, fhalf = lane >> 5;
     auto read = [&](Frags& f, int stage) {
-        const bf16_t* sA = smem + stage * S::STAGE + (wm * S::WM + frow) * BK;
-        const bf16_t* sW = smem + stage * S::STAGE + (S::BM + wn * S::WN + frow) * BK;
+        const char* sA = smem + stage * S::STAGE + (wm * S::WM + frow) * ROWB;
+        const char* sW = smem + stage * S::STAGE + (S::BM + wn * S::WN + frow) * ROWB;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const int slot = ((2 * kk + fhalf) ^ fsw) * 8;
+            const int slot = ((2 * kk + fhalf) ^ fsw) * 16;
 #pragma unroll
-            for (int i = 0; i < MB; ++i) f.a[kk][i] = *(const bf16x8*)&sA[32 * i * BK + slot];
+            for (int i = 0; i < MB; ++i) f.a[kk][i] = *(const frag*)&sA[32 * i * ROWB + slot];
 #pragma unroll
-            for (int i = 0; i < NB; ++i) f.w[kk][i] = *(const bf16x8*)&sW[32 * i * BK + slot];
+            for (int i = 0; i < NB; ++i) f.w[kk][i] = *(const frag*)&sW[32 * i * ROWB + slot];
         }
     };
     auto mfmas = [&](const Frags& f) {
+        if constexpr (ES == 4) {
+            // Each K-tile's 32 products are summed from zero and added to the running sum by the VALU
+            // (16 adds beside 1024 MFMA cycles): with the running sum inside the MFMAs the logits of
+            // a 12-layer d 768 model are 2.7e-6 off the float64 result.
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    f32x16 part = {};
+#pragma unroll
+                    for (int kk = 0; kk < KS; ++kk) part = Op::mfma(f.w[kk][nb], f.a[kk][mb], part);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[nb][mb][e] += part[e];
+                }
+            return;
+        }
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
-                    acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[kk][nb], f.a[kk][mb], acc[nb][mb], 0, 0, 0);
+                    acc[nb][mb] = Op::mfma(f.w[kk][nb], f.a[kk][mb], acc[nb][mb]);
     };
     auto clear_past = [&](Frags& f) {   // the last K-tile's fragments past K
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const bool past = (2 * kk + fhalf) * 8 >= klast;
-            const bf16x8 z = {};
+            const bool past = (2 * kk + fhalf) * CH >= klast;
+            const frag z = {};
 #pragma unroll
             for (int i = 0; i < MB; ++i) f.a[kk][i] = past ? z : f.a[kk][i];
 #pragma unroll
@@ -236,7 +281,7 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
             rd = rd + 1 == NST ? 0 : rd + 1;
             ld = ld + 1 == NST ? 0 : ld + 1;
             __builtin_amdgcn_sched_barrier(0);
-        } else if (kt1 == nkt && klast < BK) {
+        } else if (kt1 == nkt && klast < KT) {
             clear_past(cur);
         }
         mfmas(cur);
@@ -253,17 +298,20 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
     }
     __syncthreads();   // the stages become the epilogue's staging area
 
-    if constexpr (EPI == EPI_BIAS_RESID) {
+    if constexpr (EPI == EPI_BIAS_RESID || ES == 4) {
+        // fp32 rows: one 32 x 32 block at a time through this wavefront's 4 KB, chunk-swizzled by row,
+        // so that eight lanes write one 128-byte row segment
         float* cst = (float*)smem + wave * (32 * 32);
         float* C = split == 0 ? (float*)g.C : g.slab[split - 1];
-        const bf16_t* bias = (const bf16_t*)g.bias;
+        const T* bias = (const T*)g.bias;
         const int rr = lane >> 3, c4 = (lane & 7) * 4;
+        constexpr bool BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESID;
         float bv[NB][4];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                bv[nb][e] = split == 0 ? bf16_to_f32(bias[min(n0 + wn * S::WN + nb * 32 + c4 + e, g.N - 1)]) : 0.f;
+                bv[nb][e] = BIAS && split == 0 ? ring_bias(bias, min(n0 + wn * S::WN + nb * 32 + c4 + e, g.N - 1)) : 0.f;
 #pragma unroll
         for (int b = 0; b < MB * NB; ++b) {
             const int mb = b % MB, nb = b / MB;
@@ -280,16 +328,29 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
                 const int r = rr + 8 * it;
                 const float4 v = *(const float4*)&cst[r * 32 + (((c4 >> 2) ^ ((r >> 1) & 7)) * 4)];
                 const int m = m0 + wm * S::WM + mb * 32 + r;
-                if (m < M && n < g.N)
-                    *(f32x4*)(C + (int64_t)m * g.ldc + n) =
-                        f32x4{v.x + bv[nb][0], v.y + bv[nb][1], v.z + bv[nb][2], v.w + bv[nb][3]};
+                if (m >= M || n >= g.N) continue;
+                float o[4] = {v.x + bv[nb][0], v.y + bv[nb][1], v.z + bv[nb][2], v.w + bv[nb][3]};
+                if constexpr (EPI == EPI_BIAS_GELU)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = gelu_tanh_f32(o[e]);
+                if constexpr (EPI == EPI_GATE) {
+                    const float rs = gate_row_scale(g, m);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] *= rs;
+                }
+                float* dst = C + (int64_t)m * g.ldc + n;
+                if (EPI == EPI_BIAS_RESID || n + 3 < g.N) {
+                    *(f32x4*)dst = f32x4{o[0], o[1], o[2], o[3]};
+                } else {
+                    for (int e = 0; n + e < g.N; ++e) dst[e] = o[e];
+                }
             }
         }
     } else {
         // one 32 x 32 block at a time through this wavefront's staging rows (80 bytes), then 16-byte
         // pieces of 64-byte row segments
         constexpr int CSTR = 40;
-        bf16_t* cst = smem + wave * (32 * CSTR);
+        bf16_t* cst = (bf16_t*)smem + wave * (32 * CSTR);
         bf16_t* C = (bf16_t*)g.C;
         const bf16_t* bias = (const bf16_t*)g.bias;
         float b4[EPI == EPI_BIAS || EPI == EPI_BIAS_GELU ? NB : 1][16];
@@ -340,33 +401,36 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
 }
 
 
-template <int EPI, class S>
+template <typename T, int EPI, class S>
 static void launch_shape(const GemmArgs& g, hipStream_t s) {
     const int tm = ((g.m_rows > 0 ? g.m_rows : g.M) + S::BM - 1) / S::BM, tn = (g.N + S::BN - 1) / S::BN;
     static std::once_flag once;   // opt-in to more than 64 KB of LDS per workgroup
     std::call_once(once, [] {
-        (void)hipFuncSetAttribute((const void*)gemm_ring_kernel<EPI, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void*)gemm_ring_kernel<T, EPI, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)S::LDS);
     });
-    launch_k((gemm_ring_kernel<EPI, S>), dim3(tm * tn * std::max(g.splits, 1)), dim3(S::THREADS), S::LDS, s, g, tm, tn);
+    launch_k((gemm_ring_kernel<T, EPI, S>), dim3(tm * tn * std::max(g.splits, 1)), dim3(S::THREADS), S::LDS, s, g, tm, tn);
 }
 
 template <int EPI>
-static void launch_epi(RingTile tile, const GemmArgs& g, hipStream_t s) {
+static void launch_epi(int dtype, RingTile tile, const GemmArgs& g, hipStream_t s) {
+    // fp32: the matrix cores are the bound on any tile (a K-tile of 32 is 1024 MFMA cycles per
+    // wavefront), so only the small one
+    if (dtype == DD_FP32) return launch_shape<float, EPI, RingShape<64, 64, 2, 2, 4>>(g, s);
     switch (tile) {
-        case RING_128: launch_shape<EPI, RingShape<128, 128, 4, 2, 4>>(g, s); break;
-        case RING_64_DEEP: launch_shape<EPI, RingShape<64, 64, 2, 2, 4>>(g, s); break;
-        default: launch_shape<EPI, RingShape<64, 64, 2, 2, 3>>(g, s); break;
+        case RING_128: launch_shape<bf16_t, EPI, RingShape<128, 128, 4, 2, 4>>(g, s); break;
+        case RING_64_DEEP: launch_shape<bf16_t, EPI, RingShape<64, 64, 2, 2, 4>>(g, s); break;
+        default: launch_shape<bf16_t, EPI, RingShape<64, 64, 2, 2, 3>>(g, s); break;
     }
 }
 
-void launch_gemm_ring(RingTile tile, int epi, const GemmArgs& g, hipStream_t s) {
+void launch_gemm_ring(int dtype, RingTile tile, int epi, const GemmArgs& g, hipStream_t s) {
     switch (epi) {
-        case EPI_BIAS: launch_epi<EPI_BIAS>(tile, g, s); break;
-        case EPI_BIAS_GELU: launch_epi<EPI_BIAS_GELU>(tile, g, s); break;
-        case EPI_BIAS_RESID: launch_epi<EPI_BIAS_RESID>(tile, g, s); break;
-        case EPI_GATE: launch_epi<EPI_GATE>(tile, g, s); break;
-        default: launch_epi<EPI_PLAIN>(tile, g, s); break;
+        case EPI_BIAS: launch_epi<EPI_BIAS>(dtype, tile, g, s); break;
+        case EPI_BIAS_GELU: launch_epi<EPI_BIAS_GELU>(dtype, tile, g, s); break;
+        case EPI_BIAS_RESID: launch_epi<EPI_BIAS_RESID>(dtype, tile, g, s); break;
+        case EPI_GATE: launch_epi<EPI_GATE>(dtype, tile, g, s); break;
+        default: launch_epi<EPI_PLAIN>(dtype, tile, g, s); break;
     }
 }
 

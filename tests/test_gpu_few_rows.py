@@ -65,3 +65,47 @@ def test_forward_on_few_rows_matches_oracle(case):
     err = float(np.abs(got - ref).max())
     say(f"max |dlogit| = {err:.3e}")
     assert err <= TOL
+
+
+F32_CASES = [
+    # d_model, heads (head dim 16 / 32 / 64 / 128), layers, B, L, pattern, block
+    (64, 4, 2, 3, 1, None, 0),
+    (64, 4, 2, 2, 33, "causal", 0),
+    (64, 2, 2, 2, 130, None, 0),
+    (128, 2, 2, 2, 31, "block_causal", 5),
+    (256, 2, 2, 1, 160, "draft_train", 8),
+    (256, 4, 1, 2, 257, None, 0),
+    (768, 12, 1, 5, 120, None, 0),      # 600 rows: K split two ways
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=lambda c: f"d{c[0]}-h{c[1]}-B{c[3]}-L{c[4]}-{c[5]}")
+def test_fp32_forward_matches_oracle(case):
+    """The matrix-core fp32 GEMM and attention: every head dim, key and query tails, patterns.  Bar: the
+    validation build's 1e-4; fp32 sums of these lengths leave about 1e-6."""
+    torch = torch_or_skip()
+    d, H, nl, B, L, pattern, block = case
+    say("fp32", case)
+    cfg = workloads.model_cfg(1, d_model=d, n_heads=H, n_layers=nl, d_mlp=4 * d - 8, vocab=77, max_len=L)
+    P = oparams.init_params(cfg, 43)
+    blob = dd.pack_params(cfg, oparams.storage_tensors(cfg, P))
+    buf = torch.zeros(blob.size, dtype=torch.uint8, device="cuda")
+    dd.init_params(cfg, buf, host_blob=blob)
+    z = workloads.masked_state(78, B, L, cfg["vocab"], 0.5)
+    ld = int(dd.logits_ld(cfg["vocab"]))
+    logits = torch.zeros((B * L, ld), dtype=torch.float32, device="cuda")
+    ws = torch.full((dd.workspace_bytes(cfg, B, L),), 0xFF, dtype=torch.uint8, device="cuda")
+    dd.workspace_reset(ws)
+    vis, mask = None, None
+    if pattern:
+        host = dd.attn_mask_build(pattern, L, block)
+        mask = dev_i32(torch, host.reshape(-1))
+        j = np.arange(L)[None, :]
+        vis = (j < host[0][:, None]) | ((j >= host[1][:, None]) & (j < host[2][:, None]))
+    dd.denoise_forward_ex(cfg, buf, dev_i32(torch, z.reshape(-1)), B, L, 0.5, logits, ld, ws, attn_mask=mask)
+    got = logits[:, :cfg["vocab"]].double().cpu().numpy().reshape(B, L, -1)
+    assert torch.all(logits[:, cfg["vocab"]:] == 0)
+    assert dd.read_device_error(ws[:4].view(torch.int32)) == 0
+    err = float(np.abs(got - oforward.forward(cfg, P, z, 0.5, vis)).max())
+    say(f"max |dlogit| = {err:.3e}")
+    assert err <= 1e-4
