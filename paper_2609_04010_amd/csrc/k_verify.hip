@@ -11,12 +11,20 @@
 // classes, no mask group): the draw is invariant to the normaliser, so group masses and class
 // scores use the unnormalised residual.
 //
-// Kernel 1 (one workgroup per logit row): row log-sum-exp in fp32.
+// Kernel 1 (one workgroup per position of a sequence, rows p_i and q_i, or per row): row log-sum-exps
+// in fp32.
 // Kernel 2 (one workgroup per sequence): n from the B - 1 acceptance tests, then one pass over the
 // chosen row pair for the group masses and the two-level draw.
+//
+// Only the rows up to the first rejection matter.  With many sequences kernel 1 therefore also makes
+// its position's acceptance test and lowers n_out[s] to a rejected position; workgroups are dispatched
+// position by position, and one that starts after an earlier position of its sequence was rejected
+// leaves at once.  That is a hint only: kernel 2 makes the tests again from the log-sum-exps (those of
+// positions below n are always there), so a hint that arrives late costs time and nothing else.
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "elem.h"
 #include "kernels.h"
@@ -26,42 +34,83 @@ namespace dd {
 
 namespace {
 
-constexpr int VT = 256;   // threads per workgroup
+constexpr int VT = 512;    // threads per workgroup of kernel 1
+constexpr int VT2 = 1024;  // and of kernel 2
 
-// Row r < S B is target row r; otherwise draft row r - S B.  One pass over the row: each thread keeps
-// a running maximum m and the sum of exp(l - m), rescaled when m rises; the workgroup then combines
-// the (m, sum) pairs.  The result is that of the two-pass definition: NaN if a logit is NaN, else
-// +inf if one is +inf, else -inf if none is finite.
-// The pass is bound by VALU work per logit, so the hot loop spends four full-rate operations and one
-// exp2 per logit: a thread takes VU chunks at a time (loaded together, the next VU loaded while these
-// are reduced), takes their maximum with fmax (which passes over NaN), rescales its sum when the
-// maximum rises, and adds exp2(l log2 e - m log2 e).  A NaN or +inf logit makes that sum NaN
-// (exp2 of NaN, or of inf - inf), so such rows are told apart afterwards by a second scan that
-// only they take.
-constexpr int VU = 4;
+DD_DEV uint32_t verify_word(const VerifyArgs& a, int s, uint32_t stream, int idx, int explicit_off) {
+    if (a.noise) return a.noise[(int64_t)s * a.nu + explicit_off + idx];
+    return counter_word(a.seed, stream, a.step, a.row0 + (uint32_t)s, (uint32_t)idx);
+}
+
+DD_DEV float word_uniform_f(uint32_t w) { return ((float)w + 0.5f) * 0x1p-32f; }
+
+// Draft position i of sequence s is rejected: u_i > min(1, p_i(x_i) / q_i(x_i)), from the rows and
+// their log-sum-exps.  An id outside [0, V) is clamped (kernel 2 reports those it needed).
 template <typename T>
-__global__ __launch_bounds__(VT) void row_lse_kernel(VerifyArgs a, float* lse) {
-    __shared__ float sh_m[VT / 64], sh_s[VT / 64];
-    __shared__ int sh_f[VT / 64];
-    constexpr int E = Elem<T>::E;
-    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int np = a.S * a.B;
-    const char* rowp = r < np ? (const char*)a.p + (size_t)r * a.ld * sizeof(T)
-                              : (const char*)a.q + (size_t)(r - np) * a.ld * sizeof(T);
+DD_DEV bool rejected(const VerifyArgs& a, int s, int i, float lse_p, float lse_q) {
+    const int x = min(max(a.draft[(int64_t)s * (a.B - 1) + i], 0), a.V - 1);
+    const char* pr = (const char*)a.p + ((size_t)s * a.B + i) * a.ld * sizeof(T);
+    const char* qr = (const char*)a.q + ((size_t)s * (a.B - 1) + i) * a.ld * sizeof(T);
+    const float lp = Elem<T>::load1(pr, x) - lse_p, lq = Elem<T>::load1(qr, x) - lse_q;
+    const float ratio = fminf(1.f, __builtin_amdgcn_exp2f((lp - lq) * LOG2E));
+    return word_uniform_f(verify_word(a, s, STREAM_VERIFY, i, 0)) > ratio;
+}
+
+// One pass over the rows: each thread keeps a running maximum m and the sum of exp(l - m), rescaled
+// when m rises; the workgroup then combines the (m, sum) pairs.  The result is that of the two-pass
+// definition: NaN if a logit is NaN, else +inf if one is +inf, else -inf if none is finite.
+// The hot loop spends four full-rate operations and one exp2 per logit: a thread takes VU chunks of
+// both rows at a time (loaded together, the next VU loaded while these are reduced), takes a row's
+// maximum with fmax (which passes over NaN), rescales its sum when the maximum rises, and adds
+// exp2(l log2 e - m log2 e).  A NaN or +inf logit makes that sum NaN (exp2 of NaN, or of inf - inf),
+// so such rows are told apart afterwards by a second scan that only they take.  Bound by HBM; S 256,
+// B 16, V 50257 with 4.8 positions kept on average: 131 us over every row, 81 us with the hint (two
+// chunks per row in flight; with four the kernel needs 148 registers, one workgroup per CU, 115 us).
+constexpr int VU = 2;
+template <typename T>
+__global__ __launch_bounds__(VT, VT / 128) void row_lse_kernel(VerifyArgs a, float* lse, int hint) {
+    __shared__ float sh_m[2][VT / 64], sh_s[2][VT / 64];
+    __shared__ int sh_f[VT / 64], sh_skip;
+    constexpr int E = Elem<T>::E, NW = VT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // with the hint a workgroup takes a position, position by position; without it one row (target
+    // rows first)
+    const int np = a.S * a.B, r0 = (int)blockIdx.x;
+    const int i = hint ? r0 / a.S : 0, s = hint ? r0 - i * a.S : 0;
     const int V = a.V, nchunk = (V + E - 1) / E;
-    float m = -INFINITY, sum = 0.f;
+    if (hint) {
+        if (tid == 0) sh_skip = __hip_atomic_load(a.n_out + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= i;
+        __syncthreads();
+        if (sh_skip) return;
+    }
+    const bool pair = hint && i < a.B - 1;
+    const char* rows[2] = {hint ? (const char*)a.p + ((size_t)s * a.B + i) * a.ld * sizeof(T)
+                           : r0 < np ? (const char*)a.p + (size_t)r0 * a.ld * sizeof(T)
+                                     : (const char*)a.q + (size_t)(r0 - np) * a.ld * sizeof(T),
+                           pair ? (const char*)a.q + ((size_t)s * (a.B - 1) + i) * a.ld * sizeof(T) : nullptr};
+    float m[2] = {-INFINITY, -INFINITY}, sum[2] = {0.f, 0.f};
     constexpr int TS = VU * VT;   // chunks per tile
     // chunks c0 + u VT + tid, u < VU; chunks past the row read as -inf, and so does the part of the
     // last chunk past V
-    auto load = [&](uint4 (&x)[VU], int c0) {
+    auto load = [&](uint4 (&x)[VU], const char* rowp, int c0) {
+        if ((c0 + TS) * E <= V) {   // every element of the tile is in the row
 #pragma unroll
-        for (int u = 0; u < VU; ++u) {
-            const int c = c0 + u * VT + tid;
-            x[u] = c < nchunk ? *(const uint4*)(rowp + (size_t)c * 16) : Elem<T>::NEG_INF4;
-            if (V % E != 0 && c == nchunk - 1) Elem<T>::clip(x[u], V % E);
+            for (int u = 0; u < VU; ++u) x[u] = *(const uint4*)(rowp + (size_t)(c0 + u * VT + tid) * 16);
+        } else {
+#pragma unroll
+            for (int u = 0; u < VU; ++u) {
+                const int c = c0 + u * VT + tid;
+                const uint4 y = *(const uint4*)(rowp + (size_t)min(c, nchunk - 1) * 16);
+                x[u] = c < nchunk ? y : Elem<T>::NEG_INF4;
+            }
+            if (V % E != 0) {
+#pragma unroll
+                for (int u = 0; u < VU; ++u)
+                    if (c0 + u * VT + tid == nchunk - 1) Elem<T>::clip(x[u], V % E);
+            }
         }
     };
-    auto absorb = [&](const uint4 (&x)[VU]) {
+    auto absorb = [&](const uint4 (&x)[VU], float& m, float& sum) {
         float cm = -INFINITY;
 #pragma unroll
         for (int u = 0; u < VU; ++u)
@@ -77,99 +126,136 @@ __global__ __launch_bounds__(VT) void row_lse_kernel(VerifyArgs a, float* lse) {
 #pragma unroll
             for (int e = 0; e < E; ++e) sum += __builtin_amdgcn_exp2f(fmaf(Elem<T>::get(x[u], e), LOG2E, moff));
     };
-    uint4 xa[VU], xb[VU];
-    load(xa, 0);
-    for (int c0 = 0; c0 < nchunk; c0 += 2 * TS) {
-        const bool more = c0 + TS < nchunk;
-        if (more) load(xb, c0 + TS);
-        absorb(xa);
-        if (!more) break;
-        if (c0 + 2 * TS < nchunk) load(xa, c0 + 2 * TS);
-        absorb(xb);
-    }
-    // workgroup: maximum, then the sums rescaled to it
-    float M = wave_max(m);
-    if (lane == 0) sh_m[wave] = M;
-    __syncthreads();
-    M = sh_m[0];
+    auto scan = [&](auto pair_c) {
+        constexpr int R = decltype(pair_c)::value ? 2 : 1;
+        uint4 xa[R][VU], xb[R][VU];
 #pragma unroll
-    for (int w = 1; w < VT / 64; ++w) M = fmaxf(M, sh_m[w]);
-    const float Mref = M == -INFINITY ? 0.f : M;
-    // a thread that met no finite logit has sum 0, or NaN if it met a NaN: kept as it is
-    float part = m == -INFINITY ? sum : sum * __builtin_amdgcn_exp2f((m - Mref) * LOG2E);
-    part = wave_sum(part);
-    if (lane == 0) sh_s[wave] = part;
-    __syncthreads();
-    float S = sh_s[0];
+        for (int r = 0; r < R; ++r) load(xa[r], rows[r], 0);
+        for (int c0 = 0; c0 < nchunk; c0 += 2 * TS) {
+            const bool more = c0 + TS < nchunk;
+            if (more) {
 #pragma unroll
-    for (int w = 1; w < VT / 64; ++w) S += sh_s[w];
-    if (!(S == S) || M == INFINITY) {
-        // a NaN or +inf logit (the sum is NaN): NaN if any logit is NaN, else +inf
-        int fl = 0;
-        for (int c = tid; c < nchunk; c += VT) {
-            uint4 x = *(const uint4*)(rowp + (size_t)c * 16);
-            if (V % E != 0 && c == nchunk - 1) Elem<T>::clip(x, V % E);
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const float t = Elem<T>::get(x, e);
-                fl |= (t != t) ? 1 : (t == INFINITY ? 2 : 0);
+                for (int r = 0; r < R; ++r) load(xb[r], rows[r], c0 + TS);
             }
-        }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) fl |= __shfl_xor(fl, o, 64);
-        if (lane == 0) sh_f[wave] = fl;
-        __syncthreads();
-        fl = sh_f[0] | sh_f[1] | sh_f[2] | sh_f[3];
-        if (tid == 0) lse[r] = (fl & 1) ? __int_as_float(0x7FC00000) : INFINITY;
-    } else if (tid == 0) {
-        lse[r] = Mref + logf(S);
+            for (int r = 0; r < R; ++r) absorb(xa[r], m[r], sum[r]);
+            if (!more) break;
+            if (c0 + 2 * TS < nchunk) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) load(xa[r], rows[r], c0 + 2 * TS);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) absorb(xb[r], m[r], sum[r]);
+        }
+    };
+    if (pair) scan(std::true_type{});
+    else scan(std::false_type{});
+    // workgroup: maximum, then the sums rescaled to it
+    float M[2], Mref[2], S[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        M[r] = wave_max(m[r]);
+        if (lane == 0) sh_m[r][wave] = M[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        M[r] = sh_m[r][0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) M[r] = fmaxf(M[r], sh_m[r][w]);
+        Mref[r] = M[r] == -INFINITY ? 0.f : M[r];
+        // a thread that met no finite logit has sum 0, or NaN if it met a NaN: kept as it is
+        const float part = wave_sum(m[r] == -INFINITY ? sum[r] : sum[r] * __builtin_amdgcn_exp2f((m[r] - Mref[r]) * LOG2E));
+        if (lane == 0) sh_s[r][wave] = part;
+    }
+    __syncthreads();
+    float out[2] = {0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        if (r == 1 && !pair) break;
+        S[r] = sh_s[r][0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) S[r] += sh_s[r][w];
+        out[r] = Mref[r] + logf(S[r]);
+        if (!(S[r] == S[r]) || M[r] == INFINITY) {
+            // a NaN or +inf logit (the sum is NaN): NaN if any logit is NaN, else +inf
+            int fl = 0;
+            for (int c = tid; c < nchunk; c += VT) {
+                uint4 x = *(const uint4*)(rows[r] + (size_t)c * 16);
+                if (V % E != 0 && c == nchunk - 1) Elem<T>::clip(x, V % E);
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const float t = Elem<T>::get(x, e);
+                    fl |= (t != t) ? 1 : (t == INFINITY ? 2 : 0);
+                }
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) fl |= __shfl_xor(fl, o, 64);
+            __syncthreads();          // the other row's flags have been read
+            if (lane == 0) sh_f[wave] = fl;
+            __syncthreads();
+            fl = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) fl |= sh_f[w];
+            out[r] = (fl & 1) ? __int_as_float(0x7FC00000) : INFINITY;
+        }
+    }
+    if (tid == 0) {
+        lse[hint ? (size_t)s * a.B + i : (size_t)r0] = out[0];
+        if (pair) {
+            lse[np + (size_t)s * (a.B - 1) + i] = out[1];
+            if (rejected<T>(a, s, i, out[0], out[1])) atomicMin(a.n_out + s, i + 1);
+        }
     }
 }
 
-DD_DEV uint32_t verify_word(const VerifyArgs& a, int s, uint32_t stream, int idx, int explicit_off) {
-    if (a.noise) return a.noise[(int64_t)s * a.nu + explicit_off + idx];
-    return counter_word(a.seed, stream, a.step, a.row0 + (uint32_t)s, (uint32_t)idx);
+// n_out[s] = B: the hint of kernel 1 starts without a rejection
+__global__ void verify_start_kernel(int32_t* n_out, int S, int B) {
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    if (s < S) n_out[s] = B;
 }
 
-DD_DEV float word_uniform_f(uint32_t w) { return ((float)w + 0.5f) * 0x1p-32f; }
-
+// The pass over the row pair is one CU's work per sequence, so what bounds it is how much that CU has
+// in flight: 1024 threads, VU chunks of both rows each.  The tests of the drafted positions run one
+// per lane, and the draw takes one Philox block per four words (S 4, B 16, V 50257: 32.7 us with 256
+// threads, one chunk each, the tests one after the other by one thread and a block per word).
 template <typename T>
-__global__ __launch_bounds__(VT) void verify_kernel(VerifyArgs a, const float* lse) {
+__global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* lse) {
     extern __shared__ float s_mass[];   // one mass per group
     __shared__ int sh_n;
-    __shared__ float sh_tot[VT / 64];
-    constexpr int E = Elem<T>::E;
+    __shared__ float sh_tot[VT2 / 64];
+    constexpr int E = Elem<T>::E, NW = VT2 / 64;
     constexpr int LPG = DD_GUMBEL_GROUP / E;   // chunks (lanes) per group
     const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int B = a.B, V = a.V;
     const int ngroups = (V + DD_GUMBEL_GROUP - 1) / DD_GUMBEL_GROUP;
     const float* lse_p = lse + (size_t)s * B;
     const float* lse_q = lse + (size_t)a.S * B + (size_t)s * (B - 1);
-    auto prow = [&](int i) { return (const char*)a.p + ((size_t)s * B + i) * a.ld * sizeof(T); };
-    auto qrow = [&](int i) { return (const char*)a.q + ((size_t)s * (B - 1) + i) * a.ld * sizeof(T); };
 
     // ---- acceptance: the first rejected draft position (1-based), or B ----
-    if (tid == 0) {
+    if (tid < 64) {
         int n = B;
-        for (int i = 0; i < B - 1; ++i) {
-            int x = a.draft[(int64_t)s * (B - 1) + i];
-            if (x < 0 || x >= V) {
-                if (a.err) atomicOr(a.err, DD_DEVERR_TOKEN);
-                x = x < 0 ? 0 : V - 1;
+        for (int i0 = 0; i0 < B - 1; i0 += 64) {
+            const int i = i0 + lane;
+            const bool in = i < B - 1;
+            const uint64_t rej = __ballot(in && rejected<T>(a, s, in ? i : 0, in ? lse_p[i] : 0.f, in ? lse_q[i] : 0.f));
+            const int first = rej ? (int)__builtin_ctzll(rej) : 64;
+            if (in && lane <= first && a.err) {   // the tests up to the first rejection count
+                const int x = a.draft[(int64_t)s * (B - 1) + i];
+                if (x < 0 || x >= V) atomicOr(a.err, DD_DEVERR_TOKEN);
             }
-            const float lp = Elem<T>::load1(prow(i), x) - lse_p[i];
-            const float lq = Elem<T>::load1(qrow(i), x) - lse_q[i];
-            const float ratio = fminf(1.f, __builtin_amdgcn_exp2f((lp - lq) * LOG2E));
-            const float u = word_uniform_f(verify_word(a, s, STREAM_VERIFY, i, 0));
-            if (u > ratio) { n = i + 1; break; }
+            if (rej) {
+                n = i0 + first + 1;
+                break;
+            }
         }
-        sh_n = n;
+        if (lane == 0) sh_n = n;
     }
     __syncthreads();
     const int n = sh_n;
     const bool resid = n < B;
-    const char* pr = prow(n - 1);
-    const char* qr = resid ? qrow(n - 1) : nullptr;
+    const char* pr = (const char*)a.p + ((size_t)s * B + n - 1) * a.ld * sizeof(T);
+    const char* qr = resid ? (const char*)a.q + ((size_t)s * (B - 1) + n - 1) * a.ld * sizeof(T) : nullptr;
     const float lp0 = lse_p[n - 1], lq0 = resid ? lse_q[n - 1] : 0.f;
 
     // unnormalised class mass: [p - q]_+ for a rejection, p for the bonus (use_p: residual empty)
@@ -183,28 +269,39 @@ __global__ __launch_bounds__(VT) void verify_kernel(VerifyArgs a, const float* l
     const int nchunk = (V + E - 1) / E;
     auto masses = [&](bool use_p) -> float {
         float tot = 0.f;
-        for (int c0 = 0; c0 < nchunk; c0 += VT) {
-            const int c = c0 + tid;
-            float sum = 0.f;
-            if (c < nchunk) {
-                const uint4 xp = *(const uint4*)(pr + (size_t)c * 16);
-                uint4 xq = make_uint4(0u, 0u, 0u, 0u);
-                if (resid && !use_p) xq = *(const uint4*)(qr + (size_t)c * 16);
+        for (int c0 = 0; c0 < nchunk; c0 += 4 * VT2) {
+            constexpr int VU = 4;
+            uint4 xp[VU], xq[VU];
 #pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (c * E + e < V) sum += cls_mass(Elem<T>::get(xp, e), Elem<T>::get(xq, e), use_p);
+            for (int u = 0; u < VU; ++u) {
+                const int c = min(c0 + u * VT2 + tid, nchunk - 1);
+                xp[u] = *(const uint4*)(pr + (size_t)c * 16);
+                if (resid && !use_p) xq[u] = *(const uint4*)(qr + (size_t)c * 16);
+                else xq[u] = Elem<T>::NEG_INF4;
             }
 #pragma unroll
-            for (int o = 1; o < LPG; o <<= 1) sum += __shfl_xor(sum, o, 64);
-            if ((lane & (LPG - 1)) == 0 && c < nchunk) s_mass[c / LPG] = sum;
-            tot += ((lane & (LPG - 1)) == 0 && c < nchunk) ? sum : 0.f;
+            for (int u = 0; u < VU; ++u) {
+                const int c = c0 + u * VT2 + tid;
+                float sum = 0.f;
+                if (c < nchunk) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        if (c * E + e < V) sum += cls_mass(Elem<T>::get(xp[u], e), Elem<T>::get(xq[u], e), use_p);
+                }
+#pragma unroll
+                for (int o = 1; o < LPG; o <<= 1) sum += __shfl_xor(sum, o, 64);
+                if ((lane & (LPG - 1)) == 0 && c < nchunk) {
+                    s_mass[c / LPG] = sum;
+                    tot += sum;
+                }
+            }
         }
         tot = wave_sum(tot);
         if (lane == 0) sh_tot[tid >> 6] = tot;
         __syncthreads();
         float t = 0.f;
 #pragma unroll
-        for (int w = 0; w < VT / 64; ++w) t += sh_tot[w];
+        for (int w = 0; w < NW; ++w) t += sh_tot[w];
         __syncthreads();
         return t;
     };
@@ -214,48 +311,68 @@ __global__ __launch_bounds__(VT) void verify_kernel(VerifyArgs a, const float* l
         masses(true);
     }
 
-    // ---- two-level draw (one wavefront) ----
-    if ((tid >> 6) != 0) return;
+    // ---- two-level draw (one wavefront): four consecutive words per lane and Philox block ----
+    if (tid >= 64) return;
+    const int ntop = ngroups;
+    auto words = [&](uint32_t stream, int base, int count, int explicit_off, uint32_t (&wd)[4]) {
+        if (a.noise) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                wd[k] = base + k < count ? a.noise[(int64_t)s * a.nu + explicit_off + base + k] : 0u;
+        } else {
+            const Words4 W = philox4x32_10((uint32_t)(base >> 2), a.row0 + (uint32_t)s, a.step, stream,
+                                           (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) wd[k] = W.w[k];
+        }
+    };
+    auto argmax = [&](float best, int bi) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float s2 = __shfl_xor(best, o, 64);
+            const int i2 = __shfl_xor(bi, o, 64);
+            const bool take = s2 > best || (s2 == best && i2 < bi);
+            best = take ? s2 : best;
+            bi = take ? i2 : bi;
+        }
+        return bi;
+    };
     float best = -INFINITY;
     int bi = 0x7FFFFFFF;
-    for (int g = lane; g < ngroups; g += 64) {
-        const float sc = logf(s_mass[g]) + word_gumbel_f(verify_word(a, s, STREAM_TOP, g, B - 1));
-        const bool take = sc > best || (sc == best && g < bi);
-        best = take ? sc : best;
-        bi = take ? g : bi;
-    }
+    for (int g0 = 4 * lane; g0 < ngroups; g0 += 256) {
+        uint32_t wd[4];
+        words(STREAM_TOP, g0, ngroups, B - 1, wd);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float s2 = __shfl_xor(best, o, 64);
-        const int i2 = __shfl_xor(bi, o, 64);
-        const bool take = s2 > best || (s2 == best && i2 < bi);
-        best = take ? s2 : best;
-        bi = take ? i2 : bi;
+        for (int k = 0; k < 4; ++k) {
+            if (g0 + k >= ngroups) continue;
+            const float sc = logf(s_mass[g0 + k]) + word_gumbel_f(wd[k]);
+            const bool take = sc > best || (sc == best && g0 + k < bi);
+            best = take ? sc : best;
+            bi = take ? g0 + k : bi;
+        }
     }
-    const int gstar = bi;
+    const int gstar = argmax(best, bi);
     // no group with a valid score (NaN or +inf logits): report, emit token 0, index nothing
     const bool bad = gstar >= ngroups || !isfinite(lp0) || (resid && !use_p && !isfinite(lq0));
     best = -INFINITY;
     bi = 0x7FFFFFFF;
-    const int ntop = ngroups;
-    const int jend = bad ? 0 : min(V, (gstar + 1) * DD_GUMBEL_GROUP);
-    for (int j = bad ? 0 : gstar * DD_GUMBEL_GROUP + lane; j < jend; j += 64) {
-        const float lpv = Elem<T>::load1(pr, j);
-        const float lqv = (resid && !use_p) ? Elem<T>::load1(qr, j) : 0.f;
-        const float sc = logf(cls_mass(lpv, lqv, use_p)) +
-                         word_gumbel_f(verify_word(a, s, STREAM_CLASS, j, B - 1 + ntop));
-        const bool take = sc > best || (sc == best && j < bi);
-        best = take ? sc : best;
-        bi = take ? j : bi;
-    }
+    const int j0 = bad ? V : gstar * DD_GUMBEL_GROUP + 4 * lane;
+    if (j0 < V) {
+        uint32_t wd[4];
+        words(STREAM_CLASS, j0, V, B - 1 + ntop, wd);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float s2 = __shfl_xor(best, o, 64);
-        const int i2 = __shfl_xor(bi, o, 64);
-        const bool take = s2 > best || (s2 == best && i2 < bi);
-        best = take ? s2 : best;
-        bi = take ? i2 : bi;
+        for (int k = 0; k < 4; ++k) {
+            const int j = j0 + k;
+            if (j >= V) continue;
+            const float lpv = Elem<T>::load1(pr, j);
+            const float lqv = (resid && !use_p) ? Elem<T>::load1(qr, j) : 0.f;
+            const float sc = logf(cls_mass(lpv, lqv, use_p)) + word_gumbel_f(wd[k]);
+            const bool take = sc > best || (sc == best && j < bi);
+            best = take ? sc : best;
+            bi = take ? j : bi;
+        }
     }
+    bi = argmax(best, bi);
     const bool bad_z = bad || bi >= V;
     if (lane == 0) {
         if (bad_z && a.err) atomicOr(a.err, DD_DEVERR_LOGITS);
@@ -303,15 +420,19 @@ dd_status verify_noalloc_scratch(float** out) {
 
 dd_status launch_verify(const VerifyArgs& a, int logits_dtype, float* lse, hipStream_t s) {
     if (a.S == 0) return DD_OK;
-    const int rows = a.S * (2 * a.B - 1);
     const int ngroups = (a.V + DD_GUMBEL_GROUP - 1) / DD_GUMBEL_GROUP;
     const size_t shmem = (size_t)ngroups * sizeof(float);
+    // Up to about 1024 positions everything starts at once and the hint never comes in time: its
+    // launch is left out, and a workgroup takes one row instead of two (S 4, B 16: 7 against 10 us).
+    const int hint = a.B > 2 && (int64_t)a.S * a.B > 1024;
+    if (hint) launch_k(verify_start_kernel, dim3((a.S + 255) / 256), dim3(256), 0, s, a.n_out, a.S, a.B);
+    const dim3 grid((unsigned)(hint ? a.S * a.B : a.S * (2 * a.B - 1)));
     if (logits_dtype == DD_BF16) {
-        launch_k(row_lse_kernel<bf16_t>, dim3(rows), dim3(VT), 0, s, a, lse);
-        launch_k(verify_kernel<bf16_t>, dim3(a.S), dim3(VT), shmem, s, a, (const float*)lse);
+        launch_k(row_lse_kernel<bf16_t>, grid, dim3(VT), 0, s, a, lse, hint);
+        launch_k(verify_kernel<bf16_t>, dim3(a.S), dim3(VT2), shmem, s, a, (const float*)lse);
     } else {
-        launch_k(row_lse_kernel<float>, dim3(rows), dim3(VT), 0, s, a, lse);
-        launch_k(verify_kernel<float>, dim3(a.S), dim3(VT), shmem, s, a, (const float*)lse);
+        launch_k(row_lse_kernel<float>, grid, dim3(VT), 0, s, a, lse, hint);
+        launch_k(verify_kernel<float>, dim3(a.S), dim3(VT2), shmem, s, a, (const float*)lse);
     }
     return launch_status("spec_verify");
 }

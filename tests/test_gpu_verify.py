@@ -157,3 +157,44 @@ def test_spec_verify_degenerate_logits_are_reported():
     assert z1[2] == 0 and z1[3] == 0 and z1[6] == 0 and 1 <= n1[5] <= B and 0 <= z1[5] < V
     keep = [s for s in range(S) if s not in (2, 3, 5, 6)]
     assert np.array_equal(n0[keep], n1[keep]) and np.array_equal(z0[keep], z1[keep])
+
+
+HINT_CASES = [
+    # S, B, V, dtype, noise, closeness: S B at and above the line where kernel 1 works position by
+    # position (1024), blocks of more than one wavefront of drafted tokens
+    (64, 16, 700, "bf16", "philox", 0.5),
+    (65, 16, 700, "bf16", "explicit", 0.5),
+    (300, 4, 515, "fp32", "philox", 1.0),
+    (20, 70, 300, "bf16", "philox", 0.02),
+    (3, 66, 300, "fp32", "explicit", 0.05),
+]
+
+
+@pytest.mark.parametrize("case", HINT_CASES, ids=lambda c: f"S{c[0]}-B{c[1]}-{c[3]}-{c[4]}")
+def test_spec_verify_position_by_position(case):
+    test_spec_verify_parity(case)
+
+
+def test_spec_verify_reports_only_the_tokens_it_tested():
+    """A drafted id outside [0, V) is reported iff its position is tested: up to the first rejection."""
+    torch = torch_or_skip()
+    S, B, V, dt = 130, 9, 400, "bf16"
+    pl, ql, draft = _case(23, S, B, V, dt, 0.6)
+    n, _ = _run_gpu(torch, pl, ql, draft, dt, seed=4, step=1)
+    ld = int(dd.logits_ld(V))
+    p_d, q_d = logits_dev(torch, pl.reshape(S * B, V), dt, ld), logits_dev(torch, ql.reshape(S * (B - 1), V), dt, ld)
+    late = draft.copy()
+    for s in range(S):
+        late[s, n[s]:] = V + 5          # positions after the first rejection (1-based n)
+    assert (late != draft).any()
+    early = draft.copy()
+    early[7, 0] = -3
+    for d, want in ((late, 0), (early, dd.DD_DEVERR_TOKEN)):
+        no = torch.empty(S, dtype=torch.int32, device="cuda")
+        zo = torch.empty_like(no)
+        ws = torch.zeros(dd.spec_verify_workspace_bytes(S, B), dtype=torch.uint8, device="cuda")
+        err = torch.zeros(1, dtype=torch.int32, device="cuda")
+        dd.spec_verify(p_d, q_d, dt, ld, S, B, V, dev_i32(torch, d), no, zo, ws, seed=4, step=1, dev_err=err)
+        assert dd.read_device_error(err) == want
+        if want == 0:
+            assert np.array_equal(no.cpu().numpy(), n)
