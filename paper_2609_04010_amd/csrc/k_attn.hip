@@ -30,6 +30,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <mutex>
 #include <type_traits>
 
 #include "kernels.h"
@@ -40,7 +41,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int AQ = 128;  // queries per workgroup
 constexpr int AK = 64;   // keys per tile
 constexpr int DH = 64;
 constexpr int KROW = DH;   // bf16 per LDS row (128 bytes, no padding: chunks are swizzled)
@@ -94,13 +94,36 @@ DD_DEV void query_window(const AttnArgs& a, int qi, int& pre, int& lo, int& hi) 
     }
 }
 
-template <bool MASKED, bool LISTED = false>
-__global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs a) {
-    __shared__ __attribute__((aligned(1024))) bf16_t Ks[2][AK * KROW];
-    __shared__ __attribute__((aligned(1024))) bf16_t Vs[2][AK * KROW];
-    __shared__ int sh_rng[4][3];
+// KG > 1 (small grids, where a CU would hold one workgroup or none): eight wavefronts, of which KG
+// groups share the key tiles (group kg takes tiles kg, kg + KG, ..) and QG = 8 / KG wavefronts per
+// group own 32 queries each.  Every group has its own pair of K/V buffers; the KG partial results of
+// a query meet in LDS at the end.
+template <int KG> struct AttnShape {
+    static constexpr int NW = KG == 1 ? 4 : 8, QG = NW / KG, Q = 32 * QG;   // wavefronts, queries per workgroup
+    static constexpr int TI = 8 / QG;                // 1 KB K (and V) load instructions per wavefront and tile
+    static constexpr size_t LDS = KG == 1 ? 0 : (size_t)KG * 4 * AK * KROW * sizeof(bf16_t);   // dynamic
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <bool MASKED, bool LISTED, int KG>
+__global__ __launch_bounds__(64 * AttnShape<KG>::NW, KG > 1 ? 2 : MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs a) {
+    using S = AttnShape<KG>;
+    constexpr int AQ = S::Q, QG = S::QG, TI = S::TI;
+    // one group: static arrays; more: [group][buffer] of K tiles, then of V tiles, in dynamic LDS
+    __shared__ __attribute__((aligned(1024))) bf16_t Ks[2][KG == 1 ? AK * KROW : 8];
+    __shared__ __attribute__((aligned(1024))) bf16_t Vs[2][KG == 1 ? AK * KROW : 8];
+    extern __shared__ __attribute__((aligned(1024))) bf16_t attn_smem[];
+    __shared__ int sh_rng[S::NW][3];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = KG == 1 ? tid >> 6 : (tid >> 6) % QG, kg = KG == 1 ? 0 : (tid >> 6) / QG;
+    auto kt = [&](int buf, int x) -> bf16_t* {
+        if constexpr (KG == 1) return &Ks[buf][x];
+        else return attn_smem + (2 * kg + buf) * (AK * KROW) + x;
+    };
+    auto vt = [&](int buf, int x) -> bf16_t* {
+        if constexpr (KG == 1) return &Vs[buf][x];
+        else return attn_smem + (2 * KG + 2 * kg + buf) * (AK * KROW) + x;
+    };
     // one-dimensional grid: the query blocks of one (batch, head) run on one XCD, one after another,
     // so that head's K and V are fetched into that XCD's L2 once and then re-read from it
     const int nqb = (a.L + AQ - 1) / AQ;
@@ -168,14 +191,14 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
         lomax = wave_max_i(qi < L ? qlo : INT_MIN);
         himin = wave_min_i(qi < L ? qhi : INT_MAX);
         if (lane == 0) {
-            sh_rng[wave][0] = pmax;
-            sh_rng[wave][1] = wlo;
-            sh_rng[wave][2] = whi;
+            sh_rng[tid >> 6][0] = pmax;
+            sh_rng[tid >> 6][1] = wlo;
+            sh_rng[tid >> 6][2] = whi;
         }
         __syncthreads();
         int gp = 0, glo = INT_MAX, ghi = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < S::NW; ++w) {
             gp = max(gp, sh_rng[w][0]);
             glo = min(glo, sh_rng[w][1]);
             ghi = max(ghi, sh_rng[w][2]);
@@ -192,17 +215,17 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
     auto tile_of = [&](int k) { return k < tp ? k : tw0 + (k - tp); };
 
     // Tile loads: 8 KB of K and 8 KB of V per tile, eight 1 KB wave instructions each; wavefront w
-    // issues K and V instructions 2w and 2w + 1 (rows 8 i .. 8 i + 7).  Lane l fills LDS slot l % 8 of
+    // of a group issues K and V instructions TI w .. TI w + TI - 1 (rows 8 i .. 8 i + 7).  Lane l fills LDS slot l % 8 of
     // row 8 i + l / 8 with the global chunk that belongs there.  Keys past L read row L - 1 (their
     // scores are masked to -inf, so their probabilities are exactly 0).
     // Per-lane offsets (elements from the tile's first key row, under 64 rows of the qkv matrix, so
     // well inside 32 bits) are fixed; a tile adds kb0 rows.  The ragged last tile (rows past L read
     // row L - 1) takes a separate, scalar-branched path.
     const int sl = lane & 7;
-    int ok[2], ov[2];
+    int ok[TI], ov[TI];
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii) {
-        const int r = 8 * (2 * wave + ii) + (lane >> 3);
+    for (int ii = 0; ii < TI; ++ii) {
+        const int r = 8 * (TI * wave + ii) + (lane >> 3);
         ok[ii] = r * (int)a.ld + d + h * DH + 8 * (sl ^ ksw(r));
         ov[ii] = r * (int)a.ld + 2 * d + h * DH + 8 * (sl ^ vsw(r));
     }
@@ -210,20 +233,20 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
         const bf16_t* tb = base + (int64_t)kb0 * a.ld;
         if (kb0 + AK <= L) {
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int i = 2 * wave + ii;
-                __builtin_amdgcn_global_load_lds((gbl_void*)(tb + ok[ii]), (lds_void*)&Ks[buf][8 * i * KROW], 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((gbl_void*)(tb + ov[ii]), (lds_void*)&Vs[buf][8 * i * KROW], 16, 0, 0);
+            for (int ii = 0; ii < TI; ++ii) {
+                const int i = TI * wave + ii;
+                __builtin_amdgcn_global_load_lds((gbl_void*)(tb + ok[ii]), (lds_void*)kt(buf, 8 * i * KROW), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gbl_void*)(tb + ov[ii]), (lds_void*)vt(buf, 8 * i * KROW), 16, 0, 0);
             }
         } else {
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int i = 2 * wave + ii, r = 8 * i + (lane >> 3);
+            for (int ii = 0; ii < TI; ++ii) {
+                const int i = TI * wave + ii, r = 8 * i + (lane >> 3);
                 const bf16_t* row = tb + (int64_t)min(r, L - 1 - kb0) * a.ld + h * DH;
                 __builtin_amdgcn_global_load_lds((gbl_void*)(row + d + 8 * (sl ^ ksw(r))),
-                                                 (lds_void*)&Ks[buf][8 * i * KROW], 16, 0, 0);
+                                                 (lds_void*)kt(buf, 8 * i * KROW), 16, 0, 0);
                 __builtin_amdgcn_global_load_lds((gbl_void*)(row + 2 * d + 8 * (sl ^ vsw(r))),
-                                                 (lds_void*)&Vs[buf][8 * i * KROW], 16, 0, 0);
+                                                 (lds_void*)vt(buf, 8 * i * KROW), 16, 0, 0);
             }
         }
     };
@@ -235,7 +258,7 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
     // One 64-key tile; `part`: the tile is not entirely visible to every query of the wavefront
     // (the ragged last tile, or pattern boundaries), so scores get the per-element key test.
     auto tile = [&](int k, bool part) {
-        const int buf = k & 1, kb0 = tile_of(k) * AK;
+        const int buf = (k / KG) & 1, kb0 = tile_of(k) * AK;
         f32x16 sacc[2];
         // The MFMA blocks (QK^T here, PV below) run at wave priority 1, so that of the four
         // wavefronts of a SIMD the one with MFMAs to issue goes first and the softmax VALU work
@@ -250,7 +273,7 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
                     const int kr = kb * 32 + (lane & 31);
-                    const bf16x8 kf = *(const bf16x8*)&Ks[buf][kr * KROW + 8 * ((2 * kk + grp) ^ ksw(kr))];
+                    const bf16x8 kf = *(const bf16x8*)kt(buf, kr * KROW + 8 * ((2 * kk + grp) ^ ksw(kr)));
                     sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], sacc[kb], 0, 0, 0);
                 }
             }
@@ -330,8 +353,8 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
             for (int blk = 0; blk < 2; ++blk) {
                 // column blk 32 + 16 ((lane >> 4) & 1) + 4 (lane & 3): chunk vc, half vh
                 const int vc = 4 * blk + 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1), vh = 4 * (lane & 1);
-                const v4s lo = ds_read_tr16(&Vs[buf][vk * KROW + 8 * (vc ^ vsw(vk)) + vh]);
-                const v4s hi = ds_read_tr16(&Vs[buf][(vk + 8) * KROW + 8 * (vc ^ vsw(vk + 8)) + vh]);
+                const v4s lo = ds_read_tr16(vt(buf, vk * KROW + 8 * (vc ^ vsw(vk)) + vh));
+                const v4s hi = ds_read_tr16(vt(buf, (vk + 8) * KROW + 8 * (vc ^ vsw(vk + 8)) + vh));
                 const v8s v8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                 const bf16x8 vf = __builtin_bit_cast(bf16x8, v8);
                 o[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[blk], 0, 0, 0);
@@ -345,23 +368,69 @@ __global__ __launch_bounds__(256, MASKED ? 3 : 4) void attn_bf16_kernel(AttnArgs
     };
     // tile k + 1 streams into the other buffer while tile k is computed; that buffer was last
     // read in tile k - 1, which every wavefront finished before the barrier ending it
-    if (ntiles > 0) dma(tile_of(0) * AK, 0);
+    if (kg < ntiles) dma(tile_of(kg) * AK, 0);
     __builtin_amdgcn_s_waitcnt(0x3F70);          // vmcnt(0)
     __syncthreads();
-    for (int k = 0; k < ntiles; ++k) {
+    for (int k0 = 0; k0 < ntiles; k0 += KG) {
+        const int k = k0 + kg;                   // this group's tile (none past ntiles)
         // the next tile's loads go out at the top wave priority, ahead of the MFMA and softmax
         // work of the SIMD's other wavefronts (61.5-62.2 vs 63.2-65.2 us at B16 L1024)
         __builtin_amdgcn_s_setprio(3);
-        if (k + 1 < ntiles) dma(tile_of(k + 1) * AK, (k + 1) & 1);
+        if (k + KG < ntiles) dma(tile_of(k + KG) * AK, (k / KG + 1) & 1);
         __builtin_amdgcn_s_setprio(0);
-        const int kb0 = tile_of(k) * AK;
-        // is the tile entirely visible to every query of this wavefront (and inside L)?
-        const bool whole = MASKED ? (kb0 + AK <= pmin || (kb0 >= lomax && kb0 + AK <= himin)) : kb0 + AK <= L;
-        if (wave_needs(kb0)) tile(k, !whole);
-        __builtin_amdgcn_s_waitcnt(0x3F70);      // vmcnt(0): this lane's loads of tile k + 1 landed
+        if (KG == 1 || k < ntiles) {
+            const int kb0 = tile_of(k) * AK;
+            // is the tile entirely visible to every query of this wavefront (and inside L)?
+            const bool whole = MASKED ? (kb0 + AK <= pmin || (kb0 >= lomax && kb0 + AK <= himin)) : kb0 + AK <= L;
+            if (wave_needs(kb0)) tile(k, !whole);
+        }
+        __builtin_amdgcn_s_waitcnt(0x3F70);      // vmcnt(0): this lane's loads of tile k + KG landed
         __syncthreads();                          // ... everyone's
     }
 
+    if constexpr (KG > 1) {
+        // groups 1.. leave (m, l, O) in LDS (the tiles are done with), group 0 takes them to the common
+        // exponent reference.  A group that met no visible key has m = -inf and counts nothing.
+        float4* po = (float4*)attn_smem;                             // [KG - 1][QG][8][64]
+        float2* pm = (float2*)(po + (KG - 1) * QG * 8 * 64);         // [KG - 1][QG][64]
+        if (kg > 0) {
+            const int slot = (kg - 1) * QG + wave;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                po[(slot * 8 + i) * 64 + lane] = make_float4(o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1],
+                                                             o[i >> 2][4 * (i & 3) + 2], o[i >> 2][4 * (i & 3) + 3]);
+            pm[slot * 64 + lane] = make_float2(mrow, lpart);
+        }
+        __syncthreads();
+        if (kg > 0) return;
+        float2 ml[KG - 1];
+        float mx = mrow;
+#pragma unroll
+        for (int w = 0; w < KG - 1; ++w) {
+            ml[w] = pm[(w * QG + wave) * 64 + lane];
+            mx = fmaxf(mx, ml[w].x);
+        }
+        const float ref = mx == -INFINITY ? 0.f : mx;
+        const float f0 = __builtin_amdgcn_exp2f(mrow - ref);
+        lpart *= f0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[i][e] *= f0;
+#pragma unroll
+        for (int w = 0; w < KG - 1; ++w) {
+            const float f = __builtin_amdgcn_exp2f(ml[w].x - ref);
+            lpart = fmaf(ml[w].y, f, lpart);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 p = po[((w * QG + wave) * 8 + i) * 64 + lane];
+                o[i >> 2][4 * (i & 3)] = fmaf(p.x, f, o[i >> 2][4 * (i & 3)]);
+                o[i >> 2][4 * (i & 3) + 1] = fmaf(p.y, f, o[i >> 2][4 * (i & 3) + 1]);
+                o[i >> 2][4 * (i & 3) + 2] = fmaf(p.z, f, o[i >> 2][4 * (i & 3) + 2]);
+                o[i >> 2][4 * (i & 3) + 3] = fmaf(p.w, f, o[i >> 2][4 * (i & 3) + 3]);
+            }
+        }
+    }
     const float l = lpart + __shfl_xor(lpart, 32, 64);
     const float inv = 1.0f / l;
     if (qi < L) {
@@ -514,23 +583,46 @@ static int num_cus_attn() {
     return n;
 }
 
-dd_status launch_attn(int dtype, const AttnArgs& a0, hipStream_t s) {
-    const int dh = a0.d / a0.H;
+template <int KG>
+static void launch_attn_bf16(AttnArgs a, hipStream_t s) {
+    using S = AttnShape<KG>;
+    const int nqb = (int)ceil_div(a.L, S::Q);
+    // resident workgroups per XCD (three per CU at the pattern kernel's register count; with key
+    // groups two or one), shared by the query blocks of hgroup (batch, head) pairs
+    a.hgroup = std::max(1, (num_cus_attn() / 8) * (KG == 1 ? 3 : 4 / KG) / nqb);
+    static std::once_flag once;   // opt-in to more than 64 KB of LDS per workgroup
+    std::call_once(once, [] {
+        for (const void* f : {(const void*)attn_bf16_kernel<true, false, KG>, (const void*)attn_bf16_kernel<false, true, KG>,
+                              (const void*)attn_bf16_kernel<false, false, KG>})
+            (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
+    });
+    const dim3 grid((unsigned)(nqb * a.H * a.B)), blk(64 * S::NW);
+    if (a.mask) launch_k((attn_bf16_kernel<true, false, KG>), grid, blk, S::LDS, s, a);
+    else if (a.qrows) launch_k((attn_bf16_kernel<false, true, KG>), grid, blk, S::LDS, s, a);
+    else launch_k((attn_bf16_kernel<false, false, KG>), grid, blk, S::LDS, s, a);
+}
+
+dd_status launch_attn(int dtype, const AttnArgs& a, hipStream_t s) {
+    const int dh = a.d / a.H;
     ProfScope ps(KC_ATTN, s);
-    AttnArgs a = a0;
-    // resident workgroups per XCD (three per CU at the pattern kernel's register count), shared by
-    // the query blocks of hgroup (batch, head) pairs
-    const int nqb = ceil_div(a.L, AQ);
-    a.hgroup = std::max(1, (num_cus_attn() / 8) * 3 / nqb);
     if (a.qrows && (dtype != DD_BF16 || a.mask || !a.qseq)) {
         set_error("listed queries need the bf16 path, no pattern and the sequence starts");
         return DD_E_UNSUPPORTED;
     }
     if (dtype == DD_BF16) {
-        const dim3 grid((unsigned)(nqb * a.H * a.B));
-        if (a.mask) launch_k(attn_bf16_kernel<true>, grid, dim3(256), 0, s, a);
-        else if (a.qrows) launch_k((attn_bf16_kernel<false, true>), grid, dim3(256), 0, s, a);
-        else launch_k(attn_bf16_kernel<false>, grid, dim3(256), 0, s, a);
+        const int64_t bh = (int64_t)a.H * a.B, cus = num_cus_attn();
+        // Key groups where the query blocks alone leave CUs idle or unevenly loaded (12 heads, us with
+        // 1 / 2 / 4 groups; full, then causal): B 1 L 1024 27.0 / 16.7 / 12.4, 25.7 / 19.3 / 14.7; B 2
+        // L 1000 27.3 / 17.3 / 21.4, 27.7 / 19.5 / 21.6; at 1.5 blocks of 128 per CU B 4 L 1024 30.4 /
+        // 30.8 / 31.2, 28.5 / 27.2 / 33.6, B 8 L 512 19.6 / 21.2 / 22.9, B 1 L 4096 95.9 / 89.8 / 80.8,
+        // 83.8 / 58.7 / 67.7.  By B, H and L alone: a query's sums are the same listed or not.
+        const int64_t wg = bh * ceil_div(a.L, 128);
+        int kg = 1;
+        if (bh * ceil_div(a.L, 64) <= cus) kg = 4;
+        else if (wg <= cus || (a.L >= 2048 && wg < 2 * cus)) kg = 2;
+        if (kg == 4) launch_attn_bf16<4>(a, s);
+        else if (kg == 2) launch_attn_bf16<2>(a, s);
+        else launch_attn_bf16<1>(a, s);
     } else {
         const dim3 grid((unsigned)(ceil_div(a.L, 32) * a.H * a.B));
 #define DD_ATTN_F32(DV)                                                                         \

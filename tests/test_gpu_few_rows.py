@@ -67,6 +67,48 @@ def test_forward_on_few_rows_matches_oracle(case):
     assert err <= TOL
 
 
+ATTN_CASES = [
+    # B, L, pattern, block (12 heads): the key groups of the attention at the lines between 4, 2 and 1
+    # groups, groups without a tile, ragged last tiles
+    (1, 65, None, 0), (1, 130, "causal", 0), (1, 200, "draft_train", 4),
+    (5, 256, None, 0), (6, 256, "block_causal", 48), (2, 641, None, 0), (2, 641, "causal", 0),
+    (1, 2049, "causal", 0), (1, 2049, None, 0), (22, 129, None, 0), (22, 130, "draft_train", 13),
+]
+
+
+@pytest.mark.parametrize("case", ATTN_CASES, ids=lambda c: f"B{c[0]}-L{c[1]}-{c[2]}")
+def test_attention_key_groups_match_oracle(case):
+    """One layer whose attention weights are large enough (x 8) that its probabilities are not flat.
+    Bar as above."""
+    torch = torch_or_skip()
+    B, L, pattern, block = case
+    say("attention", case)
+    cfg = workloads.model_cfg(2, n_layers=1, vocab=64, d_mlp=128, max_len=L)
+    P = oparams.init_params(cfg, 44)
+    P["l0.w_qkv"] = P["l0.w_qkv"].copy()
+    P["l0.w_qkv"][:2 * cfg["d_model"]] *= 8.0      # exact in bf16
+    blob = dd.pack_params(cfg, oparams.storage_tensors(cfg, P))
+    buf = torch.zeros(blob.size, dtype=torch.uint8, device="cuda")
+    dd.init_params(cfg, buf, host_blob=blob)
+    z = workloads.masked_state(79, B, L, cfg["vocab"], 0.3)
+    ld = int(dd.logits_ld(cfg["vocab"]))
+    logits = torch.zeros((B * L, ld), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((dd.workspace_bytes(cfg, B, L),), 0xFF, dtype=torch.uint8, device="cuda")
+    dd.workspace_reset(ws)
+    vis, mask = None, None
+    if pattern:
+        host = dd.attn_mask_build(pattern, L, block)
+        mask = dev_i32(torch, host.reshape(-1))
+        j = np.arange(L)[None, :]
+        vis = (j < host[0][:, None]) | ((j >= host[1][:, None]) & (j < host[2][:, None]))
+    dd.denoise_forward_ex(cfg, buf, dev_i32(torch, z.reshape(-1)), B, L, 0.5, logits, ld, ws, attn_mask=mask)
+    got = logits[:, :cfg["vocab"]].float().cpu().numpy().reshape(B, L, -1)
+    assert dd.read_device_error(ws[:4].view(torch.int32)) == 0
+    err = float(np.abs(got - oforward.forward(cfg, P, z, 0.5, vis)).max())
+    say(f"max |dlogit| = {err:.3e}")
+    assert err <= TOL
+
+
 F32_CASES = [
     # d_model, heads (head dim 16 / 32 / 64 / 128), layers, B, L, pattern, block
     (64, 4, 2, 3, 1, None, 0),
