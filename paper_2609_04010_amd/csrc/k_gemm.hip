@@ -800,15 +800,15 @@ struct Plan {
     int tile, splits;
 };
 
-// Splits of a residual projection on ring tiles: 4 ways up to 512 rows, 2 up to 2048 (attention output,
-// K 768, N 768: 4.5 / 5.0 / 8.1 us with 4 / 2 / 1 at M 64, 7.6 / 7.4 with 2 / 1 at M 1024; MLP down,
-// K 3072: 7.0 / 10.5 / 16 at M 64, 13.6 with 2 against 13.7 with 4 at M 1024, 20.6 with 2 against 21.9
-// with 1 at M 2000; a split more costs the normalisation 0.5 to 2 us), at least k_min of K each.  Steps of M, not the best per M,
-// and cut by the model's own K, so that a row's sums are the same in calls of similar size and with
-// adapters switched off.
+// Splits of a residual projection on ring tiles, at least k_min of K each.  Attention output (K 768, N
+// 768) 4.5 / 5.5 / 7.2 us with 4 / 2 / 1 at M 64, 6.7 / 6.4 / 8.1 at M 512, 7.6 / 7.4 with 2 / 1 at M
+// 1024; MLP down (K 3072) 7.0 / 10.5 / 16 at M 64, 12.7 / 13.5 / 16 at M 512, 13.6 with 2 against 15.6
+// at M 1024, 23.4 against 25.4 at M 2000; the normalisation pays 2 us for the first slab and 1 us for
+// another per 1024 rows (M 2000: 5.1 -> 9.1 us).  Steps of M, not the best per M, and cut by the
+// model's own K, so that a row's sums are the same in calls of similar size and with adapters off.
 static int ring_splits(const GemmArgs& g, int max_splits, int k_min) {
-    const int want = g.M <= 512 ? 4 : g.M <= 2048 ? 2 : 1;
     const int k = g.k_base > 0 ? g.k_base : g.K;
+    const int want = g.M <= 512 ? (k >= 2048 ? 4 : 2) : g.M <= 1024 && k >= 2048 ? 2 : 1;
     return std::max(1, std::min(std::min(want, max_splits), k / k_min));
 }
 
@@ -842,7 +842,7 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
         t_best = 9.0 + (double)(g.K / BK) * (narrow ? r192 * 1.08 : r256 * 1.79);
     }
     const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits, 2 * BK) : 1;   // two K-tiles each
-    const double slab_us = 0.4 + (double)g.M * g.N * 4 / 5e6;
+    const double slab_us = 0.4 + (double)g.M * g.N * 4 / 2e6;
     for (int tile = 0; tile < 3; ++tile) {
         const double t = gemm_ring_us((RingTile)tile, g.M, g.N, g.K, sp, cus) + (sp - 1) * slab_us;
         if (best.tile < 0 || t < t_best) {
