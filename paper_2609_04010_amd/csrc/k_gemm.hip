@@ -800,19 +800,23 @@ struct Plan {
     int tile, splits;
 };
 
-// Splits of a residual projection on ring tiles, at least k_min of K each.  Attention output (K 768, N
+// Splits of a residual projection on ring tiles, at least two K-tiles each.  Attention output (K 768, N
 // 768) 4.5 / 5.5 / 7.2 us with 4 / 2 / 1 at M 64, 6.7 / 6.4 / 8.1 at M 512, 7.6 / 7.4 with 2 / 1 at M
 // 1024; MLP down (K 3072) 7.0 / 10.5 / 16 at M 64, 12.7 / 13.5 / 16 at M 512, 13.6 with 2 against 15.6
 // at M 1024, 23.4 against 25.4 at M 2000; the normalisation pays 2 us for the first slab and 1 us for
 // another per 1024 rows (M 2000: 5.1 -> 9.1 us).  Steps of M, not the best per M, and cut by the
 // model's own K, so that a row's sums are the same in calls of similar size and with adapters off.
-static int ring_splits(const GemmArgs& g, int max_splits, int k_min) {
+static int ring_splits(const GemmArgs& g, int max_splits) {
     const int k = g.k_base > 0 ? g.k_base : g.K;
     const int want = g.M <= 512 ? (k >= 2048 ? 4 : 2) : g.M <= 1024 && k >= 2048 ? 2 : 1;
-    return std::max(1, std::min(std::min(want, max_splits), k / k_min));
+    return std::max(1, std::min(std::min(want, max_splits), k / (2 * BK)));
 }
 
-// The smallest estimated time.  The 256-row tiles (K % 128 == 0) in whole rounds of workgroups over
+static int64_t tiles_of(const GemmArgs& g, int bm, int bn) {
+    return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+}
+
+// The smallest estimated time, or 32 x 32 tiles where those do not fill the CUs.  The 256-row tiles (K % 128 == 0) in whole rounds of workgroups over
 // the CUs: the N width (256 or 192) with the smaller time (a round of 192-wide tiles takes about 0.85
 // of a round of 256-wide ones), in the 8-wavefront form (two wavefronts per SIMD, 2-6 % faster than
 // four wavefronts of twice the sub-tile), per K-tile 1.08 us (192) or 1.79 us (256) and 9 us besides,
@@ -831,6 +835,9 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
         return {forced <= 2 ? forced : forced == 3 ? 0 : 1, 1};
     }
     const int cus = num_cus();
+    // (residual projections only up to 128 rows, so that their K order stays that of the 64 x 64 tiles
+    // over the row counts of ring_splits's first step)
+    if (tiles_of(g, 32, 32) <= cus && (epi != EPI_BIAS_RESID || g.M <= 128)) return {RING_32K, 1};
     Plan best = {-1, 1};
     double t_best = 0.0;
     if (wide_ok && g.N > 128) {
@@ -841,7 +848,7 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
         best.tile = narrow ? 7 : 6;
         t_best = 9.0 + (double)(g.K / BK) * (narrow ? r192 * 1.08 : r256 * 1.79);
     }
-    const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits, 2 * BK) : 1;   // two K-tiles each
+    const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits) : 1;
     const double slab_us = 0.4 + (double)g.M * g.N * 4 / 2e6;
     for (int tile = 0; tile < 3; ++tile) {
         const double t = gemm_ring_us((RingTile)tile, g.M, g.N, g.K, sp, cus) + (sp - 1) * slab_us;
@@ -854,7 +861,7 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
 }
 
 int gemm_splits(int dtype, int epi, const GemmArgs& g, int max_splits) {
-    return dtype == DD_BF16 ? plan_tile(g, epi, max_splits).splits : ring_splits(g, max_splits, BK);
+    return dtype == DD_BF16 ? plan_tile(g, epi, max_splits).splits : 1;
 }
 
 template <int EPI, int ROLE, int TBN, int WGM, int WGN, int DMR = DM>
@@ -877,7 +884,13 @@ static void launch_dl(const GemmArgs& g, hipStream_t s) {
 
 template <int EPI, int ROLE>
 static void launch_epi(int dtype, const GemmArgs& g, hipStream_t s) {
-    if (dtype == DD_FP32) return launch_gemm_ring(dtype, RING_64_DEEP, EPI, g, s);
+    if (dtype == DD_FP32) {
+        // the smallest tile that fits the CUs once: the matrix cores bound every one of them (M 256, K 768:
+        // N 768 9.3 / 19.1 us with 32 x 32 / 64 x 64, N 2304 27.4 / 20.8; M 512, N 768 12.5 us with 32 x 64)
+        const int cus = num_cus();
+        const RingTile t = tiles_of(g, 32, 32) <= cus ? RING_32K : tiles_of(g, 32, 64) <= cus ? RING_32X64 : RING_64_DEEP;
+        return launch_gemm_ring(dtype, t, EPI, g, s);
+    }
     int tile = g.tile_hint > 0 ? g.tile_hint - 1 : plan_tile(g, EPI, std::max(g.splits, 1)).tile;
     // the ring instance of the 256 x 192 tile takes no gathered rows and no separate residual
     // input: the four-wavefront form

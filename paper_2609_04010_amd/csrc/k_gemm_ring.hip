@@ -24,6 +24,11 @@
 // the matrix cores: 12 layers d 768 on 256 rows 15.3 -> 1.47 ms per forward pass against the VALU
 // kernel it replaced (with the attention of k_attn.hip), error against float64 1.2e-6 -> 0.6e-6.
 //
+// Where even 32 x 32 tiles do not fill the CUs, four wavefronts share such a tile's K-tiles (each with
+// stages of its own) and their sums meet in LDS: the adapter down-projection of 1320 rows to rank 64,
+// K 3072 15.1 -> 7.7 us, K 768 6.0 -> 4.8; M 32, N 2304, K 768 6.2 -> 4.9; fp32, M 128, N 1024, K 256
+// 9.8 -> 6.4.
+//
 // K needs only K % 8 == 0: the chunks of the last K-tile past K are loaded from the row's first chunk
 // (in bounds) and their fragments are replaced by zeros.
 #include <math.h>
@@ -60,14 +65,15 @@ template <> struct RingOp<float> {
 DD_DEV float ring_bias(const bf16_t* b, int i) { return bf16_to_f32(b[i]); }
 DD_DEV float ring_bias(const float* b, int i) { return b[i]; }
 
-// BM x BN x one K-tile tiles over WGM x WGN wavefronts of MB x NB 32x32 MFMA blocks, NST stages
-template <int BM_, int BN_, int WGM_, int WGN_, int NST_> struct RingShape {
-    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NST = NST_;
-    static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
+// BM x BN x one K-tile tiles over WGM x WGN wavefronts of MB x NB 32x32 MFMA blocks, NST stages; with
+// KG > 1, KG such sets of wavefronts and stages share a tile's K-tiles and their sums meet in LDS
+template <int BM_, int BN_, int WGM_, int WGN_, int NST_, int KG_ = 1> struct RingShape {
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NST = NST_, KG = KG_;
+    static constexpr int NW = WGM * WGN, THREADS = 64 * NW * KG;   // NW: wavefronts per K group
     static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
     static constexpr int NA = BM / 8 / NW, NWL = BN / 8 / NW, NL = NA + NWL;   // 1 KB loads per wave and K-tile
     static constexpr int STAGE = (BM + BN) * ROWB;   // bytes
-    static constexpr size_t LDS = (size_t)NST * STAGE;
+    static constexpr size_t LDS = (size_t)KG * NST * STAGE;
     static constexpr int WG_PER_CU = LDS * 2 <= 160 * 1024 ? 2 : 1;
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && WM % 32 == 0 && WN % 32 == 0, "split");
     static_assert(LDS <= 160 * 1024 && NST >= 2 && (NST - 2) * NL < 64, "stages; the wait counts the loads");
@@ -78,14 +84,16 @@ template <int BM_, int BN_, int WGM_, int WGN_, int NST_> struct RingShape {
 template <int N> DD_DEV void wait_vm() { __builtin_amdgcn_s_waitcnt(0x3F70 | (N & 15) | ((N >> 4) << 14)); }
 
 template <typename T, int EPI, class S>
-__global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_CU * S::NW / 4 : 1) void gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW * S::KG >= 8 ? S::WG_PER_CU * S::NW * S::KG / 4 : 1) void gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     constexpr int MB = S::MB, NB = S::NB, NA = S::NA, NWL = S::NWL, NST = S::NST;
     constexpr int AROWS = S::BM / S::NW, WROWS = S::BN / S::NW;
     using Op = RingOp<T>;
     constexpr int KT = Op::KT, CH = Op::CH, ES = sizeof(T);
     extern __shared__ __attribute__((aligned(1024))) char ring_smem[];
-    char* smem = ring_smem;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int KG = S::KG;
+    const int kg = KG == 1 ? 0 : (tid >> 6) / S::NW, wave = KG == 1 ? tid >> 6 : (tid >> 6) % S::NW;
+    char* smem = ring_smem + kg * (NST * S::STAGE);
     const int wm = wave / S::WGN, wn = wave % S::WGN;
     int M = g.M;
     if (g.m_count) {
@@ -108,7 +116,11 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
     const int m0 = tm * S::BM, n0 = tn * S::BN;
     const int nkt = (g.K + KT - 1) / KT, klast = g.K - (nkt - 1) * KT;   // valid k of the last K-tile
     const int nkb = g.k_base > 0 ? (g.k_base + KT - 1) / KT : nkt;   // K-tiles that are cut evenly
-    const int kt0 = split * nkb / nsplit, kt1 = split + 1 == nsplit ? nkt : (split + 1) * nkb / nsplit;
+    const int ks0 = split * nkb / nsplit, ks1 = split + 1 == nsplit ? nkt : (split + 1) * nkb / nsplit;
+    // K group kg takes nt K-tiles from kt0; the last groups may have fewer (`mine`): they load the
+    // split's last K-tile again and leave it out, so that every wavefront meets the same barriers
+    const int nt = (ks1 - ks0 + KG - 1) / KG, kt0 = ks0 + kg * nt;
+    const int mine = KG == 1 ? nt : max(0, min(nt, ks1 - kt0));
 
     // This lane's 16-byte slot of row r holds K-chunk (lane % 8) ^ ((r >> 1) & 7).  Byte offsets from
     // the tile's first row (under 256 rows, so 32 bits), and the chunk's first k in the K-tile.
@@ -129,6 +141,7 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
         offW[i] = (uint32_t)(min(rl, g.N - 1 - n0) * (int)g.ldw + chW[i]) * (uint32_t)ES;
     }
     auto load = [&](int t, int stage, auto whole_c) {
+        if (KG > 1) t = min(t, ks1 - 1);
         char* st = smem + stage * S::STAGE;
         const char* ap = Ab + (int64_t)t * ROWB;
         const char* wp = Wb + (int64_t)t * ROWB;
@@ -173,7 +186,7 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
                 for (int j4 = 0; j4 < 4; ++j4) {
                     const int n = min(n0 + wn * S::WN + i * 32 + 8 * j4 + 4 * (lane >> 5), g.N - 4);
                     float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (split == 0) h = *(const float4*)(C + hrow[j] * g.ldc + n);
+                    if (split == 0 && kg == 0) h = *(const float4*)(C + hrow[j] * g.ldc + n);
                     acc[i][j][4 * j4] = h.x;
                     acc[i][j][4 * j4 + 1] = h.y;
                     acc[i][j][4 * j4 + 2] = h.z;
@@ -255,7 +268,6 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
         asm volatile("s_barrier" ::: "memory");
     };
 
-    const int nt = kt1 - kt0;
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p)
         if (p < nt) load(kt0 + p, p, std::false_type{});
@@ -281,14 +293,18 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
             rd = rd + 1 == NST ? 0 : rd + 1;
             ld = ld + 1 == NST ? 0 : ld + 1;
             __builtin_amdgcn_sched_barrier(0);
-        } else if (kt1 == nkt && klast < KT) {
-            clear_past(cur);
+        }
+        if constexpr (!steady) {
+            if (kt0 + t == nkt - 1 && klast < KT) clear_past(cur);
+            if (KG > 1 && t >= mine) return;
         }
         mfmas(cur);
         __builtin_amdgcn_sched_barrier(0);
     };
     int t = 0;
-    for (; t + NST + 1 < nt; t += 2) {   // the last K-tile, which may be ragged, is loaded below
+    // (the last K-tile, which may be ragged, is loaded below; all groups leave this loop together)
+    const int nsteady = KG == 1 ? nt : ks1 - ks0 - (KG - 1) * nt;
+    for (; t + NST + 1 < nsteady; t += 2) {
         step(t, f0, f1, std::true_type{});
         step(t + 1, f1, f0, std::true_type{});
     }
@@ -297,6 +313,33 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW >= 8 ? S::WG_PER_C
         if (t + 1 < nt) step(t + 1, f1, f0, std::false_type{});
     }
     __syncthreads();   // the stages become the epilogue's staging area
+    smem = ring_smem;
+    if constexpr (KG > 1) {
+        float4* part = (float4*)ring_smem;   // [KG - 1][NW][4 MB NB][64]
+        constexpr int PV = 4 * MB * NB;
+        static_assert((size_t)(KG - 1) * S::NW * PV * 64 * 16 <= S::LDS, "partial sums");
+        if (kg > 0) {
+#pragma unroll
+            for (int i = 0; i < PV; ++i) {
+                const f32x16& c = acc[i / 4 / MB][i / 4 % MB];
+                part[(((kg - 1) * S::NW + wave) * PV + i) * 64 + lane] =
+                    make_float4(c[4 * (i & 3)], c[4 * (i & 3) + 1], c[4 * (i & 3) + 2], c[4 * (i & 3) + 3]);
+            }
+        }
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int w = 0; w < KG - 1; ++w)
+#pragma unroll
+                for (int i = 0; i < PV; ++i) {
+                    const float4 p = part[((w * S::NW + wave) * PV + i) * 64 + lane];
+                    f32x16& c = acc[i / 4 / MB][i / 4 % MB];
+                    c[4 * (i & 3)] += p.x; c[4 * (i & 3) + 1] += p.y; c[4 * (i & 3) + 2] += p.z; c[4 * (i & 3) + 3] += p.w;
+                }
+        }
+        __syncthreads();
+        if (kg > 0) return;
+    }
 
     if constexpr (EPI == EPI_BIAS_RESID || ES == 4) {
         // fp32 rows: one 32 x 32 block at a time through this wavefront's 4 KB, chunk-swizzled by row,
@@ -414,12 +457,18 @@ static void launch_shape(const GemmArgs& g, hipStream_t s) {
 
 template <int EPI>
 static void launch_epi(int dtype, RingTile tile, const GemmArgs& g, hipStream_t s) {
-    // fp32: the matrix cores are the bound on any tile (a K-tile of 32 is 1024 MFMA cycles per
-    // wavefront), so only the small one
-    if (dtype == DD_FP32) return launch_shape<float, EPI, RingShape<64, 64, 2, 2, 4>>(g, s);
+    if (dtype == DD_FP32) {
+        switch (tile) {
+            case RING_32K: launch_shape<float, EPI, RingShape<32, 32, 1, 1, 4, 4>>(g, s); break;
+            case RING_32X64: launch_shape<float, EPI, RingShape<32, 64, 1, 2, 3, 2>>(g, s); break;
+            default: launch_shape<float, EPI, RingShape<64, 64, 2, 2, 4>>(g, s); break;
+        }
+        return;
+    }
     switch (tile) {
         case RING_128: launch_shape<bf16_t, EPI, RingShape<128, 128, 4, 2, 4>>(g, s); break;
         case RING_64_DEEP: launch_shape<bf16_t, EPI, RingShape<64, 64, 2, 2, 4>>(g, s); break;
+        case RING_32K: launch_shape<bf16_t, EPI, RingShape<32, 32, 1, 1, 4, 4>>(g, s); break;
         default: launch_shape<bf16_t, EPI, RingShape<64, 64, 2, 2, 3>>(g, s); break;
     }
 }
