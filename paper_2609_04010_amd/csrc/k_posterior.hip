@@ -243,7 +243,9 @@ DD_DEV bool row_needs_draw(const PostArgs& a, int row, bool leader, int& zt) {
     return true;
 }
 
-template <typename T>
+// PT threads per row: 256, or 1024 on few rows, where one row per CU leaves a 256-thread workgroup
+// waiting for its own loads (the launcher has the line).
+template <typename T, int PT>
 __global__ __launch_bounds__(PT) void posterior_kernel(PostArgs a) {
     extern __shared__ float s_lse[];  // one log-sum-exp per group
 
@@ -561,6 +563,11 @@ dd_status launch_compact(const int32_t* z, int64_t M, int32_t mask_id, int32_t* 
     return launch_status("compact_masked");
 }
 
+// Rows up to which the streaming kernel takes 1024 threads per row: one row per CU.  V 50257, uniform
+// prior, us with 256 / 1024 threads: 64 rows 15.3 / 13.5 (fp32 19.1 / 14.8), 256 rows 16.7 / 15.8 (20.6 /
+// 19.0), 384 rows 19.0 / 23.1 (22.7 / 26.6); V 5000 the same to 256 rows.
+constexpr int WIDE_ROWS = 256;
+
 dd_status launch_posterior(const PostArgs& a, int logits_dtype, hipStream_t s) {
     if (a.rows == 0) return DD_OK;
     const int ngroups = (a.V + DD_GUMBEL_GROUP - 1) / DD_GUMBEL_GROUP;
@@ -572,10 +579,14 @@ dd_status launch_posterior(const PostArgs& a, int logits_dtype, hipStream_t s) {
             launch_k(posterior_grouped_kernel<bf16_t>, g4, dim3(256), 0, s, a);
         else if (a.glse)
             launch_k(posterior_grouped_kernel<float>, g4, dim3(256), 0, s, a);
+        else if (a.rows <= WIDE_ROWS && logits_dtype == DD_BF16)
+            launch_k((posterior_kernel<bf16_t, 1024>), dim3(a.rows), dim3(1024), shmem, s, a);
+        else if (a.rows <= WIDE_ROWS)
+            launch_k((posterior_kernel<float, 1024>), dim3(a.rows), dim3(1024), shmem, s, a);
         else if (logits_dtype == DD_BF16)
-            launch_k(posterior_kernel<bf16_t>, dim3(a.rows), dim3(PT), shmem, s, a);
+            launch_k((posterior_kernel<bf16_t, PT>), dim3(a.rows), dim3(PT), shmem, s, a);
         else
-            launch_k(posterior_kernel<float>, dim3(a.rows), dim3(PT), shmem, s, a);
+            launch_k((posterior_kernel<float, PT>), dim3(a.rows), dim3(PT), shmem, s, a);
     }
     if (a.probs && !a.count) {
         if (logits_dtype == DD_BF16)
