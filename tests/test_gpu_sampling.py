@@ -7,7 +7,7 @@ import workloads
 from oracle import latent as olatent, params as oparams, philox as ophilox, posterior as oposterior, \
     sampler as osampler
 from paper_2609_04010_amd import _lib as dd
-from tests.gpu_util import (PROB_TOL, compare_ids, dev_i32, dev_words, logits_dev, round_to_dtype,
+from tests.gpu_util import (GAP, PROB_TOL, compare_ids, dev_i32, dev_words, logits_dev, round_to_dtype,
                             say, torch_or_skip)
 
 pytestmark = pytest.mark.gpu
@@ -339,3 +339,29 @@ def test_degenerate_logit_rows_are_reported_and_keep_their_token(prior, dt):
         else:
             assert dirty[r] == clean[r], r
     assert ((dirty >= 0) & (dirty <= V)).all()
+
+
+@pytest.mark.parametrize("V", [1, 2, 5, 1023, 1024, 1025, 1030, 2047])
+def test_gaussian_latent_at_block_edges(V):
+    """Clean tokens in the first, the last whole and the ragged block of four classes, and in the
+    blocks on either side of a thread's first (256 blocks): the ids equal the oracle's."""
+    torch = torch_or_skip()
+    x = np.array([v for v in (0, 1, 3, 4, 5, 1019, 1020, 1023, 1024, 1027, 1028, V - 5, V - 4, V - 2, V - 1)
+                  if 0 <= v < V] * 4, dtype=np.int64)
+    for at in (0.0, 0.999):
+        sigma = float(np.sqrt(1 - at * at))
+        z = torch.empty(x.size, dtype=torch.int32, device="cuda")
+        dd.gaussian_latent_argmax(dev_i32(torch, x), x.size, V, at, sigma, seed=99, step=7, z_out=z)
+        ref = olatent.latent_argmax(x, V, at, sigma, seed=99, step=7)
+        assert np.array_equal(z.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("rows", [1, 256, 257])
+@pytest.mark.parametrize("prior,dt,V", [("mask", "bf16", 33000), ("uniform", "fp32", 17000), ("uniform", "bf16", 9)])
+def test_posterior_rows_at_the_wide_workgroup_line(rows, prior, dt, V):
+    """1024 threads per row up to 256 rows, 256 above: tiles that fill, cross and fall short of a row."""
+    torch = torch_or_skip()
+    zt, got, ref, gaps, _, _ = _run_posterior(torch, prior, V, rows, dt, "philox", 0.6, 0.4,
+                                              0.5 if prior == "mask" else 0.0, 2.0, 0.0)
+    clear = (gaps.min(axis=1) if gaps.ndim == 2 else gaps) > GAP
+    assert np.array_equal(got[clear], ref[clear])
