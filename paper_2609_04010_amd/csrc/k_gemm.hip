@@ -850,7 +850,7 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
     }
     const int sp = epi == EPI_BIAS_RESID ? ring_splits(g, max_splits) : 1;
     const double slab_us = 0.4 + (double)g.M * g.N * 4 / 2e6;
-    for (int tile = 0; tile < 3; ++tile) {
+    for (int tile : {RING_128, RING_64_DEEP, RING_64, RING_128X192}) {
         const double t = gemm_ring_us((RingTile)tile, g.M, g.N, g.K, sp, cus) + (sp - 1) * slab_us;
         if (best.tile < 0 || t < t_best) {
             best = {tile, sp};

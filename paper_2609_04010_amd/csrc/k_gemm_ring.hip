@@ -24,6 +24,11 @@
 // the matrix cores: 12 layers d 768 on 256 rows 15.3 -> 1.47 ms per forward pass against the VALU
 // kernel it replaced (with the attention of k_attn.hip), error against float64 1.2e-6 -> 0.6e-6.
 //
+// Between the two (about 1300 to 3000 rows) 128 x 192 tiles take one round of the CUs: M 2000, K 768, N
+// 2304 / 3072 15.6 / 16.6 us against 18.3 / 20.2 with 64 x 64 tiles and 20.4 / 20.9 with 256-row ones.
+// Their two sets of fragments would not leave room for the sums: they read after the barrier (with
+// two sets 17.9 / 18.9).
+//
 // Where even 32 x 32 tiles do not fill the CUs, four wavefronts share such a tile's K-tiles (each with
 // stages of its own) and their sums meet in LDS: the adapter down-projection of 1320 rows to rank 64,
 // K 3072 15.1 -> 7.7 us, K 768 6.0 -> 4.8; M 32, N 2304, K 768 6.2 -> 4.9; fp32, M 128, N 1024, K 256
@@ -67,7 +72,8 @@ DD_DEV float ring_bias(const float* b, int i) { return b[i]; }
 
 // BM x BN x one K-tile tiles over WGM x WGN wavefronts of MB x NB 32x32 MFMA blocks, NST stages; with
 // KG > 1, KG such sets of wavefronts and stages share a tile's K-tiles and their sums meet in LDS
-template <int BM_, int BN_, int WGM_, int WGN_, int NST_, int KG_ = 1> struct RingShape {
+template <int BM_, int BN_, int WGM_, int WGN_, int NST_, int KG_ = 1, bool AHEAD_ = true> struct RingShape {
+    static constexpr bool AHEAD = AHEAD_;   // fragments are read one K-tile ahead (two sets)
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NST = NST_, KG = KG_;
     static constexpr int NW = WGM * WGN, THREADS = 64 * NW * KG;   // NW: wavefronts per K group
     static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
@@ -271,46 +277,62 @@ __global__ __launch_bounds__(S::THREADS, S::WG_PER_CU * S::NW * S::KG >= 8 ? S::
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p)
         if (p < nt) load(kt0 + p, p, std::false_type{});
-    Frags f0, f1;
-    publish(min(nt - 1, NST - 2));
-    read(f0, 0);
-    int rd = 1, ld = NST - 1;   // stages of K-tile t + 1 and of K-tile t + NST - 1
-    // K-tile t from `cur`; K-tile t + 1 is read into `nxt` and K-tile t + NST - 1 loaded into the
-    // stage of K-tile t - 1, whose fragments every wavefront had waited for before this barrier.
-    // `steady`: both exist, and nothing branches, so that the compiler's waits before the MFMAs count
-    // the reads of `nxt` as still in flight.
-    auto step = [&](int t, Frags& cur, Frags& nxt, auto steady_c) {
-        constexpr bool steady = decltype(steady_c)::value;
-        if (steady || t + 1 < nt) {
-            if constexpr (steady) {
-                wait_vm<(NST - 3) * S::NL>();
-                asm volatile("s_barrier" ::: "memory");
-            } else {
-                publish(min(nt - 2 - t, NST - 3));
-            }
-            read(nxt, rd);
-            if (steady || t + NST - 1 < nt) load(kt0 + t + NST - 1, ld, steady_c);
-            rd = rd + 1 == NST ? 0 : rd + 1;
+    if constexpr (!S::AHEAD) {
+        // one set: a K-tile's fragments are read after the barrier that publishes it
+        static_assert(KG == 1, "K groups read ahead");
+        Frags f;
+        int cur = 0, ld = NST - 1;
+        for (int t = 0; t < nt; ++t) {
+            publish(min(nt - 1 - t, NST - 2));
+            if (t + NST - 1 < nt) load(kt0 + t + NST - 1, ld, std::false_type{});
+            read(f, cur);
+            if (kt0 + t == nkt - 1 && klast < KT) clear_past(f);
+            mfmas(f);
+            cur = cur + 1 == NST ? 0 : cur + 1;
             ld = ld + 1 == NST ? 0 : ld + 1;
+        }
+    } else {
+        Frags f0, f1;
+        publish(min(nt - 1, NST - 2));
+        read(f0, 0);
+        int rd = 1, ld = NST - 1;   // stages of K-tile t + 1 and of K-tile t + NST - 1
+        // K-tile t from `cur`; K-tile t + 1 is read into `nxt` and K-tile t + NST - 1 loaded into the
+        // stage of K-tile t - 1, whose fragments every wavefront had waited for before this barrier.
+        // `steady`: both exist, and nothing branches, so that the compiler's waits before the MFMAs count
+        // the reads of `nxt` as still in flight.
+        auto step = [&](int t, Frags& cur, Frags& nxt, auto steady_c) {
+            constexpr bool steady = decltype(steady_c)::value;
+            if (steady || t + 1 < nt) {
+                if constexpr (steady) {
+                    wait_vm<(NST - 3) * S::NL>();
+                    asm volatile("s_barrier" ::: "memory");
+                } else {
+                    publish(min(nt - 2 - t, NST - 3));
+                }
+                read(nxt, rd);
+                if (steady || t + NST - 1 < nt) load(kt0 + t + NST - 1, ld, steady_c);
+                rd = rd + 1 == NST ? 0 : rd + 1;
+                ld = ld + 1 == NST ? 0 : ld + 1;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (!steady) {
+                if (kt0 + t == nkt - 1 && klast < KT) clear_past(cur);
+                if (KG > 1 && t >= mine) return;
+            }
+            mfmas(cur);
             __builtin_amdgcn_sched_barrier(0);
+        };
+        int t = 0;
+        // (the last K-tile, which may be ragged, is loaded below; all groups leave this loop together)
+        const int nsteady = KG == 1 ? nt : ks1 - ks0 - (KG - 1) * nt;
+        for (; t + NST + 1 < nsteady; t += 2) {
+            step(t, f0, f1, std::true_type{});
+            step(t + 1, f1, f0, std::true_type{});
         }
-        if constexpr (!steady) {
-            if (kt0 + t == nkt - 1 && klast < KT) clear_past(cur);
-            if (KG > 1 && t >= mine) return;
+        for (; t < nt; t += 2) {
+            step(t, f0, f1, std::false_type{});
+            if (t + 1 < nt) step(t + 1, f1, f0, std::false_type{});
         }
-        mfmas(cur);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    int t = 0;
-    // (the last K-tile, which may be ragged, is loaded below; all groups leave this loop together)
-    const int nsteady = KG == 1 ? nt : ks1 - ks0 - (KG - 1) * nt;
-    for (; t + NST + 1 < nsteady; t += 2) {
-        step(t, f0, f1, std::true_type{});
-        step(t + 1, f1, f0, std::true_type{});
-    }
-    for (; t < nt; t += 2) {
-        step(t, f0, f1, std::false_type{});
-        if (t + 1 < nt) step(t + 1, f1, f0, std::false_type{});
     }
     __syncthreads();   // the stages become the epilogue's staging area
     smem = ring_smem;
@@ -469,6 +491,7 @@ static void launch_epi(int dtype, RingTile tile, const GemmArgs& g, hipStream_t 
         case RING_128: launch_shape<bf16_t, EPI, RingShape<128, 128, 4, 2, 4>>(g, s); break;
         case RING_64_DEEP: launch_shape<bf16_t, EPI, RingShape<64, 64, 2, 2, 4>>(g, s); break;
         case RING_32K: launch_shape<bf16_t, EPI, RingShape<32, 32, 1, 1, 4, 4>>(g, s); break;
+        case RING_128X192: launch_shape<bf16_t, EPI, RingShape<128, 192, 4, 2, 3, 1, false>>(g, s); break;
         default: launch_shape<bf16_t, EPI, RingShape<64, 64, 2, 2, 3>>(g, s); break;
     }
 }
@@ -488,17 +511,20 @@ void launch_gemm_ring(int dtype, RingTile tile, int epi, const GemmArgs& g, hipS
 // co-residents leave it.  Fitted to 17 products (N 64..4096, K 256..4096) at 16 row counts from 64 to
 // 16384, 1 to 4 splits, the weights rotating as the layers of a model do: 9 to 13 % rms.
 double gemm_ring_us(RingTile tile, int64_t M, int64_t N, int64_t K, int splits, int cus) {
-    const int b = tile == RING_128 ? 128 : 64;
-    const int P = tile == RING_128 ? 1 : tile == RING_64_DEEP ? 2 : 3;
-    const double t0 = tile == RING_128 ? 0.0 : tile == RING_64_DEEP ? 1.3 : 0.5;
-    const double tw = tile == RING_128 ? 6.3 : tile == RING_64_DEEP ? 2.9 : 3.3;
-    const double lat = tile == RING_128 ? 0.49 : tile == RING_64_DEEP ? 0.21 : 0.41;
-    const double share = tile == RING_128 ? 0.49 : tile == RING_64_DEEP ? 0.214 : 0.241;
-    const int64_t wg = ((M + b - 1) / b) * ((N + b - 1) / b) * splits;
+    struct Fit {
+        int bm, bn, P;
+        double t0, tw, lat, share;
+    };
+    static const Fit fits[] = {{128, 128, 1, 0.0, 6.3, 0.49, 0.49},
+                               {64, 64, 2, 1.3, 2.9, 0.21, 0.214},
+                               {64, 64, 3, 0.5, 3.3, 0.41, 0.241},
+                               {128, 192, 1, 1.8, 2.2, 1.0, 1.0}};
+    const Fit& f = fits[tile == RING_128 ? 0 : tile == RING_64_DEEP ? 1 : tile == RING_64 ? 2 : 3];
+    const int64_t wg = ((M + f.bm - 1) / f.bm) * ((N + f.bn - 1) / f.bn) * splits;
     const int64_t kt = ((K + BK - 1) / BK + splits - 1) / splits;
-    const int64_t full = wg / ((int64_t)cus * P), rest = wg - full * cus * P;
-    double t = t0 + (double)full * (tw + (double)kt * std::max(lat, P * share));
-    if (rest > 0) t += tw + (double)kt * std::max(lat, (double)((rest + cus - 1) / cus) * share);
+    const int64_t full = wg / ((int64_t)cus * f.P), rest = wg - full * cus * f.P;
+    double t = f.t0 + (double)full * (f.tw + (double)kt * std::max(f.lat, f.P * f.share));
+    if (rest > 0) t += f.tw + (double)kt * std::max(f.lat, (double)((rest + cus - 1) / cus) * f.share);
     return t;
 }
 
