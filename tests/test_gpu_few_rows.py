@@ -32,10 +32,15 @@ CASES = [
     (dict(n_layers=1, vocab=300, d_mlp=120), 5, 500),
     (dict(n_layers=2, vocab=300, lora_rank=8, lora_alpha=16.0), 1, 90),
     (dict(n_layers=1, vocab=300, lora_rank=72, lora_alpha=144.0), 3, 250),
-    # other widths (normalisation by the row-per-wavefront kernels), K of one to eight K-tiles
+    # other widths, K of one to eight K-tiles
     (dict(n_layers=2, vocab=300, d_model=64, n_heads=1, d_mlp=256), 2, 40),
     (dict(n_layers=2, vocab=300, d_model=256, n_heads=4, d_mlp=256), 2, 100),
     (dict(n_layers=2, vocab=300, d_model=512, n_heads=8, d_mlp=2048, norm="rms"), 2, 150),
+    # the widths the four-features-per-lane normalisation takes besides 768 and 1024
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4, d_mlp=256, norm="rms"), 1, 33),
+    (dict(n_layers=1, vocab=300, d_model=1536, n_heads=24, d_mlp=256), 2, 70),
+    # 128 x 192 tiles with ragged rows, columns and K
+    (dict(n_layers=1, vocab=300, lora_rank=8, lora_alpha=16.0), 7, 241),
 ]
 
 
