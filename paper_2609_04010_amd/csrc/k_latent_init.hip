@@ -13,6 +13,10 @@ namespace dd {
 // Bound by the VALU work of the Philox blocks (one per four classes).  16384 rows x 50257 classes:
 // 486 us with a compare and two selects per class, 370 with one per block, 297 with the three-input
 // exclusive or in the Philox rounds as well.
+// FEW: up to FEW_BLOCKS blocks per row, all of them class by class (V 1030, 16000 rows: 47.2 us, 49.1 by
+// largest words).
+constexpr int FEW_BLOCKS = 1024;
+template <bool FEW>
 __global__ __launch_bounds__(256) void latent_kernel(const int32_t* x, int32_t V, double at,
                                                      double sigma, uint64_t seed, uint32_t step,
                                                      uint32_t row0, int32_t* z, int32_t* err) {
@@ -31,7 +35,8 @@ __global__ __launch_bounds__(256) void latent_kernel(const int32_t* x, int32_t V
     const int nblk = (V + 3) >> 2, nfull = V >> 2, xb = xr >> 2;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     auto block = [&](int b) { return philox4x32_10((uint32_t)b, grow, step, STREAM_LATENT, k0, k1); };
-    // class by class: the first block of each thread, and the blocks with classes to leave out
+    // class by class: every block (FEW), else the first block of each thread and the blocks with classes
+    // to leave out
     auto careful = [&](int b) {
         const Words4 W = block(b);
 #pragma unroll
@@ -44,24 +49,28 @@ __global__ __launch_bounds__(256) void latent_kernel(const int32_t* x, int32_t V
         }
         if (b == xb) sh_wx = W.w[xr & 3];
     };
-    if (tid < nblk) careful(tid);
-    // The other whole blocks by their largest word alone; only a larger word takes the place of an
-    // earlier block's.  Its class comes from drawing that one block again.
-    int bb = -1;
-    for (int b = tid + 256; b < nfull; b += 256) {
-        const Words4 W = block(b);
-        const uint32_t m = max(max(W.w[0], W.w[1]), max(W.w[2], W.w[3]));
-        const bool take = m > bw && b != xb;
-        bw = take ? m : bw;
-        bb = take ? b : bb;
-    }
-    if (bb >= 0) {
-        const Words4 W = block(bb);
+    if constexpr (FEW) {
+        for (int b = tid; b < nblk; b += 256) careful(b);
+    } else {
+        careful(tid);
+        // The other whole blocks by their largest word alone; only a larger word takes the place of an
+        // earlier block's.  Its class comes from drawing that one block again.
+        int bb = -1;
+        for (int b = tid + 256; b < nfull; b += 256) {
+            const Words4 W = block(b);
+            const uint32_t m = max(max(W.w[0], W.w[1]), max(W.w[2], W.w[3]));
+            const bool take = m > bw && b != xb;
+            bw = take ? m : bw;
+            bb = take ? b : bb;
+        }
+        if (bb >= 0) {
+            const Words4 W = block(bb);
 #pragma unroll
-        for (int e = 3; e >= 0; --e) bi = W.w[e] == bw ? 4 * bb + e : bi;   // the lowest of equal words
+            for (int e = 3; e >= 0; --e) bi = W.w[e] == bw ? 4 * bb + e : bi;   // the lowest of equal words
+        }
+        if (xb >= 256 && xb < nfull && (xb & 255) == tid) careful(xb);
+        if (nblk > nfull && (nfull & 255) == tid) careful(nfull);
     }
-    if (xb >= 256 && xb < nfull && (xb & 255) == tid) careful(xb);
-    if (nfull >= 256 && nblk > nfull && (nfull & 255) == tid) careful(nfull);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const uint32_t w2 = __shfl_xor(bw, o, 64);
@@ -88,8 +97,8 @@ dd_status launch_latent(const int32_t* x, int32_t rows, int32_t V, double at, do
                         hipStream_t s) {
     if (rows == 0) return DD_OK;
     ProfScope ps(KC_LATENT, s);
-    launch_k(latent_kernel, dim3(rows), dim3(256), 0, s, x, V, at, sigma, seed, step, row0,
-                       z, err);
+    if ((V + 3) / 4 <= FEW_BLOCKS) launch_k(latent_kernel<true>, dim3(rows), dim3(256), 0, s, x, V, at, sigma, seed, step, row0, z, err);
+    else launch_k(latent_kernel<false>, dim3(rows), dim3(256), 0, s, x, V, at, sigma, seed, step, row0, z, err);
     return launch_status("gaussian_latent_argmax");
 }
 

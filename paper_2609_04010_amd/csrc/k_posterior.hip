@@ -565,8 +565,9 @@ dd_status launch_compact(const int32_t* z, int64_t M, int32_t mask_id, int32_t* 
 
 // Rows up to which the streaming kernel takes 1024 threads per row: one row per CU.  V 50257, uniform
 // prior, us with 256 / 1024 threads: 64 rows 15.3 / 13.5 (fp32 19.1 / 14.8), 256 rows 16.7 / 15.8 (20.6 /
-// 19.0), 384 rows 19.0 / 23.1 (22.7 / 26.6); V 5000 the same to 256 rows.
-constexpr int WIDE_ROWS = 256;
+// 19.0), 384 rows 19.0 / 23.1 (22.7 / 26.6); rows of up to two of the
+// 256-thread form's tiles (2048 chunks of 16 bytes) gain nothing (V 4000: 10.5 / 11.4).
+constexpr int WIDE_ROWS = 256, WIDE_CHUNKS = 2 * TILE_IT * PT;
 
 dd_status launch_posterior(const PostArgs& a, int logits_dtype, hipStream_t s) {
     if (a.rows == 0) return DD_OK;
@@ -575,13 +576,14 @@ dd_status launch_posterior(const PostArgs& a, int logits_dtype, hipStream_t s) {
     {
         ProfScope ps(KC_POSTERIOR, s);
         const dim3 g4((unsigned)((a.rows + 3) / 4));
+        const bool wide = a.rows <= WIDE_ROWS && a.V > WIDE_CHUNKS * (logits_dtype == DD_BF16 ? 8 : 4);
         if (a.glse && logits_dtype == DD_BF16)
             launch_k(posterior_grouped_kernel<bf16_t>, g4, dim3(256), 0, s, a);
         else if (a.glse)
             launch_k(posterior_grouped_kernel<float>, g4, dim3(256), 0, s, a);
-        else if (a.rows <= WIDE_ROWS && logits_dtype == DD_BF16)
+        else if (wide && logits_dtype == DD_BF16)
             launch_k((posterior_kernel<bf16_t, 1024>), dim3(a.rows), dim3(1024), shmem, s, a);
-        else if (a.rows <= WIDE_ROWS)
+        else if (wide)
             launch_k((posterior_kernel<float, 1024>), dim3(a.rows), dim3(1024), shmem, s, a);
         else if (logits_dtype == DD_BF16)
             launch_k((posterior_kernel<bf16_t, PT>), dim3(a.rows), dim3(PT), shmem, s, a);

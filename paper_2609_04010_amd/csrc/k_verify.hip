@@ -34,8 +34,10 @@ namespace dd {
 
 namespace {
 
-constexpr int VT = 512;    // threads per workgroup of kernel 1
-constexpr int VT2 = 1024;  // and of kernel 2
+// Threads per workgroup of kernel 1 and of kernel 2; 256 in both on short rows (SHORT_CHUNKS chunks of
+// 16 bytes), where more only idle: S 250, B 3, V 5000 15.8 against 20.5 us, S 200, B 16, V 2000 27.6
+// against 30.6; S 3, B 16, V 20000 20.9 against 16.1 the other way.
+constexpr int VT_LONG = 512, VT2_LONG = 1024, VT_SHORT = 256, SHORT_CHUNKS = 2048;
 
 DD_DEV uint32_t verify_word(const VerifyArgs& a, int s, uint32_t stream, int idx, int explicit_off) {
     if (a.noise) return a.noise[(int64_t)s * a.nu + explicit_off + idx];
@@ -66,9 +68,8 @@ DD_DEV bool rejected(const VerifyArgs& a, int s, int i, float lse_p, float lse_q
 // so such rows are told apart afterwards by a second scan that only they take.  Bound by HBM; S 256,
 // B 16, V 50257 with 4.8 positions kept on average: 131 us over every row, 81 us with the hint (two
 // chunks per row in flight; with four the kernel needs 148 registers, one workgroup per CU, 115 us).
-constexpr int VU = 2;
-template <typename T>
-__global__ __launch_bounds__(VT, VT / 128) void row_lse_kernel(VerifyArgs a, float* lse, int hint) {
+template <typename T, int VT, int VU>
+__global__ __launch_bounds__(VT, 4) void row_lse_kernel(VerifyArgs a, float* lse, int hint) {
     __shared__ float sh_m[2][VT / 64], sh_s[2][VT / 64];
     __shared__ int sh_f[VT / 64], sh_skip;
     constexpr int E = Elem<T>::E, NW = VT / 64;
@@ -154,12 +155,14 @@ __global__ __launch_bounds__(VT, VT / 128) void row_lse_kernel(VerifyArgs a, flo
     float M[2], Mref[2], S[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
+        if (r == 1 && !pair) break;
         M[r] = wave_max(m[r]);
         if (lane == 0) sh_m[r][wave] = M[r];
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
+        if (r == 1 && !pair) break;
         M[r] = sh_m[r][0];
 #pragma unroll
         for (int w = 1; w < NW; ++w) M[r] = fmaxf(M[r], sh_m[r][w]);
@@ -219,7 +222,7 @@ __global__ void verify_start_kernel(int32_t* n_out, int S, int B) {
 // in flight: 1024 threads, VU chunks of both rows each.  The tests of the drafted positions run one
 // per lane, and the draw takes one Philox block per four words (S 4, B 16, V 50257: 32.7 us with 256
 // threads, one chunk each, the tests one after the other by one thread and a block per word).
-template <typename T>
+template <typename T, int VT2, int VU>
 __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* lse) {
     extern __shared__ float s_mass[];   // one mass per group
     __shared__ int sh_n;
@@ -269,8 +272,7 @@ __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* 
     const int nchunk = (V + E - 1) / E;
     auto masses = [&](bool use_p) -> float {
         float tot = 0.f;
-        for (int c0 = 0; c0 < nchunk; c0 += 4 * VT2) {
-            constexpr int VU = 4;
+        for (int c0 = 0; c0 < nchunk; c0 += VU * VT2) {
             uint4 xp[VU], xq[VU];
 #pragma unroll
             for (int u = 0; u < VU; ++u) {
@@ -422,18 +424,28 @@ dd_status launch_verify(const VerifyArgs& a, int logits_dtype, float* lse, hipSt
     if (a.S == 0) return DD_OK;
     const int ngroups = (a.V + DD_GUMBEL_GROUP - 1) / DD_GUMBEL_GROUP;
     const size_t shmem = (size_t)ngroups * sizeof(float);
-    // Up to about 1024 positions everything starts at once and the hint never comes in time: its
-    // launch is left out, and a workgroup takes one row instead of two (S 4, B 16: 7 against 10 us).
-    const int hint = a.B > 2 && (int64_t)a.S * a.B > 1024;
+    // Up to about 1024 positions everything starts at once and the hint never comes in time (and a
+    // short row is no loss): its launch is left out, and a workgroup takes one row instead of two (S 4,
+    // B 16: 7 against 10 us).
+    const int chunk = logits_dtype == DD_BF16 ? 8 : 4;
+    const bool is_short = a.V <= SHORT_CHUNKS * chunk;
+    const int hint = !is_short && a.B > 2 && (int64_t)a.S * a.B > 1024;
     if (hint) launch_k(verify_start_kernel, dim3((a.S + 255) / 256), dim3(256), 0, s, a.n_out, a.S, a.B);
     const dim3 grid((unsigned)(hint ? a.S * a.B : a.S * (2 * a.B - 1)));
-    if (logits_dtype == DD_BF16) {
-        launch_k(row_lse_kernel<bf16_t>, grid, dim3(VT), 0, s, a, lse, hint);
-        launch_k(verify_kernel<bf16_t>, dim3(a.S), dim3(VT2), shmem, s, a, (const float*)lse);
-    } else {
-        launch_k(row_lse_kernel<float>, grid, dim3(VT), 0, s, a, lse, hint);
-        launch_k(verify_kernel<float>, dim3(a.S), dim3(VT2), shmem, s, a, (const float*)lse);
-    }
+    auto run = [&](auto lse_k, auto draw_k, int vt, int vt2) {
+        launch_k(lse_k, grid, dim3(vt), 0, s, a, lse, hint);
+        launch_k(draw_k, dim3(a.S), dim3(vt2), shmem, s, a, (const float*)lse);
+    };
+    // chunks in flight per thread and row: two where 256 threads cover the row with that
+    const bool two = a.V <= 2 * VT_SHORT * chunk;
+    auto pick = [&](auto t) {
+        using T = decltype(t);
+        if (two) run(row_lse_kernel<T, VT_SHORT, 2>, verify_kernel<T, VT_SHORT, 2>, VT_SHORT, VT_SHORT);
+        else if (is_short) run(row_lse_kernel<T, VT_SHORT, 4>, verify_kernel<T, VT_SHORT, 4>, VT_SHORT, VT_SHORT);
+        else run(row_lse_kernel<T, VT_LONG, 2>, verify_kernel<T, VT2_LONG, 4>, VT_LONG, VT2_LONG);
+    };
+    if (logits_dtype == DD_BF16) pick(bf16_t{});
+    else pick(float{});
     return launch_status("spec_verify");
 }
 
