@@ -79,8 +79,7 @@ DD_DEV float round_bf16(float x) {
 // results are never stored).
 constexpr int DM = 256;                       // tile rows (M) of the wide tiles
 // DM_ x TBN_ tiles over WGM x WGN wavefronts, each owning a WM x WN sub-tile of MB x NB 32x32 MFMA
-// blocks.  The 64-row form (64 x 128, four wavefronts side by side) serves skinny products: every
-// CU streams one 64-row strip of A while all of them share the small W through L2.
+// blocks.
 template <int TBN_, int WGM_, int WGN_, int DM_ = DM> struct DLShape {
     static constexpr int DM = DM_;                            // tile rows (M)
     static constexpr int TBN = TBN_;                          // tile columns (N)
@@ -95,9 +94,6 @@ template <int TBN_, int WGM_, int WGN_, int DM_ = DM> struct DLShape {
     // two operand stages; the epilogue stages half a sub-tile per wave above stage 0
     static constexpr size_t STAGING = (size_t)STAGE * 2 + (size_t)NW * (WM / 2) * CSTR * 2;
     static constexpr size_t LDS = STAGING > (size_t)2 * STAGE * 2 ? STAGING : (size_t)2 * STAGE * 2;
-    // workgroups per CU the launcher allows: one for the wide tiles (persistent), several for the
-    // one-wavefront skinny tile, whose K loop is latency-bound
-    static constexpr int WG_PER_CU = NW >= 4 ? 1 : 8 / NW;
     static_assert(WM % 64 == 0 && WN % 32 == 0 && (MB * NB) % 2 == 0, "wave sub-tile (two row halves)");
     static_assert(DM % (8 * NW) == 0 && TBN % (8 * NW) == 0, "load split");
     static_assert(LDS <= 160 * 1024, "LDS");
@@ -876,8 +872,8 @@ static void launch_dl(const GemmArgs& g, hipStream_t s) {
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         attr = true;
     }
-    // persistent: at most WG_PER_CU workgroups per CU
-    const int grid = (int)std::min<int64_t>((int64_t)tm * tn, (int64_t)num_cus() * S::WG_PER_CU);
+    // persistent: at most one workgroup per CU
+    const int grid = (int)std::min<int64_t>((int64_t)tm * tn, (int64_t)num_cus());
     launch_k((gemm_bf16_dl_kernel<EPI, ROLE, TBN, WGM, WGN, DMR>), dim3(grid), dim3(S::THREADS), lds,
                        s, g, tm, tn);
 }
