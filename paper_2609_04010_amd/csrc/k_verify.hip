@@ -34,10 +34,7 @@ namespace dd {
 
 namespace {
 
-// Threads per workgroup of kernel 1 and of kernel 2; 256 in both on short rows (SHORT_CHUNKS chunks of
-// 16 bytes), where more only idle: S 250, B 3, V 5000 15.8 against 20.5 us, S 200, B 16, V 2000 27.6
-// against 30.6; S 3, B 16, V 20000 20.9 against 16.1 the other way.
-constexpr int VT_LONG = 512, VT2_LONG = 1024, VT_SHORT = 256, SHORT_CHUNKS = 2048;
+constexpr int SHORT_CHUNKS = 2048;   // 16-byte chunks of a short row
 
 DD_DEV uint32_t verify_word(const VerifyArgs& a, int s, uint32_t stream, int idx, int explicit_off) {
     if (a.noise) return a.noise[(int64_t)s * a.nu + explicit_off + idx];
@@ -68,28 +65,39 @@ DD_DEV bool rejected(const VerifyArgs& a, int s, int i, float lse_p, float lse_q
 // so such rows are told apart afterwards by a second scan that only they take.  Bound by HBM; S 256,
 // B 16, V 50257 with 4.8 positions kept on average: 131 us over every row, 81 us with the hint (two
 // chunks per row in flight; with four the kernel needs 148 registers, one workgroup per CU, 115 us).
-template <typename T, int VT, int VU>
-__global__ __launch_bounds__(VT, 4) void row_lse_kernel(VerifyArgs a, float* lse, int hint) {
-    __shared__ float sh_m[2][VT / 64], sh_s[2][VT / 64];
-    __shared__ int sh_f[VT / 64], sh_skip;
-    constexpr int E = Elem<T>::E, NW = VT / 64;
+// HINT is a template parameter because the pair's registers (bf16: 128 instead of 80 at four chunks) cost
+// the one-row form its occupancy: S 256, B 16, V 5000 24.3 -> 17.8 us without them.
+template <typename T, int VT, int VU, bool HINT>
+__global__ __launch_bounds__(VT, HINT ? 4 : 1) void row_lse_kernel(VerifyArgs a, float* lse) {
+    constexpr int E = Elem<T>::E, NW = VT / 64, NR = HINT ? 2 : 1;   // NR: rows of a workgroup
+    __shared__ float sh_m[NR][NW], sh_s[NR][NW];
+    __shared__ int sh_f[NW], sh_skip;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // with the hint a workgroup takes a position, position by position; without it one row (target
     // rows first)
     const int np = a.S * a.B, r0 = (int)blockIdx.x;
-    const int i = hint ? r0 / a.S : 0, s = hint ? r0 - i * a.S : 0;
+    const int i = HINT ? r0 / a.S : 0, s = HINT ? r0 - i * a.S : 0;
     const int V = a.V, nchunk = (V + E - 1) / E;
-    if (hint) {
+    if constexpr (HINT) {
         if (tid == 0) sh_skip = __hip_atomic_load(a.n_out + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= i;
         __syncthreads();
         if (sh_skip) return;
     }
-    const bool pair = hint && i < a.B - 1;
-    const char* rows[2] = {hint ? (const char*)a.p + ((size_t)s * a.B + i) * a.ld * sizeof(T)
-                           : r0 < np ? (const char*)a.p + (size_t)r0 * a.ld * sizeof(T)
-                                     : (const char*)a.q + (size_t)(r0 - np) * a.ld * sizeof(T),
-                           pair ? (const char*)a.q + ((size_t)s * (a.B - 1) + i) * a.ld * sizeof(T) : nullptr};
-    float m[2] = {-INFINITY, -INFINITY}, sum[2] = {0.f, 0.f};
+    const bool pair = HINT && i < a.B - 1;
+    const char* rows[NR];
+    if constexpr (HINT) {
+        rows[0] = (const char*)a.p + ((size_t)s * a.B + i) * a.ld * sizeof(T);
+        rows[1] = pair ? (const char*)a.q + ((size_t)s * (a.B - 1) + i) * a.ld * sizeof(T) : nullptr;
+    } else {
+        rows[0] = r0 < np ? (const char*)a.p + (size_t)r0 * a.ld * sizeof(T)
+                          : (const char*)a.q + (size_t)(r0 - np) * a.ld * sizeof(T);
+    }
+    float m[NR], sum[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        m[r] = -INFINITY;
+        sum[r] = 0.f;
+    }
     constexpr int TS = VU * VT;   // chunks per tile
     // chunks c0 + u VT + tid, u < VU; chunks past the row read as -inf, and so does the part of the
     // last chunk past V
@@ -149,19 +157,23 @@ __global__ __launch_bounds__(VT, 4) void row_lse_kernel(VerifyArgs a, float* lse
             for (int r = 0; r < R; ++r) absorb(xb[r], m[r], sum[r]);
         }
     };
-    if (pair) scan(std::true_type{});
-    else scan(std::false_type{});
+    if constexpr (HINT) {
+        if (pair) scan(std::true_type{});
+        else scan(std::false_type{});
+    } else {
+        scan(std::false_type{});
+    }
     // workgroup: maximum, then the sums rescaled to it
-    float M[2], Mref[2], S[2];
+    float M[NR], Mref[NR], S[NR];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NR; ++r) {
         if (r == 1 && !pair) break;
         M[r] = wave_max(m[r]);
         if (lane == 0) sh_m[r][wave] = M[r];
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NR; ++r) {
         if (r == 1 && !pair) break;
         M[r] = sh_m[r][0];
 #pragma unroll
@@ -172,9 +184,9 @@ __global__ __launch_bounds__(VT, 4) void row_lse_kernel(VerifyArgs a, float* lse
         if (lane == 0) sh_s[r][wave] = part;
     }
     __syncthreads();
-    float out[2] = {0.f, 0.f};
+    float out[NR] = {};
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NR; ++r) {
         if (r == 1 && !pair) break;
         S[r] = sh_s[r][0];
 #pragma unroll
@@ -204,10 +216,12 @@ __global__ __launch_bounds__(VT, 4) void row_lse_kernel(VerifyArgs a, float* lse
         }
     }
     if (tid == 0) {
-        lse[hint ? (size_t)s * a.B + i : (size_t)r0] = out[0];
-        if (pair) {
-            lse[np + (size_t)s * (a.B - 1) + i] = out[1];
-            if (rejected<T>(a, s, i, out[0], out[1])) atomicMin(a.n_out + s, i + 1);
+        lse[HINT ? (size_t)s * a.B + i : (size_t)r0] = out[0];
+        if constexpr (HINT) {
+            if (pair) {
+                lse[np + (size_t)s * (a.B - 1) + i] = out[1];
+                if (rejected<T>(a, s, i, out[0], out[1])) atomicMin(a.n_out + s, i + 1);
+            }
         }
     }
 }
@@ -219,9 +233,11 @@ __global__ void verify_start_kernel(int32_t* n_out, int S, int B) {
 }
 
 // The pass over the row pair is one CU's work per sequence, so what bounds it is how much that CU has
-// in flight: 1024 threads, VU chunks of both rows each.  The tests of the drafted positions run one
-// per lane, and the draw takes one Philox block per four words (S 4, B 16, V 50257: 32.7 us with 256
-// threads, one chunk each, the tests one after the other by one thread and a block per word).
+// in flight: VT2 threads (the launcher has the lines), VU chunks of both rows each.  The tests of the
+// drafted positions run one per lane, and the draw takes one Philox block per four words, or where 64
+// lanes cover the candidates one each, since four scores one after the other cost more than the
+// blocks (V 64 7.5 -> 5.2 us).  S 4, B 16, V 50257: 32.7 -> 14.5 us against 256 threads, one chunk each,
+// the tests by one thread and a block per word.
 template <typename T, int VT2, int VU>
 __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* lse) {
     extern __shared__ float s_mass[];   // one mass per group
@@ -276,6 +292,7 @@ __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* 
             uint4 xp[VU], xq[VU];
 #pragma unroll
             for (int u = 0; u < VU; ++u) {
+                if (c0 + u * VT2 >= nchunk) break;   // the same for the whole workgroup
                 const int c = min(c0 + u * VT2 + tid, nchunk - 1);
                 xp[u] = *(const uint4*)(pr + (size_t)c * 16);
                 if (resid && !use_p) xq[u] = *(const uint4*)(qr + (size_t)c * 16);
@@ -283,6 +300,7 @@ __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* 
             }
 #pragma unroll
             for (int u = 0; u < VU; ++u) {
+                if (c0 + u * VT2 >= nchunk) break;
                 const int c = c0 + u * VT2 + tid;
                 float sum = 0.f;
                 if (c < nchunk) {
@@ -313,7 +331,8 @@ __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* 
         masses(true);
     }
 
-    // ---- two-level draw (one wavefront): four consecutive words per lane and Philox block ----
+    // ---- two-level draw (one wavefront): one candidate per lane up to 64, beyond that four
+    // consecutive words per lane and Philox block ----
     if (tid >= 64) return;
     const int ntop = ngroups;
     auto words = [&](uint32_t stream, int base, int count, int explicit_off, uint32_t (&wd)[4]) {
@@ -339,18 +358,23 @@ __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* 
         }
         return bi;
     };
+    // score of class (or group) j with mass `mass` and word w against the best so far
     float best = -INFINITY;
     int bi = 0x7FFFFFFF;
-    for (int g0 = 4 * lane; g0 < ngroups; g0 += 256) {
-        uint32_t wd[4];
-        words(STREAM_TOP, g0, ngroups, B - 1, wd);
+    auto consider = [&](int j, float mass, uint32_t w, bool in) {
+        const float sc = logf(mass) + word_gumbel_f(w);
+        const bool take = in && (sc > best || (sc == best && j < bi));
+        best = take ? sc : best;
+        bi = take ? j : bi;
+    };
+    if (ngroups <= 64) {
+        if (lane < ngroups) consider(lane, s_mass[lane], verify_word(a, s, STREAM_TOP, lane, B - 1), true);
+    } else {
+        for (int g0 = 4 * lane; g0 < ngroups; g0 += 256) {
+            uint32_t wd[4];
+            words(STREAM_TOP, g0, ngroups, B - 1, wd);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (g0 + k >= ngroups) continue;
-            const float sc = logf(s_mass[g0 + k]) + word_gumbel_f(wd[k]);
-            const bool take = sc > best || (sc == best && g0 + k < bi);
-            best = take ? sc : best;
-            bi = take ? g0 + k : bi;
+            for (int k = 0; k < 4; ++k) consider(g0 + k, s_mass[min(g0 + k, ngroups - 1)], wd[k], g0 + k < ngroups);
         }
     }
     const int gstar = argmax(best, bi);
@@ -358,20 +382,28 @@ __global__ __launch_bounds__(VT2) void verify_kernel(VerifyArgs a, const float* 
     const bool bad = gstar >= ngroups || !isfinite(lp0) || (resid && !use_p && !isfinite(lq0));
     best = -INFINITY;
     bi = 0x7FFFFFFF;
-    const int j0 = bad ? V : gstar * DD_GUMBEL_GROUP + 4 * lane;
-    if (j0 < V) {
-        uint32_t wd[4];
-        words(STREAM_CLASS, j0, V, B - 1 + ntop, wd);
+    if (!bad) {
+        const int base = gstar * DD_GUMBEL_GROUP, n2 = min(V - base, DD_GUMBEL_GROUP);
+        const bool with_q = resid && !use_p;
+        if (n2 <= 64) {
+            const int j = base + lane;
+            if (lane < n2)
+                consider(j, cls_mass(Elem<T>::load1(pr, j), with_q ? Elem<T>::load1(qr, j) : 0.f, use_p),
+                         verify_word(a, s, STREAM_CLASS, j, B - 1 + ntop), true);
+        } else if (4 * lane < n2) {
+            const int j0 = base + 4 * lane;
+            // the four classes' loads go out together (those past V read the last class and are not taken)
+            float lpv[4], lqv[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int j = j0 + k;
-            if (j >= V) continue;
-            const float lpv = Elem<T>::load1(pr, j);
-            const float lqv = (resid && !use_p) ? Elem<T>::load1(qr, j) : 0.f;
-            const float sc = logf(cls_mass(lpv, lqv, use_p)) + word_gumbel_f(wd[k]);
-            const bool take = sc > best || (sc == best && j < bi);
-            best = take ? sc : best;
-            bi = take ? j : bi;
+            for (int k = 0; k < 4; ++k) {
+                const int j = min(j0 + k, V - 1);
+                lpv[k] = Elem<T>::load1(pr, j);
+                lqv[k] = with_q ? Elem<T>::load1(qr, j) : 0.f;
+            }
+            uint32_t wd[4];
+            words(STREAM_CLASS, j0, V, B - 1 + ntop, wd);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) consider(j0 + k, cls_mass(lpv[k], lqv[k], use_p), wd[k], j0 + k < V);
         }
     }
     bi = argmax(best, bi);
@@ -424,25 +456,33 @@ dd_status launch_verify(const VerifyArgs& a, int logits_dtype, float* lse, hipSt
     if (a.S == 0) return DD_OK;
     const int ngroups = (a.V + DD_GUMBEL_GROUP - 1) / DD_GUMBEL_GROUP;
     const size_t shmem = (size_t)ngroups * sizeof(float);
+    const int chunk = logits_dtype == DD_BF16 ? 8 : 4, nchunk = (a.V + chunk - 1) / chunk;
     // Up to about 1024 positions everything starts at once and the hint never comes in time (and a
     // short row is no loss): its launch is left out, and a workgroup takes one row instead of two (S 4,
     // B 16: 7 against 10 us).
-    const int chunk = logits_dtype == DD_BF16 ? 8 : 4;
-    const bool is_short = a.V <= SHORT_CHUNKS * chunk;
-    const int hint = !is_short && a.B > 2 && (int64_t)a.S * a.B > 1024;
+    const bool is_short = nchunk <= SHORT_CHUNKS;
+    const bool hint = !is_short && a.B > 2 && (int64_t)a.S * a.B > 1024;
     if (hint) launch_k(verify_start_kernel, dim3((a.S + 255) / 256), dim3(256), 0, s, a.n_out, a.S, a.B);
-    const dim3 grid((unsigned)(hint ? a.S * a.B : a.S * (2 * a.B - 1)));
-    auto run = [&](auto lse_k, auto draw_k, int vt, int vt2) {
-        launch_k(lse_k, grid, dim3(vt), 0, s, a, lse, hint);
-        launch_k(draw_k, dim3(a.S), dim3(vt2), shmem, s, a, (const float*)lse);
-    };
-    // chunks in flight per thread and row: two where 256 threads cover the row with that
-    const bool two = a.V <= 2 * VT_SHORT * chunk;
+    const int rows = a.S * (hint ? a.B : 2 * a.B - 1);
+    auto lse_run = [&](auto kernel, int vt) { launch_k(kernel, dim3(rows), dim3(vt), 0, s, a, lse); };
+    auto draw_run = [&](auto kernel, int vt) { launch_k(kernel, dim3(a.S), dim3(vt), shmem, s, a, (const float*)lse); };
     auto pick = [&](auto t) {
         using T = decltype(t);
-        if (two) run(row_lse_kernel<T, VT_SHORT, 2>, verify_kernel<T, VT_SHORT, 2>, VT_SHORT, VT_SHORT);
-        else if (is_short) run(row_lse_kernel<T, VT_SHORT, 4>, verify_kernel<T, VT_SHORT, 4>, VT_SHORT, VT_SHORT);
-        else run(row_lse_kernel<T, VT_LONG, 2>, verify_kernel<T, VT2_LONG, 4>, VT_LONG, VT2_LONG);
+        // Threads and chunks in flight per thread of a row, bf16 us with 256 x 2 / 256 x 4 / 512 x 2: two
+        // where 256 threads then cover the row (S 1000, B 2, V 2000 6.4 / 8.3 / 10.8), 512 threads on few
+        // long rows (S 1, B 2, V 50257 6.5 / 6.0 / 5.6; fp32 8.1 / 6.7 / 6.0), else four (S 256, B 16, V
+        // 5000 19.2 / 17.8 / 24.4)
+        if (hint) lse_run(row_lse_kernel<T, 512, 2, true>, 512);
+        else if (nchunk <= 2 * 256) lse_run(row_lse_kernel<T, 256, 2, false>, 256);
+        else if (!is_short && rows <= 256) lse_run(row_lse_kernel<T, 512, 2, false>, 512);
+        else lse_run(row_lse_kernel<T, 256, 4, false>, 256);
+        // Threads of a sequence's draw: as many as fit where every sequence has a CU to itself, fewer the
+        // more of them share one (bf16, B 2 or 3, us with 256 / 512 / 1024 threads: V 50257 S 256 28.8 /
+        // 19.0 / 15.9, S 700 32.9 / 27.5 / 34.1, S 3000 87 / 88 / 123; V 5000 10.6 / 9.7 / 9.4, 11.0 / 10.3 /
+        // 14.3, 22.2 / 27.2 / 41.1); 256 where those cover the row
+        if (nchunk <= 2 * 256 || a.S > 768) draw_run(verify_kernel<T, 256, 2>, 256);
+        else if (a.S > 256) draw_run(verify_kernel<T, 512, 2>, 512);
+        else draw_run(verify_kernel<T, 1024, 2>, 1024);
     };
     if (logits_dtype == DD_BF16) pick(bf16_t{});
     else pick(float{});

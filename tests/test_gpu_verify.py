@@ -198,3 +198,27 @@ def test_spec_verify_reports_only_the_tokens_it_tested():
         assert dd.read_device_error(err) == want
         if want == 0:
             assert np.array_equal(no.cpu().numpy(), n)
+
+
+DRAW_CASES = [
+    # S, B, V, dtype, noise, closeness: either side of the lines where the drawing kernel changes its
+    # threads (256 threads while 512 chunks of 16 bytes cover a row; beyond that 1024 up to 256 sequences,
+    # 512 up to 768, then 256) and its layout of words (one candidate per lane up to 64 groups, and in a
+    # last group of up to 64 classes), and where the log-sum-exp kernel takes 512 threads (more than 2048
+    # chunks on up to 256 rows)
+    (256, 2, 4096, "bf16", "philox", 1.0),
+    (256, 2, 4104, "bf16", "philox", 1.0),
+    (257, 2, 4104, "bf16", "explicit", 1.0),
+    (768, 2, 2052, "fp32", "philox", 1.0),
+    (769, 2, 2052, "fp32", "philox", 1.0),
+    (40, 3, 16384, "bf16", "philox", 1.0),
+    (40, 3, 16448, "bf16", "philox", 1.0),
+    (52, 3, 16449, "bf16", "explicit", 1.0),
+    (200, 3, 64, "fp32", "philox", 1.0),
+    (200, 3, 65, "bf16", "explicit", 1.0),
+]
+
+
+@pytest.mark.parametrize("case", DRAW_CASES, ids=lambda c: f"S{c[0]}-B{c[1]}-V{c[2]}-{c[3]}-{c[4]}")
+def test_spec_verify_at_the_lines_between_draw_forms(case):
+    test_spec_verify_parity(case)
