@@ -352,12 +352,14 @@ dd_status dd_psi_posterior_sample(int32_t prior, const void* logits, int32_t log
  * and carried-over rows need no logits.  With d_model and d_mlp multiples of 128 and no
  * adapters, the last layer also runs on those rows alone from its attention queries on (keys and
  * values still cover every row), since past that point a row's values reach only its own logits;
- * the listed rows' logits are unchanged.  bf16 with d_model % 128
+ * the listed rows' normalised rows are bit for bit those of dd_denoise_forward.  bf16 with d_model % 128
  * == 0: the vocabulary projection also writes, beside each logit row, the log-sum-exp of each
  * group of DD_GUMBEL_GROUP classes (from the rounded logits it stores), and the draw reads those
  * and one group of logits per row instead of the whole row.  The result equals calling
- * dd_denoise_forward and dd_posterior_sample on every row, up to the summation order inside each
- * group's log-sum-exp (a draw can differ only where two level-1 scores lie within a few ulps);
+ * dd_denoise_forward and dd_posterior_sample on every row, up to two orders of summation: inside each
+ * group's log-sum-exp, and inside a logit where the vocabulary projection begins K elsewhere because the
+ * row falls into another tile (it may then round to the neighbouring bf16 value).  A draw can differ only
+ * where two of its scores lie that close;
  * dd_psi_sample_loop with DD_LOOP_POSTERIOR_PASS makes the draw take its own pass over the
  * logit rows instead, as dd_posterior_sample does.  The mask id is cfg->mask_id.  The last
  * step's logits and log-sum-exps stay in the workspace (dd_loop_workspace_layout).
@@ -398,7 +400,7 @@ dd_status dd_sample_loop(const dd_config* cfg, const void* params, int32_t B, in
  * unmasked before a step first keep or remask (no logits), then the
  * masked rows that the step unmasks run the vocabulary projection and the draw
  * as in dd_sample_loop; the result equals dd_denoise_forward followed by
- * dd_psi_posterior_sample on every row.
+ * dd_psi_posterior_sample on every row, up to the same orders of summation.
  */
 dd_status dd_psi_sample_loop(const dd_config* cfg, const void* params, int32_t B, int32_t L,
                              int32_t T, const double* alphas, const double* kappas,

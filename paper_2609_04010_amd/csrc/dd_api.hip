@@ -287,21 +287,23 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         return launch_gemm(dt, EPI_GATE, KC_GEMM_LORA, g, s);
     };
 
-    // Splits a residual projection over K (launch_gemm's choice, or `forced` ways where given) as far
-    // as the free regions of the workspace hold its partials ([rows][d] fp32 each), and describes
-    // them to the normalisation that reads the row next.
+    // Free regions of the workspace as slabs of [M][d] fp32, at most MAX_SPLITS - 1.
     struct Region {
         char *begin, *end;
     };
-    auto split_k = [&](GemmArgs& g, LnSlabs& add, int64_t rows, int forced, std::initializer_list<Region> free_ws) {
-        g.k_base = g.K - r;
-        const size_t need = (size_t)rows * d * sizeof(float);
-        add = LnSlabs{};
-        g.splits = 1;
+    auto slabs = [&](float** out, std::initializer_list<Region> free_ws) {
+        const size_t need = (size_t)M * d * sizeof(float);
         int n = 0;
         for (const Region& f : free_ws)
-            for (char* p = f.begin; n < MAX_SPLITS - 1 && p + need <= f.end; p += need) g.slab[n++] = (float*)p;
-        g.splits = forced ? std::max(1, std::min({forced, n + 1, g.k_base / 128})) : gemm_splits(dt, EPI_BIAS_RESID, g, n + 1);
+            for (char* p = f.begin; n < MAX_SPLITS - 1 && p + need <= f.end; p += need) out[n++] = (float*)p;
+        return n;
+    };
+    // Splits a residual projection over K by launch_gemm's choice for M rows, as far as `free_ws` holds
+    // its partials, and describes them to the normalisation that reads the row next.
+    auto split_k = [&](GemmArgs& g, LnSlabs& add, std::initializer_list<Region> free_ws) {
+        g.k_base = g.K - r;
+        add = LnSlabs{};
+        g.splits = gemm_plan(dt, EPI_BIAS_RESID, g, slabs(g.slab, free_ws) + 1).splits;
         add.n = g.splits - 1;
         for (int i = 0; i < add.n; ++i) add.slab[i] = g.slab[i];
     };
@@ -335,23 +337,24 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         DD_TRY(launch_attn(dt, aa, s));
         if (tail) {
             // The listed rows are few in most steps (about M / T from an all-mask start), where the
-            // 256-row tiles leave most CUs idle through a whole K loop.  Up to TAIL_ROWS rows the ring
-            // kernel's 64 x 64 tiles do these GEMMs, the residual ones split over K; for larger M each
-            // is launched twice, gated on the device-side count, with the shape's usual tiles above.
+            // 256-row tiles leave most CUs idle through a whole K loop.  Up to TAIL_ROWS rows ring
+            // tiles do these GEMMs; for larger M each is launched twice, gated on the device-side
+            // count, with the shape's usual tiles above.  The sums keep the order that the same layer
+            // has on all M rows (its splits, and its 32 x 32 tiles where it takes those; the other
+            // tiles all walk K from its start), so the listed rows end as they would there, bit for
+            // bit: split four ways by their own number they would save about 6 us per step at B 1 L
+            // 1024 T 16 (of 860) and draw other tokens than the separate entry points.
             constexpr int TAIL_ROWS = 2048;
-            const int64_t cap = std::min<int64_t>(M, TAIL_ROWS);
             auto gated = [&](GemmArgs ga, int epi, int cls) -> dd_status {
+                const int tile = gemm_plan(dt, epi, ga, ga.splits).tile == TILE_32K ? TILE_32K : TILE_TAIL;
                 if (M > TAIL_ROWS) {
-                    GemmArgs big = ga;
-                    big.m_gate = TAIL_ROWS;
-                    big.m_side = 0;
-                    big.splits = 1;
-                    DD_TRY(launch_gemm(dt, epi, cls, big, s));
                     ga.m_gate = TAIL_ROWS;
+                    ga.m_side = 0;
+                    DD_TRY(launch_gemm(dt, epi, cls, ga, s));
                     ga.m_side = 1;
                 }
-                ga.m_rows = (int)cap;
-                ga.tile_hint = TILE_TAIL + 1;
+                ga.m_rows = (int)std::min<int64_t>(M, TAIL_ROWS);
+                ga.tile_hint = tile + 1;
                 return launch_gemm(dt, epi, cls, ga, s);
             };
             float* hc = (float*)qkv;
@@ -359,17 +362,16 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
             g = {att, dr, tp(b + 4), dr, tp(b + 5), hc, d, (int)M, d, dr, nullptr, vocab_count};
             g.c_in = h;
             g.c_rows = vocab_rows;
-            split_k(g, add, cap, MAX_SPLITS, {{(char*)mlp, (char*)ws + w.total_fwd}});
-            add.gate = M > TAIL_ROWS ? TAIL_ROWS : 0;
+            split_k(g, add, {{(char*)mlp, (char*)ws + w.total_fwd}});
             add.h_out = hc;
             DD_TRY(gated(g, EPI_BIAS_RESID, KC_GEMM_O));
             DD_TRY(launch_ln(dt, c->norm, hc, M, d, tp(b + 6), tp(b + 7), c->norm_eps, xln, dr, s, vocab_count, &add));
             g = {xln, dr, tp(b + 8), dr, tp(b + 9), mlp, Fr, (int)M, F, dr, nullptr, vocab_count};
             DD_TRY(gated(g, EPI_BIAS_GELU, KC_GEMM_MLP1));
-            // (the residual rows h have been read for the last time)
+            // (the residual rows h have been read for the last time; like the q|k|v buffer of the
+            // other layers, the two regions hold two slabs)
             g = {mlp, Fr, tp(b + 10), Fr, tp(b + 11), hc, d, (int)M, d, Fr, nullptr, vocab_count};
-            split_k(g, add, cap, MAX_SPLITS, {{(char*)h, (char*)xln}, {(char*)(hc + M * d), (char*)mlp}});
-            add.gate = M > TAIL_ROWS ? TAIL_ROWS : 0;
+            split_k(g, add, {{(char*)h, (char*)xln}, {(char*)(hc + M * d), (char*)mlp}});
             DD_TRY(gated(g, EPI_BIAS_RESID, KC_GEMM_MLP2));
             DD_TRY(launch_ln(dt, c->norm, hc, M, d, tp(lnf), tp(lnf + 1), c->norm_eps, xln, dr, s, vocab_count, &add));
             break;
@@ -377,7 +379,8 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         if (r > 0) DD_TRY(lora_down(att, dr, d, a0 + 1));
         LnSlabs add;
         g = {att, dr, tp(b + 4), dr, tp(b + 5), h, d, (int)M, d, dr, nullptr, nullptr};
-        split_k(g, add, M, 0, {{(char*)mlp, (char*)ws + w.total_fwd}, {(char*)qkv, (char*)att}});
+        // (the q|k|v buffer is free as well, but not in the compacted last layer, which has to split alike)
+        split_k(g, add, {{(char*)mlp, (char*)ws + w.total_fwd}});
         add.h_out = h;
         DD_TRY(launch_gemm(dt, EPI_BIAS_RESID, KC_GEMM_O, g, s));
         DD_TRY(launch_ln(dt, c->norm, h, M, d, tp(b + 6), tp(b + 7), c->norm_eps, xln, dr, s, nullptr, &add));
@@ -386,7 +389,7 @@ static dd_status run_forward(const dd_config* c, const void* params, const int32
         DD_TRY(launch_gemm(dt, EPI_BIAS_GELU, KC_GEMM_MLP1, g, s));
         if (r > 0) DD_TRY(lora_down(mlp, Fr, F, a0 + 3));
         g = {mlp, Fr, tp(b + 10), Fr, tp(b + 11), h, d, (int)M, d, Fr, nullptr, nullptr};
-        split_k(g, add, M, 0, {{(char*)qkv, (char*)mlp}});
+        split_k(g, add, {{(char*)qkv, (char*)mlp}});
         add.h_out = l + 1 < nl ? h : nullptr;   // after the last layer only the normalised row is read
         DD_TRY(launch_gemm(dt, EPI_BIAS_RESID, KC_GEMM_MLP2, g, s));
         const int gn = (l + 1 < nl) ? b + 12 : lnf;
@@ -726,8 +729,9 @@ dd_status dd_psi_sample_loop(const dd_config* cfg, const void* params, int32_t B
         return DD_OK;
     };
     // Masked prior: rows already unmasked are carried over and need no logits, so the vocabulary
-    // projection and the draw run on the compacted list of still-masked rows (same per-row
-    // arithmetic and noise counters as the full path, so the result is identical).
+    // projection and the draw run on the compacted list of still-masked rows (same per-row arithmetic
+    // up to the normalised rows and same noise counters as the full path; the vocabulary projection's
+    // K order goes with the tile a row falls into, see its kernel).
     const bool compact = cfg->prior == DD_PRIOR_MASK && gemm_gather_supported(cfg->dtype, cfg->d_model);
     int32_t* rows = (int32_t*)(wsc + w.rows);
     int32_t* count = (int32_t*)(wsc + w.count);

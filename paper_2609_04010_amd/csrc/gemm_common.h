@@ -38,7 +38,7 @@ DD_DEV float gate_row_scale(const GemmArgs& g, int m) {
 // wavefronts per CU), 64 x 64 with four stages (two workgroups of four wavefronts per CU) or three
 // stages (three per CU), 32 x 32 with K over the four wavefronts, and (fp32) 32 x 64 with K over two
 // pairs of wavefronts, and 128 x 192 with three stages (one workgroup of eight wavefronts per CU)
-enum RingTile { RING_128 = 0, RING_64_DEEP = 1, RING_64 = 2, RING_32K = 11, RING_32X64 = 12,
+enum RingTile { RING_128 = 0, RING_64_DEEP = TILE_TAIL, RING_64 = 2, RING_32K = TILE_32K, RING_32X64 = 12,
                 RING_128X192 = 13 };
 void launch_gemm_ring(int dtype, RingTile tile, int epi, const GemmArgs& g, hipStream_t s);
 double gemm_ring_us(RingTile tile, int64_t M, int64_t N, int64_t K, int splits, int cus);

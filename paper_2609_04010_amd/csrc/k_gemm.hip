@@ -790,12 +790,6 @@ static int num_cus() {
     return n;
 }
 
-// The tile of a bf16 product: one of the ring kernel's (0 .. 2) or a 256-row tile of this file (4 .. 7),
-// and over how many workgroups K is split (residual epilogue on a ring tile only).
-struct Plan {
-    int tile, splits;
-};
-
 // Splits of a residual projection on ring tiles, at least two K-tiles each.  Attention output (K 768, N
 // 768) 4.5 / 5.5 / 7.2 us with 4 / 2 / 1 at M 64, 6.7 / 6.4 / 8.1 at M 512, 7.6 / 7.4 with 2 / 1 at M
 // 1024; MLP down (K 3072) 7.0 / 10.5 / 16 at M 64, 12.7 / 13.5 / 16 at M 512, 13.6 with 2 against 15.6
@@ -812,8 +806,10 @@ static int64_t tiles_of(const GemmArgs& g, int bm, int bn) {
     return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
 }
 
-// The smallest estimated time, or 32 x 32 tiles where those do not fill the CUs.  The 256-row tiles (K % 128 == 0) in whole rounds of workgroups over
-// the CUs: the N width (256 or 192) with the smaller time (a round of 192-wide tiles takes about 0.85
+// The tile of a bf16 product: one of the ring kernel's (RingTile) or a 256-row tile of this file (4 .. 7),
+// and over how many workgroups K is split (residual epilogue on a ring tile only).  The smallest
+// estimated time, or 32 x 32 tiles where those do not fill the CUs.  The 256-row tiles (K % 128 == 0) in
+// whole rounds of workgroups over the CUs: the N width (256 or 192) with the smaller time (a round of 192-wide tiles takes about 0.85
 // of a round of 256-wide ones), in the 8-wavefront form (two wavefronts per SIMD, 2-6 % faster than
 // four wavefronts of twice the sub-tile), per K-tile 1.08 us (192) or 1.79 us (256) and 9 us besides,
 // fitted like the ring tiles' (10 % rms).  Measured at K 768, N 2304 / 3072: ring 11.1 / 11.6 us against
@@ -821,7 +817,7 @@ static int64_t tiles_of(const GemmArgs& g, int bm, int bn) {
 // against 57.6 at M 1024, 35.9 against 57.8 at M 4096, 103.7 against 76.8 at M 16384.  Products with
 // N <= 128 (adapter down-projections) leave the 256-row tiles one workgroup per 256 rows: ring tiles
 // only.  A split costs the next normalisation one more slab to read.
-static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
+static GemmPlan plan_tile(const GemmArgs& g, int epi, int max_splits) {
     const char* e = getenv("DD_GEMM_TILE");
     const int forced = e ? atoi(e) : -1;
     const bool wide_ok = g.K % (2 * BK) == 0;
@@ -831,10 +827,10 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
         return {forced <= 2 ? forced : forced == 3 ? 0 : 1, 1};
     }
     const int cus = num_cus();
-    // (residual projections only up to 128 rows, so that their K order stays that of the 64 x 64 tiles
-    // over the row counts of ring_splits's first step)
+    // (residual projections only up to 128 rows: four groups of K summed in the workgroup there, two to
+    // four slabs from 129 rows on)
     if (tiles_of(g, 32, 32) <= cus && (epi != EPI_BIAS_RESID || g.M <= 128)) return {RING_32K, 1};
-    Plan best = {-1, 1};
+    GemmPlan best = {-1, 1};
     double t_best = 0.0;
     if (wide_ok && g.N > 128) {
         const int64_t tm = (g.M + DM - 1) / DM;
@@ -856,8 +852,8 @@ static Plan plan_tile(const GemmArgs& g, int epi, int max_splits) {
     return best;
 }
 
-int gemm_splits(int dtype, int epi, const GemmArgs& g, int max_splits) {
-    return dtype == DD_BF16 ? plan_tile(g, epi, max_splits).splits : 1;
+GemmPlan gemm_plan(int dtype, int epi, const GemmArgs& g, int max_splits) {
+    return dtype == DD_BF16 ? plan_tile(g, epi, std::max(max_splits, 1)) : GemmPlan{-1, 1};
 }
 
 template <int EPI, int ROLE, int TBN, int WGM, int WGN, int DMR = DM>

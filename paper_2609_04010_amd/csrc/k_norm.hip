@@ -91,10 +91,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const float* h, int64_t rows, c
                                                  const int32_t* m_count, LnSlabs add) {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (m_count) {
-        if (add.gate > 0 && *m_count > add.gate) add.n = 0;
-        rows = min(rows, (int64_t)*m_count);
-    }
+    if (m_count) rows = min(rows, (int64_t)*m_count);
     if (row >= rows) return;
     constexpr int d = NPL * 64;
     float x[NPL];
@@ -178,10 +175,7 @@ __global__ __launch_bounds__(256) void ln_bf16_v4_kernel(const float* h, int64_t
                                                          const int32_t* m_count, LnSlabs add) {
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * LN_RPW;
     const int lane = threadIdx.x & 63;
-    if (m_count) {
-        if (add.gate > 0 && *m_count > add.gate) add.n = 0;
-        rows = min(rows, (int64_t)*m_count);
-    }
+    if (m_count) rows = min(rows, (int64_t)*m_count);
     if (row0 >= rows) return;
     constexpr int d = NV * 256;
     float4 x[LN_RPW][NV];

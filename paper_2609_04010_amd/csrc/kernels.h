@@ -55,8 +55,10 @@ enum Epi { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESID = 2, EPI_PLAIN = 3, E
            EPI_LSE_CDF = 6 };
 
 constexpr int MAX_SPLITS = 4;
-// the ring kernel's 64 x 64 tile with four stages, as a GemmArgs::tile_hint (+ 1) for few listed rows
-constexpr int TILE_TAIL = 1;
+// tiles of the ring kernel by number (a GemmArgs::tile_hint is one of them + 1): 64 x 64 with four stages,
+// for few listed rows; 32 x 32 with K over four wavefronts, the one tile that does not sum K from its
+// start to its end
+constexpr int TILE_TAIL = 1, TILE_32K = 11;
 
 struct GemmArgs {
     const void* A;   // [M][K], row stride lda
@@ -165,11 +167,10 @@ dd_status launch_embed_ln(int dtype, int norm, const int32_t* z, int64_t rows, i
                           const void* b, float eps, float* h, void* xln, int64_t ldo, int32_t* err,
                           hipStream_t s);
 // Partials of a split residual projection: a row is h + slab[0] + .. + slab[n - 1] (each [rows][d]),
-// written back to h_out (nullable) and normalised.  With m_count, only while *m_count <= gate
-// (gate 0: always): above it the projection was not split.
+// written back to h_out (nullable) and normalised.
 struct LnSlabs {
     const float* slab[MAX_SPLITS - 1];
-    int n, gate;
+    int n;
     float* h_out;
 };
 // out rows have stride ldo (elements) >= d
@@ -186,9 +187,13 @@ bool attn_supported(int dtype, int dh);
 // by *pre unmasks (the others stay masked and need no logits)
 dd_status launch_compact(const int32_t* z, int64_t M, int32_t mask_id, int32_t* idx, int32_t* count,
                          hipStream_t s, int L = 0, int32_t* seq = nullptr, const PostArgs* pre = nullptr);
-// Over how many workgroups launch_gemm would split K for this product, at most max_splits (1: not
-// split; a caller that takes more sets g.splits and g.slab and adds the slabs afterwards).
-int gemm_splits(int dtype, int epi, const GemmArgs& g, int max_splits);
+// The tile launch_gemm takes for this product (bf16) and over how many workgroups it splits K, at most
+// max_splits (1: not split; a caller that takes more sets g.splits and g.slab and adds the slabs
+// afterwards).
+struct GemmPlan {
+    int tile, splits;
+};
+GemmPlan gemm_plan(int dtype, int epi, const GemmArgs& g, int max_splits);
 bool gemm_gather_supported(int dtype, int K);
 // the EPI_LSE epilogue (group log-sum-exps beside the logits) runs for this dtype and K
 bool gemm_lse_supported(int dtype, int K);

@@ -299,8 +299,9 @@ def _mixed_start(B, L, V, seed):
 def test_compacted_loop_equals_full_path_loop(c, over, B, L, T, start):
     """dd_sample_loop (vocabulary projection and draw on the still-masked rows only, and the last
     layer from its attention queries on as well) must give the same trajectory as
-    dd_denoise_forward + dd_posterior_sample applied to every row.  (The loop's group
-    log-sum-exps come from the projection's epilogue, the entry point's from its own pass:
+    dd_denoise_forward + dd_posterior_sample applied to every row.  (The normalised rows are the same
+    bits on both sides.  The group log-sum-exps come from the projection's epilogue in the loop and from
+    the entry point's own pass there, and a logit's K order goes with the tile its row falls into:
     summation order only, which no draw at these seeds is close enough to feel.)"""
     torch = torch_or_skip()
     say("compacted loop", c, over, B, L, T, start)
@@ -425,7 +426,8 @@ def test_psi_loop_config1_free_running_matches_oracle():
 def test_psi_compacted_loop_equals_full_path_loop(kappa):
     """dd_psi_sample_loop (keep/remask of decoded rows, then the vocabulary projection and draw on
     the still-masked rows) must give the same trajectory as dd_denoise_forward +
-    dd_psi_posterior_sample on every row."""
+    dd_psi_posterior_sample on every row (up to the summation orders named above, which no draw here
+    feels)."""
     torch = torch_or_skip()
     say("psi compacted loop", kappa)
     cfg = workloads.model_cfg(2, n_layers=2)

@@ -156,3 +156,50 @@ def test_fp32_forward_matches_oracle(case):
     err = float(np.abs(got - oforward.forward(cfg, P, z, 0.5, vis)).max())
     say(f"max |dlogit| = {err:.3e}")
     assert err <= 1e-4
+
+
+LISTED_CASES = [
+    # overrides, B, L: the row counts on either side of the lines of the residual projections' split
+    # (128, 512, 1024 rows), and above 2048, where the layer is launched for many and for few listed rows
+    (dict(d_model=128, n_heads=2, vocab=12000), 1, 40),
+    (dict(d_model=128, n_heads=2, vocab=12000), 2, 64),
+    (dict(d_model=128, n_heads=2, vocab=12000), 3, 43),
+    (dict(d_model=128, n_heads=2, vocab=12000, d_mlp=128), 3, 50),    # no room for a slab beside the MLP rows
+    (dict(), 1, 150),
+    (dict(), 2, 256),
+    (dict(), 3, 200),
+    (dict(), 4, 275),
+    (dict(), 7, 300),
+]
+
+
+@pytest.mark.parametrize("case", LISTED_CASES, ids=lambda c: f"B{c[1]}-L{c[2]}-" + "-".join(f"{k}{v}" for k, v in c[0].items()))
+def test_listed_rows_have_the_full_path_logits(case):
+    """The loop's last layer runs on the listed rows alone; their logits are those of
+    dd_denoise_forward on every row, bit for bit.  Compared where the vocabulary projection sums K in
+    the same order on both sides: list index and token row both in the first tile of 256 rows."""
+    torch = torch_or_skip()
+    over, B, L = case
+    say("listed rows", case)
+    cfg = workloads.model_cfg(2, n_layers=2, max_len=L, **over)
+    V, M, T = cfg["vocab"], B * L, 3
+    buf = torch.zeros(dd.param_bytes(cfg), dtype=torch.uint8, device="cuda")
+    dd.init_params(cfg, buf, seed=45)
+    al = 1.0 - np.arange(T + 1) / T
+    z = torch.full((M,), V, dtype=torch.int32, device="cuda")
+    trace = torch.zeros((T + 1, M), dtype=torch.int32, device="cuda")
+    ws = torch.full((dd.loop_workspace_bytes(cfg, B, L),), 0xFF, dtype=torch.uint8, device="cuda")
+    dd.workspace_reset(ws)
+    dd.sample_loop(cfg, buf, B, L, T, al, z, ws, noise_seed=5, z_trace=trace)
+    lay = dd.loop_workspace_layout(cfg, B, L)
+    ld = lay["logits_ld"]
+    count = int(ws[lay["count"]:lay["count"] + 4].view(torch.int32).item())
+    rows = ws[lay["rows"]:lay["rows"] + 4 * count].view(torch.int32).long()
+    got = ws[lay["logits"]:lay["logits"] + 2 * count * ld].view(torch.bfloat16).view(count, ld)[:, :V]
+    full = torch.zeros((M, ld), dtype=torch.bfloat16, device="cuda")
+    ws_f = torch.zeros(dd.workspace_bytes(cfg, B, L), dtype=torch.uint8, device="cuda")
+    dd.denoise_forward(cfg, buf, trace[T - 1].clone(), B, L, al[1], full, ld, ws_f)
+    first = rows[:256][rows[:256] < 256]
+    say(f"{count} listed rows of {M}, {first.numel()} compared")
+    assert count == int((trace[T - 1] == V).sum()) and first.numel() > 0
+    assert torch.equal(got[:first.numel()], full[first][:, :V])
