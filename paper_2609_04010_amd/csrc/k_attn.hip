@@ -531,6 +531,23 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
             lt += s[j];
         }
         l = fmaf(l, corr, lt);
+        // A V element that is not finite would reach the queries that do not see its key as 0 times it:
+        // the products below then take 0 in its place, and the queries that see it get it afterwards.
+        bool odd = false;
+        if (MASKED) {
+            float t = 0.f;
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) t = fmaf(vf[i][j], 0.f, t);
+            odd = __any(t != t);
+            if (odd) {
+#pragma unroll
+                for (int i = 0; i < DB; ++i)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) vf[i][j] = isfinite(vf[i][j]) ? vf[i][j] : 0.f;
+            }
+        }
         // the tile's sums from zero, then added by the VALU (see the ring GEMM's fp32 sums)
 #pragma unroll
         for (int i = 0; i < DB; ++i) {
@@ -539,6 +556,27 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
             for (int j = 0; j < 16; ++j) part = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[i][j], s[j], part, 0, 0, 0);
 #pragma unroll
             for (int e = 0; e < 16; ++e) o[i][e] = fmaf(o[i][e], corr, part[e]);
+        }
+        if (MASKED && odd) {
+#pragma unroll 1
+            for (int x = 0; x < min(FK, L - kb0); ++x) {
+                // key x is score 4 (x / 8) + x % 4 of the lanes with lane / 32 == (x / 4) % 2
+                const int jx = 4 * (x >> 3) + (x & 3), key = kb0 + x;
+                float p = 0.f;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) p = j == jx ? s[j] : p;
+                p = __shfl(p, (lane & 31) + 32 * ((x >> 2) & 1), 64);
+                const bool vis = key < pre || (key >= lo && key < hi);
+                const float* vr = base + 2 * d + (int64_t)key * a.ld;
+#pragma unroll
+                for (int i = 0; i < DB; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int c = 32 * i + 8 * (e >> 2) + 4 * grp + (e & 3);
+                        const float v = vr[min(c, D - 1)];
+                        if (vis && !isfinite(v)) o[i][e] = fmaf(p, v, o[i][e]);
+                    }
+            }
         }
         m = mn;
     }

@@ -279,3 +279,43 @@ def test_forward_ex_without_pattern_or_gate_equals_forward(c):
             outs.append(logits.float().cpu().numpy())
         say(f"workload {c} {extra}: identical {np.array_equal(outs[0], outs[1])}")
         assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("d,heads", [(64, 4), (64, 2), (64, 1), (128, 1)])   # head dims 16, 32, 64, 128
+@pytest.mark.parametrize("pattern,block", [("causal", 0), ("block_causal", 6), ("draft_train", 7)])
+def test_fp32_non_finite_rows_stay_with_the_queries_that_see_them(pattern, block, d, heads, bad):
+    """A token whose values are not finite, in the middle of a 32-key tile and once more in the ragged last
+    one: a position that sees neither (through both layers) keeps its logits bit for bit, every other
+    one's are NaN."""
+    torch = torch_or_skip()
+    L, V = 84, 50
+    say("non-finite", pattern, block, d, heads, bad)
+    cfg = workloads.model_cfg(1, d_model=d, n_heads=heads, d_mlp=128, vocab=V, max_len=L)
+    P = oparams.init_params(cfg, 51)
+    P["tok_emb"] = P["tok_emb"].copy()
+    P["tok_emb"][V - 1, 3] = bad
+    blob = dd.pack_params(cfg, oparams.storage_tensors(cfg, P))
+    buf = torch.zeros(blob.size, dtype=torch.uint8, device="cuda")
+    dd.init_params(cfg, buf, host_blob=blob)
+    host = dd.attn_mask_build(pattern, L, block)
+    j = np.arange(L)[None, :]
+    vis = (j < host[0][:, None]) | ((j >= host[1][:, None]) & (j < host[2][:, None]))
+    seen = np.linalg.matrix_power(vis.astype(np.int64) | np.eye(L, dtype=np.int64), cfg["n_layers"]) > 0
+    at = [45, 82]
+    clean = np.random.default_rng(3).integers(0, V - 1, size=(1, L))
+    dirty = clean.copy()
+    dirty[0, at] = V - 1
+    ld = int(dd.logits_ld(V))
+    out = []
+    for z in (clean, dirty):
+        logits = torch.zeros((L, ld), dtype=torch.float32, device="cuda")
+        ws = torch.zeros(dd.workspace_bytes(cfg, 1, L), dtype=torch.uint8, device="cuda")
+        dd.denoise_forward_ex(cfg, buf, dev_i32(torch, z.reshape(-1)), 1, L, 0.5, logits, ld, ws,
+                              attn_mask=dev_i32(torch, host.reshape(-1)))
+        assert dd.read_device_error(ws[:4].view(torch.int32)) == 0
+        out.append(logits[:, :V].cpu().numpy())
+    hit = seen[:, at].any(axis=1)
+    assert hit.any() and not hit.all()
+    assert np.array_equal(out[1][~hit], out[0][~hit])
+    assert np.isnan(out[1][hit]).all()
