@@ -649,15 +649,19 @@ dd_status launch_attn(int dtype, const AttnArgs& a, hipStream_t s) {
     }
     if (dtype == DD_BF16) {
         const int64_t bh = (int64_t)a.H * a.B, cus = num_cus_attn();
-        // Key groups where the query blocks alone leave CUs idle or unevenly loaded (12 heads, us with
-        // 1 / 2 / 4 groups; full, then causal): B 1 L 1024 27.0 / 16.7 / 12.4, 25.7 / 19.3 / 14.7; B 2
-        // L 1000 27.3 / 17.3 / 21.4, 27.7 / 19.5 / 21.6; at 1.5 blocks of 128 per CU B 4 L 1024 30.4 /
-        // 30.8 / 31.2, 28.5 / 27.2 / 33.6, B 8 L 512 19.6 / 21.2 / 22.9, B 1 L 4096 95.9 / 89.8 / 80.8,
-        // 83.8 / 58.7 / 67.7.  By B, H and L alone: a query's sums are the same listed or not.
+        // Key groups where the query blocks alone leave CUs idle, and under a pattern on long sequences up
+        // to two blocks of 128 per CU, whose work differs.  Us with 1 / 2 / 4 groups, without a pattern,
+        // then causal, then [x, z_1]: 0.4 blocks per CU (12 heads B 1 L 1024) 19.0 / 15.3 / 11.2, 25.1 / 18.3
+        // / 13.5, 20.0 / 15.0 / 11.8; 0.75 (B 2 L 1024) 20.2 / 16.6 / 20.7, 25.9 / 18.6 / 20.6, 20.6 / 15.2 /
+        // 19.1; 1.5 (B 4 L 1024) 24.0 / 29.8 / 30.5, 26.7 / 26.0 / 31.9, 21.2 / 22.6 / 27.8; 1.5 (B 1 L 4096)
+        // 76.1 / 90.4 / 83.2, 79.4 / 58.8 / 67.5, 47.4 / 39.2 / 46.7; 2 (16 heads B 1 L 4096) 76.3 / 91.2 /
+        // 106, 79.8 / 58.2 / 75.7, 48.6 / 39.2 / 54.6; 2.25 (24 heads B 1 L 3000) 74.3 / 99.8 / 101, 60.5 /
+        // 68.0 / 71.9, 39.9 / 49.2 / 51.7.  By B, H and L alone: a query's sums are the same listed or not
+        // (listed ones have no pattern).
         const int64_t wg = bh * ceil_div(a.L, 128);
         int kg = 1;
         if (bh * ceil_div(a.L, 64) <= cus) kg = 4;
-        else if (wg <= cus || (a.L >= 2048 && wg < 2 * cus)) kg = 2;
+        else if (wg <= cus || (a.mask && a.L >= 2048 && wg <= 2 * cus)) kg = 2;
         if (kg == 4) launch_attn_bf16<4>(a, s);
         else if (kg == 2) launch_attn_bf16<2>(a, s);
         else launch_attn_bf16<1>(a, s);

@@ -78,6 +78,8 @@ ATTN_CASES = [
     (1, 65, None, 0), (1, 130, "causal", 0), (1, 200, "draft_train", 4),
     (5, 256, None, 0), (6, 256, "block_causal", 48), (2, 641, None, 0), (2, 641, "causal", 0),
     (1, 2049, "causal", 0), (1, 2049, None, 0), (22, 129, None, 0), (22, 130, "draft_train", 13),
+    # between one and two query blocks per CU on a long sequence: two groups under a pattern only
+    (2, 2049, None, 0), (2, 2049, "causal", 0), (2, 2050, "draft_train", 41),
 ]
 
 
