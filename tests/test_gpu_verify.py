@@ -125,14 +125,15 @@ def test_spec_verify_is_lossless_chi2():
     assert pvalue > 1e-3
 
 
-def test_spec_verify_degenerate_logits_are_reported():
+@pytest.mark.parametrize("S,B,V", [(8, 4, 600), (342, 3, 16391)])   # row by row, position by position
+def test_spec_verify_degenerate_logits_are_reported(S, B, V):
     """NaN in every target row of one sequence, a NaN inside an otherwise -inf 16-byte chunk of every
     target row of another (the thread reading that chunk meets no finite logit), +inf in every
     target row of a third: DD_DEVERR_LOGITS and z = 0 there.  NaN in the draft rows of another: its
     draw stays valid (the residual falls back to p).  Every other sequence is bit-identical to the
     clean call."""
     torch = torch_or_skip()
-    S, B, V, dt = 8, 4, 600, "bf16"
+    dt = "bf16"
     pl, ql, draft = _case(17, S, B, V, dt, 0.3)
     pd, qd = pl.copy(), ql.copy()
     pd[2, :, 5] = np.nan
@@ -160,25 +161,34 @@ def test_spec_verify_degenerate_logits_are_reported():
 
 
 HINT_CASES = [
-    # S, B, V, dtype, noise, closeness: S B at and above the line where kernel 1 works position by
-    # position (1024), blocks of more than one wavefront of drafted tokens
+    # S, B, V, dtype, noise, closeness: either side of the lines where the log-sum-exp kernel works
+    # position by position (more than 2048 chunks of 16 bytes in a row: V 16384 bf16, 8192 fp32; more than
+    # 1024 positions), at low and high acceptance, and blocks of more than one wavefront of drafted tokens
     (64, 16, 700, "bf16", "philox", 0.5),
     (65, 16, 700, "bf16", "explicit", 0.5),
     (300, 4, 515, "fp32", "philox", 1.0),
     (20, 70, 300, "bf16", "philox", 0.02),
     (3, 66, 300, "fp32", "explicit", 0.05),
+    (342, 3, 16384, "bf16", "philox", 0.5),
+    (341, 3, 16391, "bf16", "philox", 0.5),
+    (342, 3, 16391, "bf16", "philox", 0.5),
+    (342, 3, 8195, "fp32", "explicit", 0.05),
+    (129, 8, 8196, "fp32", "philox", 1.5),
+    (65, 16, 16400, "bf16", "explicit", 2.0),
+    (16, 66, 8196, "fp32", "philox", 0.02),
 ]
 
 
-@pytest.mark.parametrize("case", HINT_CASES, ids=lambda c: f"S{c[0]}-B{c[1]}-{c[3]}-{c[4]}")
+@pytest.mark.parametrize("case", HINT_CASES, ids=lambda c: f"S{c[0]}-B{c[1]}-V{c[2]}-{c[3]}-{c[4]}")
 def test_spec_verify_position_by_position(case):
     test_spec_verify_parity(case)
 
 
-def test_spec_verify_reports_only_the_tokens_it_tested():
+@pytest.mark.parametrize("S,B,V", [(130, 9, 400), (342, 3, 16391)])   # row by row, position by position
+def test_spec_verify_reports_only_the_tokens_it_tested(S, B, V):
     """A drafted id outside [0, V) is reported iff its position is tested: up to the first rejection."""
     torch = torch_or_skip()
-    S, B, V, dt = 130, 9, 400, "bf16"
+    dt = "bf16"
     pl, ql, draft = _case(23, S, B, V, dt, 0.6)
     n, _ = _run_gpu(torch, pl, ql, draft, dt, seed=4, step=1)
     ld = int(dd.logits_ld(V))
