@@ -341,19 +341,42 @@ def test_degenerate_logit_rows_are_reported_and_keep_their_token(prior, dt):
     assert ((dirty >= 0) & (dirty <= V)).all()
 
 
-@pytest.mark.parametrize("V", [1, 2, 5, 1023, 1024, 1025, 1030, 2047])
+@pytest.mark.parametrize("V", [1, 2, 5, 1023, 1024, 1025, 1030, 2047, 4096, 4097, 4100, 4103])
 def test_gaussian_latent_at_block_edges(V):
     """Clean tokens in the first, the last whole and the ragged block of four classes, and in the
-    blocks on either side of a thread's first (256 blocks): the ids equal the oracle's."""
+    blocks on either side of a thread's first (256 blocks), class by class (up to 1024 blocks) and by
+    largest words (more): the ids equal the oracle's.  At 0.9 the clean token wins in some rows."""
     torch = torch_or_skip()
     x = np.array([v for v in (0, 1, 3, 4, 5, 1019, 1020, 1023, 1024, 1027, 1028, V - 5, V - 4, V - 2, V - 1)
                   if 0 <= v < V] * 4, dtype=np.int64)
-    for at in (0.0, 0.999):
+    for at in (0.0, 0.9, 0.999):
         sigma = float(np.sqrt(1 - at * at))
         z = torch.empty(x.size, dtype=torch.int32, device="cuda")
         dd.gaussian_latent_argmax(dev_i32(torch, x), x.size, V, at, sigma, seed=99, step=7, z_out=z)
         ref = olatent.latent_argmax(x, V, at, sigma, seed=99, step=7)
         assert np.array_equal(z.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("V", [4097, 4100, 4103, 20481])
+def test_gaussian_latent_winner_at_block_edges(V):
+    """Rows whose largest latent is a class of the first block, of the blocks on either side of a
+    thread's first, of the last whole or of the ragged block (found by their words), with the clean token
+    beside it in the same block and elsewhere: the ids equal the oracle's."""
+    torch = torch_or_skip()
+    whole = V // 4 * 4
+    met = 0
+    for t in sorted({0, 3, 1020, 1023, 1024, 1027, whole - 4, whole - 1, min(whole, V - 1), V - 1}):
+        w = ophilox.counter_words(7, ophilox.STREAM_LATENT, 4, np.arange(100000), t)
+        for row in np.argsort(w)[-4:]:
+            for x in (t ^ 1, 2000):
+                if not 0 <= x < V:
+                    continue
+                z = torch.empty(1, dtype=torch.int32, device="cuda")
+                dd.gaussian_latent_argmax(dev_i32(torch, [x]), 1, V, 0.0, 1.0, seed=7, step=4, z_out=z, row0=int(row))
+                ref = olatent.latent_argmax([x], V, 0.0, 1.0, seed=7, step=4, rows=[int(row)])
+                assert int(z.item()) == ref[0], (t, row, x)
+                met += int(ref[0] == t)
+    assert met > 40
 
 
 @pytest.mark.parametrize("rows", [1, 256, 257])
