@@ -1,7 +1,8 @@
-"""Products on few rows (64 x 64 and 128 x 128 ring tiles, K split over workgroups): the forward pass
-against the oracle at the row counts where the tile or the split changes (1, 64 and 65 rows, 512 and
-513, 2048 and 2049), at K-tiles that are ragged (d_mlp and adapter ranks that are no multiple of 64),
-and the loop's listed rows against the full path.
+"""Products on few rows (ring tiles, K split over workgroups): the forward pass against the oracle at
+the row counts where the tile or the split changes (1, 64 and 65 rows; residual projections: 32 x 32
+tiles up to 128 rows, then MLP down split three ways up to 512 where its K is 2048 or more, two ways up
+to 1024, not split from 1025 on; 2048 and 2049), at K-tiles that are ragged (d_mlp and adapter ranks that
+are no multiple of 64), and the loop's listed rows against the full path.
 
 Bar: as for every forward pass, max |dlogit| <= 5e-2 in bf16 (measured here up to 1.3e-2)."""
 import numpy as np
@@ -26,7 +27,7 @@ CASES = [
     (dict(n_layers=1, vocab=300), 3, 171),
     (dict(n_layers=1, vocab=300), 8, 256),
     (dict(n_layers=1, vocab=300), 3, 683),
-    # one ragged K-tile (40, 8 and 56 of 64), split four and two ways and not split
+    # one ragged K-tile (40, 8 and 56 of 64), not split
     (dict(n_layers=1, vocab=300, d_mlp=1000), 1, 70),
     (dict(n_layers=1, vocab=300, d_mlp=520), 3, 200),
     (dict(n_layers=1, vocab=300, d_mlp=120), 5, 500),
@@ -39,7 +40,19 @@ CASES = [
     # the widths the four-features-per-lane normalisation takes besides 768 and 1024
     (dict(n_layers=1, vocab=300, d_model=256, n_heads=4, d_mlp=256, norm="rms"), 1, 33),
     (dict(n_layers=1, vocab=300, d_model=1536, n_heads=24, d_mlp=256), 2, 70),
-    # 128 x 192 tiles with ragged rows, columns and K
+    # MLP down at 128, 129, 1024 and 1025 rows
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4), 1, 128),
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4), 3, 43),
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4), 2, 512),
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4), 5, 205),
+    # a ragged K-tile (56 of 64; 24 adapter columns after it) in the last of three splits, then of two
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4, d_mlp=2104), 1, 150),
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4, d_mlp=2104), 2, 256),
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4, d_mlp=2104), 3, 171),
+    (dict(n_layers=1, vocab=300, d_model=256, n_heads=4, d_mlp=3000, lora_rank=24, lora_alpha=48.0), 2, 200),
+    # a residual projection on 128 x 192 tiles (attention output), ragged rows and columns
+    (dict(n_layers=1, vocab=64, d_model=256, n_heads=4, d_mlp=1024), 53, 238),
+    # 128 x 192 tiles with ragged rows, columns and K (MLP up)
     (dict(n_layers=1, vocab=300, lora_rank=8, lora_alpha=16.0), 7, 241),
 ]
 
@@ -124,7 +137,8 @@ F32_CASES = [
     (128, 2, 2, 2, 31, "block_causal", 5),
     (256, 2, 2, 1, 160, "draft_train", 8),
     (256, 4, 1, 2, 257, None, 0),
-    (768, 12, 1, 5, 120, None, 0),      # 600 rows: K split two ways
+    (768, 12, 1, 5, 120, None, 0),      # 600 rows: residual projections on 64 x 64 tiles, not split
+    (256, 4, 1, 4, 120, None, 0),       # 480 rows: on 32 x 64 tiles with K over two pairs of wavefronts
 ]
 
 
