@@ -33,10 +33,11 @@
  *     with dd_read_device_error.  No call aborts and no exception crosses the ABI.
  *   - Tuning override: the environment variable DD_GEMM_TILE = 0..10, when set,
  *     forces one tile variant of the bf16 projections (for tuning and for tests
- *     that cover every variant; 0 to 2: the ring kernel's 128 x 128 and 64 x 64
- *     tiles, 4 to 7: the 256-row tiles, 3 and 8 to 10: as 0 and 1).  It changes
- *     speed and the order in which K-slices are summed (vocabulary projection;
- *     residual projections on few rows); never the operation.
+ *     that cover every variant; 0 to 3: the ring kernel's 128 x 128, 64 x 64 with
+ *     four and with three stages, and 128 x 192 tiles, 4 to 7: the 256-row tiles,
+ *     8: the ring kernel's 32 x 32 tiles, 9 and 10: as 1).  It changes speed and the
+ *     order in which K-slices are summed (vocabulary projection; residual
+ *     projections on few rows; every projection with 8); never the operation.
  *     Nothing else in the library reads the environment.
  */
 #ifndef DD_H

@@ -823,8 +823,11 @@ static GemmPlan plan_tile(const GemmArgs& g, int epi, int max_splits) {
     const bool wide_ok = g.K % (2 * BK) == 0;
     if (g.a_rows) return {forced >= 4 && forced <= 7 ? forced : 6, 1};   // row gather: 256-row tiles only
     if (forced >= 0 && forced <= 10) {
-        if (forced >= 4 && forced <= 7) return {wide_ok ? forced : 0, 1};
-        return {forced <= 2 ? forced : forced == 3 ? 0 : 1, 1};
+        if (forced >= 4 && forced <= 7 && wide_ok) return {forced, 1};
+        static const int ring[11] = {RING_128, RING_64_DEEP, RING_64, RING_128X192, RING_128, RING_128, RING_128, RING_128,
+                                     RING_32K, RING_64_DEEP, RING_64_DEEP};
+        const int tile = ring[forced];
+        return {tile, epi == EPI_BIAS_RESID && tile != RING_32K ? ring_splits(g, max_splits) : 1};
     }
     const int cus = num_cus();
     // (residual projections only up to 128 rows: four groups of K summed in the workgroup there, two to

@@ -261,15 +261,21 @@ def test_loop_uniform_prior_runs_in_range():
     assert np.mean(trace[-1] != trace[0]) > 0.5          # the uniform prior keeps revising tokens
 
 
-@pytest.mark.parametrize("tile", ["0", "1", "2", "3", "4", "5", "6", "7", "8", "9", "10"])
-def test_forward_parity_every_gemm_tile(tile, monkeypatch):
-    """Each GEMM tile variant (64/128/256 rows x 32/128/192/256 columns, 1, 4 or 8 wavefronts) on
-    ragged M and N."""
+@pytest.mark.parametrize("tile,rank", [(t, 0) for t in range(9)] + [(t, 8) for t in (0, 1, 2, 3, 8)])
+def test_forward_parity_every_gemm_tile(tile, rank, monkeypatch):
+    """Each tile variant of the bf16 projections on ragged M and N: the ring kernel's 128 x 128, 64 x 64
+    (four and three stages), 128 x 192 (tile 3) and 32 x 32 (tile 8) tiles, K of the residual ones split
+    where the row count asks for it (MLP down two ways here, not on 32 x 32), and the four 256-row
+    variants.  With adapters of rank 8 every K is ragged (ring tiles only)."""
     torch = torch_or_skip()
-    monkeypatch.setenv("DD_GEMM_TILE", tile)
-    say("gemm tile", tile)
-    cfg = workloads.model_cfg(2, n_layers=2)
-    P, buf = _params_host(torch, cfg, 7)
+    monkeypatch.setenv("DD_GEMM_TILE", str(tile))
+    say("gemm tile", tile, rank)
+    if rank:
+        cfg = workloads.model_cfg(2, n_layers=2, vocab=1003, lora_rank=rank, lora_alpha=16.0)
+        P, buf = _params_seeded(torch, cfg, 7)
+    else:
+        cfg = workloads.model_cfg(2, n_layers=2)
+        P, buf = _params_host(torch, cfg, 7)
     z = workloads.masked_state(8, 3, 190, cfg["vocab"], 0.5)
     got = _forward_gpu(torch, cfg, buf, z, 0.5)
     ref = oforward.forward(cfg, P, z, 0.5)
