@@ -1,14 +1,10 @@
-// Types and device helpers shared by the bf16 GEMM kernels.
+// Device helpers shared by the GEMM kernels.
 #pragma once
 
 #include "kernels.h"
+#include "mfma.h"
 
 namespace dd {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // gelu_tanh(x) = 0.5 x (1 + tanh(y)) = x / (1 + exp(-2y)), y = sqrt(2/pi) (x + 0.044715 x^3), with
 // exp(-2y) = 2^(x (a + b x^2)), a = -2 sqrt(2/pi) log2(e), b = 0.044715 a: five VALU operations plus
@@ -24,9 +20,6 @@ DD_DEV float gelu_tanh_f32(float x) {
 }
 
 constexpr int BK = 64;   // K depth of an operand tile
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_void;
 
 // EPI_GATE row factor of output row m (m % gate_period is in range for any m, clamped rows too)
 DD_DEV float gate_row_scale(const GemmArgs& g, int m) {

@@ -34,12 +34,9 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "mfma.h"
 
 namespace dd {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int AK = 64;   // keys per tile
 constexpr int DH = 64;
@@ -62,8 +59,6 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 DD_DEV int ksw(int r) { return (r >> 1) & 7; }
 DD_DEV int vsw(int r) { return r & 6; }
 
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_void;
 DD_DEV v4s ds_read_tr16(const bf16_t* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
 }
@@ -611,23 +606,13 @@ bool attn_supported(int dtype, int dh) {
     return dh == 16 || dh == 32 || dh == 64 || dh == 128;
 }
 
-static int num_cus_attn() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0, v = 0;
-        (void)hipGetDevice(&dev);
-        n = (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) ? v : 256;
-    }
-    return n;
-}
-
 template <int KG>
 static void launch_attn_bf16(AttnArgs a, hipStream_t s) {
     using S = AttnShape<KG>;
     const int nqb = (int)ceil_div(a.L, S::Q);
     // resident workgroups per XCD (three per CU at the pattern kernel's register count; with key
     // groups two or one), shared by the query blocks of hgroup (batch, head) pairs
-    a.hgroup = std::max(1, (num_cus_attn() / 8) * (KG == 1 ? 3 : 4 / KG) / nqb);
+    a.hgroup = std::max(1, (num_cus() / 8) * (KG == 1 ? 3 : 4 / KG) / nqb);
     static std::once_flag once;   // opt-in to more than 64 KB of LDS per workgroup
     std::call_once(once, [] {
         for (const void* f : {(const void*)attn_bf16_kernel<true, false, KG>, (const void*)attn_bf16_kernel<false, true, KG>,
@@ -648,7 +633,7 @@ dd_status launch_attn(int dtype, const AttnArgs& a, hipStream_t s) {
         return DD_E_UNSUPPORTED;
     }
     if (dtype == DD_BF16) {
-        const int64_t bh = (int64_t)a.H * a.B, cus = num_cus_attn();
+        const int64_t bh = (int64_t)a.H * a.B, cus = num_cus();
         // Key groups where the query blocks alone leave CUs idle, and under a pattern on long sequences up
         // to two blocks of 128 per CU, whose work differs.  Us with 1 / 2 / 4 groups, without a pattern,
         // then causal, then [x, z_1]: 0.4 blocks per CU (12 heads B 1 L 1024) 19.0 / 15.3 / 11.2, 25.1 / 18.3

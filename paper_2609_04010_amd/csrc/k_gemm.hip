@@ -77,11 +77,10 @@ DD_DEV float round_bf16(float x) {
 // The 192-wide variant exists for tile quantisation: with d = 768 it divides N = 768, 2304 and
 // 3072 into whole rounds of 256 CUs.  Requires K % 128 == 0; rows past M or N are clamped (their
 // results are never stored).
-constexpr int DM = 256;                       // tile rows (M) of the wide tiles
-// DM_ x TBN_ tiles over WGM x WGN wavefronts, each owning a WM x WN sub-tile of MB x NB 32x32 MFMA
+constexpr int DM = 256;                       // tile rows (M)
+// DM x TBN_ tiles over WGM x WGN wavefronts, each owning a WM x WN sub-tile of MB x NB 32x32 MFMA
 // blocks.
-template <int TBN_, int WGM_, int WGN_, int DM_ = DM> struct DLShape {
-    static constexpr int DM = DM_;                            // tile rows (M)
+template <int TBN_, int WGM_, int WGN_> struct DLShape {
     static constexpr int TBN = TBN_;                          // tile columns (N)
     static constexpr int WGM = WGM_, WGN = WGN_, NW = WGM * WGN;
     static constexpr int THREADS = 64 * NW;
@@ -108,20 +107,20 @@ template <int TBN_, int WGM_, int WGN_, int DM_ = DM> struct DLShape {
 // strip is read by the four tiles across N = d, W by every tile of the XCD), and with one K-tile of
 // lead the loop waited for its loads.  The other projections (QKV, MLP up) gained nothing from it.
 template <int EPI, class S> constexpr bool dl_ring() {
-    return DD_GEMM_RING && S::TBN == 192 && S::DM == 256 && S::NW == 8 && EPI == EPI_BIAS_RESID;
+    return DD_GEMM_RING && S::TBN == 192 && S::NW == 8 && EPI == EPI_BIAS_RESID;
 }
 // the ring's LDS: three A stages and two W stages (the residual epilogue stages in the A stage of
 // the last K-tile)
 template <class S> constexpr size_t dl_ring_lds() {
-    return ((size_t)3 * S::DM * BK + (size_t)2 * S::TBN * BK) * sizeof(bf16_t);
+    return ((size_t)3 * DM * BK + (size_t)2 * S::TBN * BK) * sizeof(bf16_t);
 }
 
 // LDS of the direct-to-LDS kernel: the shape's stages and staging (or the ring's), plus for EPI_LSE
 // the (max, sum) partials of each tile row from each of the WGN wavefronts across it
 template <int EPI, class S> constexpr size_t dl_lds_bytes() {
     if constexpr (dl_ring<EPI, S>()) return dl_ring_lds<S>();
-    return S::LDS + (EPI == EPI_LSE || EPI == EPI_LSE_CDF ? (size_t)S::DM * S::WGN * sizeof(float2) : 0) +
-           (EPI == EPI_LSE_CDF ? (size_t)S::DM * sizeof(float2) : 0);
+    return S::LDS + (EPI == EPI_LSE || EPI == EPI_LSE_CDF ? (size_t)DM * S::WGN * sizeof(float2) : 0) +
+           (EPI == EPI_LSE_CDF ? (size_t)DM * sizeof(float2) : 0);
 }
 
 // ROLE (the profiler class of the layer) only separates the symbols of layers sharing an epilogue.
@@ -130,10 +129,9 @@ template <int EPI, class S> constexpr size_t dl_lds_bytes() {
 // current one into stage 0, which the staged epilogue leaves alone: they land while it runs.  (The
 // operand ring of the residual projections fetches the next tile's first K-tiles the same way, into
 // the stages its epilogue does not use.)
-template <int EPI, int ROLE, int TBN_, int WGM_, int WGN_, int DM_>
+template <int EPI, int ROLE, int TBN_, int WGM_, int WGN_>
 __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    using S = DLShape<TBN_, WGM_, WGN_, DM_>;
-    constexpr int DM = S::DM;
+    using S = DLShape<TBN_, WGM_, WGN_>;
     constexpr int MB = S::MB, NB = S::NB, NA = S::ALOADS, NWL = S::WLOADS;
     constexpr bool GROUP_EPI = EPI == EPI_LSE || EPI == EPI_LSE_CDF;
     // M-tiles per group of the tile order: 8 for the vocabulary projection, 2 for QKV (whose output,
@@ -494,7 +492,7 @@ __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmA
                 // 32 banks, in operand stage 1: the last K-tile read it and the next tile's first
                 // K-tile loads go to stage 0
                 constexpr int CHK_LD = S::TBN / 4;
-                static_assert(EPI != EPI_LSE_CDF || (CHK_LD == 64 && (size_t)S::DM * CHK_LD * sizeof(float) <=
+                static_assert(EPI != EPI_LSE_CDF || (CHK_LD == 64 && (size_t)DM * CHK_LD * sizeof(float) <=
                                                                       S::STAGE * sizeof(bf16_t)),
                               "chunk sums fit in one operand stage");
                 float* chk = (float*)(smem + S::STAGE);
@@ -780,7 +778,7 @@ __global__ __launch_bounds__(64 * WGM_ * WGN_, 1) void gemm_bf16_dl_kernel(GemmA
     __builtin_amdgcn_s_waitcnt(0x3F70);           // vmcnt(0): no LDS write in flight at exit
 }
 
-static int num_cus() {
+int num_cus() {
     static int n = 0;
     if (n == 0) {
         int dev = 0, v = 0;
@@ -859,21 +857,21 @@ GemmPlan gemm_plan(int dtype, int epi, const GemmArgs& g, int max_splits) {
     return dtype == DD_BF16 ? plan_tile(g, epi, std::max(max_splits, 1)) : GemmPlan{-1, 1};
 }
 
-template <int EPI, int ROLE, int TBN, int WGM, int WGN, int DMR = DM>
+template <int EPI, int ROLE, int TBN, int WGM, int WGN>
 static void launch_dl(const GemmArgs& g, hipStream_t s) {
-    using S = DLShape<TBN, WGM, WGN, DMR>;
+    using S = DLShape<TBN, WGM, WGN>;
     constexpr size_t lds = dl_lds_bytes<EPI, S>();
     static_assert(lds <= 160 * 1024, "LDS");
-    const int tm = (g.M + S::DM - 1) / S::DM, tn = (g.N + S::TBN - 1) / S::TBN;
+    const int tm = (g.M + DM - 1) / DM, tn = (g.N + S::TBN - 1) / S::TBN;
     static bool attr = false;
     if (!attr) {
-        (void)hipFuncSetAttribute((const void*)gemm_bf16_dl_kernel<EPI, ROLE, TBN, WGM, WGN, DMR>,
+        (void)hipFuncSetAttribute((const void*)gemm_bf16_dl_kernel<EPI, ROLE, TBN, WGM, WGN>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         attr = true;
     }
     // persistent: at most one workgroup per CU
     const int grid = (int)std::min<int64_t>((int64_t)tm * tn, (int64_t)num_cus());
-    launch_k((gemm_bf16_dl_kernel<EPI, ROLE, TBN, WGM, WGN, DMR>), dim3(grid), dim3(S::THREADS), lds,
+    launch_k((gemm_bf16_dl_kernel<EPI, ROLE, TBN, WGM, WGN>), dim3(grid), dim3(S::THREADS), lds,
                        s, g, tm, tn);
 }
 

@@ -194,6 +194,7 @@ struct GemmPlan {
     int tile, splits;
 };
 GemmPlan gemm_plan(int dtype, int epi, const GemmArgs& g, int max_splits);
+int num_cus();   // compute units of the device the library first ran on
 bool gemm_gather_supported(int dtype, int K);
 // the EPI_LSE epilogue (group log-sum-exps beside the logits) runs for this dtype and K
 bool gemm_lse_supported(int dtype, int K);
