@@ -42,8 +42,9 @@ def log(*a):
 
 
 TRIMMED = ("attention", "gemm_attn_out", "gemm_mlp_up", "gemm_mlp_down")
-# the trimmed last layer launches each of its GEMMs twice, gated on the listed-row count: the
-# shape's usual tiles above TAIL_ROWS rows, 64-row tiles up to it (the library's threshold)
+# with more than TAIL_ROWS rows in all (the library's threshold) the trimmed last layer launches each of
+# its GEMMs twice, gated on the listed-row count: the shape's usual tiles above TAIL_ROWS listed rows, ring
+# tiles up to it; else once
 GATED = ("gemm_attn_out", "gemm_mlp_up", "gemm_mlp_down")
 TAIL_ROWS = 2048
 
@@ -76,7 +77,7 @@ def launch_rows(cls, cfg, B, L, T, n, masked, trimmed):
     M, nl = B * L, cfg["n_layers"]
     if masked is None or n <= 0:
         return M
-    gated = trimmed and cls in GATED
+    gated = trimmed and cls in GATED and M > TAIL_ROWS
     per_step = 1 if cls == "gemm_vocab" else nl + (1 if gated else 0)
     total = 0
     for i in range(n):

@@ -33,22 +33,25 @@ def test_launch_rows_follow_the_compacted_loop():
     projection (the still-masked rows of its step) and, in a trimmed loop, the last layer's
     attention, attention output and MLPs (the same rows)."""
     cfg = workloads.model_cfg(2, n_layers=3)
-    B, L, T = 2, 8, 4
+    B, L, T = 2, 2000, 4
     M = B * L
     masked = [16, 12, 7, 3]                       # before steps 4, 3, 2, 1
     assert bench.launch_rows("gemm_mlp_up", cfg, B, L, T, 5, None, True) == M
     # vocabulary: one launch per step, wrapping into the next loop after T launches
     assert bench.launch_rows("gemm_vocab", cfg, B, L, T, 6, masked, False) == (16 + 12 + 7 + 3 + 16 + 12) / 6
     # three layers per step: launches 0, 1 take all rows; the last layer's GEMMs are a gated pair
-    # (usual tiles, then 64-row tiles), of which the small-tile launch does the listed rows here
+    # (usual tiles, then ring tiles), of which the second launch does the listed rows here
     assert bench.launch_rows("gemm_mlp_down", cfg, B, L, T, 8, masked, True) == (4 * M + 0 + 16 + 0 + 12) / 8
     assert bench.launch_rows("gemm_mlp_down", cfg, B, L, T, 6, masked, False) == M
     assert bench.launch_rows("gemm_qkv", cfg, B, L, T, 6, masked, True) == M
     # the attention has one listed-query launch per step
     assert bench.launch_rows("attention", cfg, B, L, T, 3, masked, True) == (2 * M + 16) / 3
     # above the gate the usual tiles do the rows
-    big = [5000, 4000, 3000, 2000]
-    assert bench.launch_rows("gemm_mlp_up", cfg, B, L, T, 4, big, True) == (2 * M + 5000 + 0) / 4
+    big = [4000, 3500, 3000, 2000]
+    assert bench.launch_rows("gemm_mlp_up", cfg, B, L, T, 4, big, True) == (2 * M + 4000 + 0) / 4
+    # up to 2048 rows in all there is no pair: one launch per layer, the last one on the listed rows
+    assert bench.launch_rows("gemm_mlp_down", cfg, 2, 8, T, 6, masked, True) == (4 * 16 + 16 + 12) / 6
+    assert bench.launch_rows("gemm_mlp_up", cfg, 2, 1024, T, 3, [2048, 9, 9, 9], True) == 2048
 
 
 def _record(tmp_path, sha, cls="gemm_mlp_down"):
