@@ -243,10 +243,12 @@ DD_DEV bool row_needs_draw(const PostArgs& a, int row, bool leader, int& zt) {
     return true;
 }
 
-// PT threads per row: 256, or 1024 on few rows, where one row per CU leaves a 256-thread workgroup
-// waiting for its own loads (the launcher has the line).
-template <typename T, int PT>
-__global__ __launch_bounds__(PT) void posterior_kernel(PostArgs a) {
+// THREADS per row: PT, or 1024 on few rows, where one row per CU leaves a 256-thread workgroup waiting
+// for its own loads (the launcher has the line).  The wide form is THREADS / PT workgroups of PT threads
+// side by side, each with a tile of its own, so that every wavefront meets the chunks it meets in the
+// narrow form: a row's sums do not depend on how many rows its call has.
+template <typename T, int THREADS>
+__global__ __launch_bounds__(THREADS) void posterior_kernel(PostArgs a) {
     extern __shared__ float s_lse[];  // one log-sum-exp per group
 
     constexpr int E = Elem<T>::E;
@@ -271,24 +273,26 @@ __global__ __launch_bounds__(PT) void posterior_kernel(PostArgs a) {
     // partial sums (one per iteration, i.e. per group slice); a butterfly over the LPG lanes of a
     // group halves the list at every step, so TILE_IT sums cost log2(LPG) steps and TILE_IT
     // shuffles in total instead of TILE_IT * log2(LPG).
-    // tiles of TILE_IT * PT chunks; the loads of the next tile are issued before the current one
-    // is reduced (two register buffers), so a wavefront always has a tile in flight
+    // tiles of TILE_IT * PT chunks, THREADS / PT of them at a time; the loads of the next ones are
+    // issued before the current ones are reduced (two register buffers), so a wavefront always has a
+    // tile in flight.  Chunk `it` of this thread: tile0 + it PT + tc.
+    const int tc = THREADS == PT ? tid : (tid / PT) * (TILE_IT * PT) + tid % PT;
     auto load_tile = [&](uint4 (&buf)[TILE_IT], const int tile0) {
-        if ((tile0 + TILE_IT * PT) * E <= V) {   // every element of the tile is in the row
+        if ((tile0 + TILE_IT * THREADS) * E <= V) {   // every element of the tiles is in the row
 #pragma unroll
             for (int it = 0; it < TILE_IT; ++it)
-                buf[it] = *(const uint4*)(rowp + (size_t)(tile0 + it * PT + tid) * 16);
+                buf[it] = *(const uint4*)(rowp + (size_t)(tile0 + it * PT + tc) * 16);
         } else {   // last tile: clamped loads, -inf past the row, the ragged chunk clipped
 #pragma unroll
             for (int it = 0; it < TILE_IT; ++it) {
-                const int c = tile0 + it * PT + tid;
+                const int c = tile0 + it * PT + tc;
                 const uint4 x = *(const uint4*)(rowp + (size_t)min(c, nchunk - 1) * 16);
                 buf[it] = (c < nchunk) ? x : Elem<T>::NEG_INF4;
             }
             if (V % E != 0) {
 #pragma unroll
                 for (int it = 0; it < TILE_IT; ++it)
-                    if (tile0 + it * PT + tid == nchunk - 1) Elem<T>::clip(buf[it], V % E);
+                    if (tile0 + it * PT + tc == nchunk - 1) Elem<T>::clip(buf[it], V % E);
             }
         }
     };
@@ -334,11 +338,11 @@ __global__ __launch_bounds__(PT) void posterior_kernel(PostArgs a) {
         }
         constexpr int DUP = (LPG / TILE_IT) > 1 ? LPG / TILE_IT : 1;   // lanes holding the same sum
         if ((lane & (DUP - 1)) == 0) {
-            const int c = tile0 + idx * PT + (tid & ~(LPG - 1));
+            const int c = tile0 + idx * PT + (tc & ~(LPG - 1));
             if (c < nchunk) s_lse[c / LPG] = mref + logf(v[0]);
         }
     };
-    constexpr int TS = TILE_IT * PT;
+    constexpr int TS = TILE_IT * THREADS;
     uint4 ba[TILE_IT], bb[TILE_IT];
     load_tile(ba, 0);
     for (int t0 = 0; t0 < nchunk; t0 += 2 * TS) {

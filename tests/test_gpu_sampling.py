@@ -388,3 +388,24 @@ def test_posterior_rows_at_the_wide_workgroup_line(rows, prior, dt, V):
                                               0.5 if prior == "mask" else 0.0, 2.0, 0.0)
     clear = (gaps.min(axis=1) if gaps.ndim == 2 else gaps) > GAP
     assert np.array_equal(got[clear], ref[clear])
+
+
+@pytest.mark.parametrize("prior,dt,V", [("mask", "bf16", 50257), ("uniform", "fp32", 20003), ("uniform", "bf16", 17000)])
+def test_posterior_rows_do_not_depend_on_the_number_of_rows(prior, dt, V):
+    """The same rows drawn in one call of 300, in calls of 256 and 44 (1024 threads per row) and one by
+    one: the same log-sum-exps, bit for bit, and the same ids."""
+    torch = torch_or_skip()
+    R, ld = 300, int(dd.logits_ld(V))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(12)
+    logits = (3.0 * torch.randn((R, ld), generator=g, device="cuda")).to(torch.bfloat16 if dt == "bf16" else torch.float32)
+    z = torch.full((R,), V if prior == "mask" else 5, dtype=torch.int32, device="cuda")
+    res = []
+    for parts in ([(0, R)], [(0, 256), (256, R)], [(i, i + 1) for i in range(0, R)]):
+        out, lse = torch.empty_like(z), torch.zeros(R, dtype=torch.float32, device="cuda")
+        for a, b in parts:
+            dd.posterior_sample(prior, logits[a:b], dt, ld, b - a, V, z[a:b], 0.3, 0.6, out[a:b], seed=4, step=2, row0=a,
+                                row_lse=lse[a:b])
+        res.append((out, lse))
+    for out, lse in res[1:]:
+        assert torch.equal(lse, res[0][1]) and torch.equal(out, res[0][0])
