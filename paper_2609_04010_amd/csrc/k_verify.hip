@@ -469,13 +469,14 @@ dd_status launch_verify(const VerifyArgs& a, int logits_dtype, float* lse, hipSt
     auto pick = [&](auto t) {
         using T = decltype(t);
         // Threads and chunks in flight per thread of a row, bf16 us with 256 x 2 / 256 x 4 / 512 x 2: two
-        // where 256 threads then cover the row (S 1000, B 2, V 2000 6.4 / 8.3 / 10.8), 512 threads on few
-        // long rows (S 1, B 2, V 50257 6.5 / 6.0 / 5.6; fp32 8.1 / 6.7 / 6.0), else four (S 256, B 16, V
-        // 5000 19.2 / 17.8 / 24.4)
+        // where 256 threads then cover the row (S 1000, B 2, V 2000 6.4 / 8.3 / 10.8), four up to 2048
+        // chunks (S 256, B 16, V 5000 19.2 / 17.8 / 24.4), 512 threads on longer rows (S 1, B 2, V 50257
+        // 6.5 / 6.0 / 5.6; S 3000 151 / 151 / 149).  By the row's length alone: its sum does not depend on
+        // how many rows the call has.
         if (hint) lse_run(row_lse_kernel<T, 512, 2, true>, 512);
         else if (nchunk <= 2 * 256) lse_run(row_lse_kernel<T, 256, 2, false>, 256);
-        else if (!is_short && rows <= 256) lse_run(row_lse_kernel<T, 512, 2, false>, 512);
-        else lse_run(row_lse_kernel<T, 256, 4, false>, 256);
+        else if (is_short) lse_run(row_lse_kernel<T, 256, 4, false>, 256);
+        else lse_run(row_lse_kernel<T, 512, 2, false>, 512);
         // Threads of a sequence's draw: as many as fit where every sequence has a CU to itself, fewer the
         // more of them share one (bf16, B 2 or 3, us with 256 / 512 / 1024 threads: V 50257 S 256 28.8 /
         // 19.0 / 15.9, S 700 32.9 / 27.5 / 34.1, S 3000 87 / 88 / 123; V 5000 10.6 / 9.7 / 9.4, 11.0 / 10.3 /

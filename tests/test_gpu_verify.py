@@ -215,7 +215,7 @@ DRAW_CASES = [
     # threads (256 threads while 512 chunks of 16 bytes cover a row; beyond that 1024 up to 256 sequences,
     # 512 up to 768, then 256) and its layout of words (one candidate per lane up to 64 groups, and in a
     # last group of up to 64 classes), and where the log-sum-exp kernel takes 512 threads (more than 2048
-    # chunks on up to 256 rows)
+    # chunks)
     (256, 2, 4096, "bf16", "philox", 1.0),
     (256, 2, 4104, "bf16", "philox", 1.0),
     (257, 2, 4104, "bf16", "explicit", 1.0),
@@ -232,3 +232,33 @@ DRAW_CASES = [
 @pytest.mark.parametrize("case", DRAW_CASES, ids=lambda c: f"S{c[0]}-B{c[1]}-V{c[2]}-{c[3]}-{c[4]}")
 def test_spec_verify_at_the_lines_between_draw_forms(case):
     test_spec_verify_parity(case)
+
+
+@pytest.mark.parametrize("V,dt", [(16391, "bf16"), (8196, "fp32"), (9000, "bf16"), (300, "fp32")])
+def test_spec_verify_sequences_do_not_depend_on_the_number_of_sequences(V, dt):
+    """The same sequences verified in one call of 342 (position by position on long rows), in calls of 100
+    and one by one: the same n and z, and the same log-sum-exps of the tested positions, bit for bit."""
+    torch = torch_or_skip()
+    S, B = 342, 3
+    pl, ql, draft = _case(29, S, B, V, dt, 0.6)
+    ld = int(dd.logits_ld(V))
+    p_d, q_d = logits_dev(torch, pl.reshape(S * B, V), dt, ld), logits_dev(torch, ql.reshape(S * (B - 1), V), dt, ld)
+    dr = dev_i32(torch, draft)
+
+    def run(s0, s1):
+        n = torch.empty(s1 - s0, dtype=torch.int32, device="cuda")
+        z = torch.empty_like(n)
+        ws = torch.zeros(dd.spec_verify_workspace_bytes(s1 - s0, B), dtype=torch.uint8, device="cuda")
+        dd.spec_verify(p_d[s0 * B:s1 * B], q_d[s0 * (B - 1):s1 * (B - 1)], dt, ld, s1 - s0, B, V, dr[s0:s1], n, z, ws,
+                       seed=6, step=1, row0=s0)
+        lse = ws.view(torch.float32).cpu().numpy()[:(s1 - s0) * (2 * B - 1)]
+        return n.cpu().numpy(), z.cpu().numpy(), lse[:(s1 - s0) * B].reshape(-1, B), lse[(s1 - s0) * B:].reshape(-1, B - 1)
+
+    n, z, lp, lq = run(0, S)
+    assert 0 < (n == B).sum() < S
+    for s0, s1 in [(s, min(s + 100, S)) for s in range(0, S, 100)] + [(s, s + 1) for s in range(0, S, 7)]:
+        n1, z1, lp1, lq1 = run(s0, s1)
+        assert np.array_equal(n1, n[s0:s1]) and np.array_equal(z1, z[s0:s1])
+        for s in range(s1 - s0):
+            assert np.array_equal(lp1[s, :n1[s]], lp[s0 + s, :n1[s]])
+            assert np.array_equal(lq1[s, :n1[s]], lq[s0 + s, :n1[s]])
