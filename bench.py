@@ -32,7 +32,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 vector
+PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 (matrix and vector alike)
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 PROFILED_LAUNCHES = 256       # launches of the dominant kernel class timed with events per run
 
@@ -245,10 +245,11 @@ def forward_bench(args):
 
 
 # ALU roofline of the Gaussian-latent argmax, per Philox-4x32-10 block (4 classes): 10 rounds of two
-# 32x32 -> 64-bit multiplies (v_mad_u64_u32) and two xors, plus a compare, compare and select per class
-# for the running argmax: 52 VALU instructions.  Peak = 256 CUs x 64 lanes x 2.4 GHz / 52 with every
-# instruction at full rate (an upper bound; the 64-bit multiplies may issue slower).
-LATENT_VALU_PER_BLOCK = 52
+# 32x32 -> 64-bit multiplies (v_mad_u64_u32) and two three-input exclusive ors, plus the block's largest
+# word and one compare and select for the running argmax: 45 VALU instructions in the compiled loop (part
+# of the first and last rounds is shared or not needed).  Peak = 256 CUs x 64 lanes x 2.4 GHz / 45 with
+# every instruction at full rate (an upper bound; the 64-bit multiplies may issue slower).
+LATENT_VALU_PER_BLOCK = 45
 LATENT_PEAK_GBLOCKS = 256 * 64 * 2.4e9 / LATENT_VALU_PER_BLOCK / 1e9
 HBM_PEAK_GBS = 8000.0
 
@@ -310,7 +311,10 @@ def kernels_bench(args):
     ms = timed(lambda: dd.spec_verify(p, q, "bf16", ld, S, B, V, draft, n_out, z_out, ws, seed=5, step=1,
                                       dev_err=err))
     assert int(err.item()) == 0
-    nbytes = S * (2 * B + 1) * V * 2     # every p and q row once (log-sum-exps), the chosen pair again
+    # every p and q row up to the first rejection once (log-sum-exps; the rows after it are not needed), and
+    # the chosen pair, or the last p row, again
+    n = n_out.double()
+    nbytes = float((2 * n - (n == B).double() + 2 - (n == B).double()).sum()) * V * 2
     gbs = nbytes / (ms * 1e-3) / 1e9
     print(json.dumps({"mode": "kernel", "kernel": "spec_verify", "S": S, "B": B, "V": V, "dtype": "bf16",
                       "calls": args.steps, "ms_per_call": ms, "accepted_mean": float(n_out.float().mean()) - 1,
@@ -441,8 +445,6 @@ def main():
     per_launch, unit, bound = algorithmic_units(dominant, cfg, B, L, rows)
     achieved = per_launch / (ms_l / n_l * 1e-3) / 1e12
     peak = PEAK_BF16_TFLOPS if cfg["dtype"] == "bf16" else PEAK_FP32_TFLOPS
-    if cfg["dtype"] != "bf16":   # the fp32 validation build multiplies with vector FMAs, not MFMA
-        bound = "alu"
     tokens = args.steps * M
     out = {
         "metric": f"generated tokens/sec at L={L},B={B},T={T} on 1 GPU; ms per reverse step",

@@ -792,8 +792,11 @@ int num_cus() {
 // 768) 4.5 / 5.5 / 7.2 us with 4 / 2 / 1 at M 64, 6.7 / 6.4 / 8.1 at M 512, 7.6 / 7.4 with 2 / 1 at M
 // 1024; MLP down (K 3072) 7.0 / 10.5 / 16 at M 64, 12.7 / 13.5 / 16 at M 512, 13.6 with 2 against 15.6
 // at M 1024, 23.4 against 25.4 at M 2000; the normalisation pays 2 us for the first slab and 1 us for
-// another per 1024 rows (M 2000: 5.1 -> 9.1 us).  Steps of M, not the best per M, and cut by the
-// model's own K, so that a row's sums are the same in calls of similar size and with adapters off.
+// another per 1024 rows (M 2000: 5.1 -> 9.1 us).  Steps of M (all of d 768's making), not the best per M,
+// and cut by the model's own K, so that a row's sums are the same in calls of similar size and with
+// adapters off; they change in their last bits between 128 and 129 rows (32 x 32 tiles below, see
+// plan_tile), 512 and 513, 1024 and 1025.  The workspace holds two slabs beside MLP down's operands, so it
+// splits three ways where four are wanted.
 static int ring_splits(const GemmArgs& g, int max_splits) {
     const int k = g.k_base > 0 ? g.k_base : g.K;
     const int want = g.M <= 512 ? (k >= 2048 ? 4 : 2) : g.M <= 1024 && k >= 2048 ? 2 : 1;
@@ -814,7 +817,9 @@ static int64_t tiles_of(const GemmArgs& g, int bm, int bn) {
 // 20.3 / 21.0 at M 1024, 29.4 / 37.4 against 21.5 / 24.5 at M 4096; MLP down (K 3072, N 768): 13.6
 // against 57.6 at M 1024, 35.9 against 57.8 at M 4096, 103.7 against 76.8 at M 16384.  Products with
 // N <= 128 (adapter down-projections) leave the 256-row tiles one workgroup per 256 rows: ring tiles
-// only.  A split costs the next normalisation one more slab to read.
+// only.  A split costs the next normalisation one more slab to read.  Every tile but the 32 x 32 one sums a
+// split's K from its start to its end, so among those the choice does not change a bit (the vocabulary
+// projection apart, where the 256-row tiles start at different K-slices).
 static GemmPlan plan_tile(const GemmArgs& g, int epi, int max_splits) {
     const char* e = getenv("DD_GEMM_TILE");
     const int forced = e ? atoi(e) : -1;

@@ -20,9 +20,10 @@
 // L2, 16 TB/s.  Against the register-staged 128 x 128 tiles this kernel replaced for K % 128 != 0:
 // M 1320, N 3072, K 832 24.0 -> 13.3 us, M 16384 143.5 -> 134.4.
 //
-// fp32 (the validation build) takes the same kernel with v_mfma_f32_32x32x2_f32, 64 x 64 tiles, bound by
-// the matrix cores: 12 layers d 768 on 256 rows 15.3 -> 1.47 ms per forward pass against the VALU
-// kernel it replaced (with the attention of k_attn.hip), error against float64 1.2e-6 -> 0.6e-6.
+// fp32 (the validation build) takes the same kernel with v_mfma_f32_32x32x2_f32 and the smallest of the
+// 32 x 32, 32 x 64 and 64 x 64 tiles that fits the CUs once, not split over workgroups, bound by the matrix
+// cores: 12 layers d 768 on 256 rows 15.3 -> 1.45 ms per forward pass against the VALU kernel it
+// replaced (with the attention of k_attn.hip), error against float64 1.2e-6 -> 0.55e-6.
 //
 // Between the two (about 1300 to 3000 rows) 128 x 192 tiles take one round of the CUs: M 2000, K 768, N
 // 2304 / 3072 15.6 / 16.6 us against 18.3 / 20.2 with 64 x 64 tiles and 20.4 / 20.9 with 256-row ones.

@@ -4,7 +4,7 @@ dd_denoise_forward_ex, against the float64 oracle on the same seeded inputs.
 Patterns: causal (AR pathway, drafting pass), block-causal, the [x, z_1] block-diffusion pattern;
 lengths that span several 128-query workgroups and 64-key tiles with a ragged tail, block sizes
 aligned and not aligned to the tiles.  Adapters: the paper's rank 128 / alpha 256 on the bf16
-GPT-2-small shape, a rank whose K = in + r misses the 128 multiple (fallback GEMM), the fp32 build,
+GPT-2-small shape, a rank whose K = in + r misses the 128 multiple (ring tiles only), the fp32 build,
 mixed per-position gates, and the teacher property of the [x, z_1] pass.
 """
 import numpy as np
@@ -188,8 +188,8 @@ def test_teacher_logits_in_one_pass_match_base_model_on_gpu(tile, monkeypatch):
     the [x, z_1] call but all in M-tile 0 of the call on x alone, so their fp32 sums are taken in
     another order and a logit can round to the neighbouring bf16 value.  Hence: at most one bf16
     ulp of the logit with the default tiles (2^-6 = 1.6e-2 for |logit| in [2, 4)), and bit-identical
-    logits with the register-staged 128 x 128 tile (DD_GEMM_TILE=0), whose K loop always starts at
-    slice 0."""
+    logits with the ring kernel's 128 x 128 tile (DD_GEMM_TILE=0), whose K loop always starts at slice 0
+    (both calls split the residual projections alike: 192 and 384 rows, cut by the model's own K)."""
     torch = torch_or_skip()
     if tile is None:
         monkeypatch.delenv("DD_GEMM_TILE", raising=False)
