@@ -85,7 +85,9 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* z, int64_t
     ln_row<W, NPL, RMS>(x, lane, d, g, b, eps, xln + row * ldo);
 }
 
-template <typename W, int NPL, bool RMS>
+// SLABS: the row has partials to add (a template parameter: the loads of the gain and shift would wait
+// behind the branch)
+template <typename W, int NPL, bool RMS, bool SLABS>
 __global__ __launch_bounds__(256) void ln_kernel(const float* h, int64_t rows, const W* g,
                                                  const W* b, float eps, W* out, int64_t ldo,
                                                  const int32_t* m_count, LnSlabs add) {
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const float* h, int64_t rows, c
     float x[NPL];
 #pragma unroll
     for (int k = 0; k < NPL; ++k) x[k] = h[row * d + lane + 64 * k];
-    if (add.n > 0) {   // partials of a split projection, in slab order
+    if constexpr (SLABS) {   // partials of a split projection, in slab order
 #pragma unroll
         for (int i = 0; i < MAX_SPLITS - 1; ++i) {
             if (i >= add.n) break;
@@ -167,8 +169,11 @@ DD_DEV void load_gain_shift(const bf16_t* g, const bf16_t* b, int lane, uint2 (&
 // the residual row arrives from the Infinity Cache (the residual projection stores it normally),
 // one row per wavefront is the faster choice: 11.7 vs 12.0 us at B16 L1024 d768, 29.7 vs 30.5 us
 // at B8 L4096 d1024.
+//
+// SLABS as above: with the test for partials in the one kernel the gain and shift were loaded after it,
+// 12.7 against 11.6 us at B16 L1024.
 constexpr int LN_RPW = 1;
-template <int NV, bool RMS>
+template <int NV, bool RMS, bool SLABS>
 __global__ __launch_bounds__(256) void ln_bf16_v4_kernel(const float* h, int64_t rows,
                                                          const bf16_t* g, const bf16_t* b,
                                                          float eps, bf16_t* out, int64_t ldo,
@@ -185,7 +190,7 @@ __global__ __launch_bounds__(256) void ln_bf16_v4_kernel(const float* h, int64_t
         const float4* hr = (const float4*)(h + (row0 + r) * d);
 #pragma unroll
         for (int k = 0; k < NV; ++k) x[r][k] = hr[lane + 64 * k];
-        if (add.n > 0) {   // partials of a split projection, in slab order
+        if constexpr (SLABS) {   // partials of a split projection, in slab order
             float4 p[MAX_SPLITS - 1][NV];
 #pragma unroll
             for (int i = 0; i < MAX_SPLITS - 1; ++i)
@@ -336,10 +341,15 @@ template <typename W, bool RMS>
 dd_status launch_ln_t(const float* h, int64_t rows, int d, const void* g, const void* b, float eps,
                       void* out, int64_t ldo, hipStream_t s, const int32_t* m_count, const LnSlabs& add) {
     const dim3 grid((unsigned)ceil_div(rows, 4)), blk(256);
+    const bool with_slabs = add.n > 0;
     switch (d / 64) {
 #define X(n)                                                                                     \
     case n:                                                                                      \
-        launch_k((ln_kernel<W, n, RMS>), grid, blk, 0, s, h, rows, (const W*)g,       \
+        if (with_slabs)                                                                           \
+            launch_k((ln_kernel<W, n, RMS, true>), grid, blk, 0, s, h, rows, (const W*)g,         \
+                           (const W*)b, eps, (W*)out, ldo, m_count, add);                        \
+        else                                                                                      \
+            launch_k((ln_kernel<W, n, RMS, false>), grid, blk, 0, s, h, rows, (const W*)g,        \
                            (const W*)b, eps, (W*)out, ldo, m_count, add);                        \
         break;
         DD_NPL_CASES(X)
@@ -353,10 +363,14 @@ template <bool RMS>
 void launch_ln_v4(int d, dim3 grid, const float* h, int64_t rows, const bf16_t* g, const bf16_t* b,
                   float eps, bf16_t* o, int64_t ldo, hipStream_t s, const int32_t* mc, const LnSlabs& add) {
     const dim3 blk(256);
+    const bool with_slabs = add.n > 0;
     switch (d / 256) {
 #define X(n)                                                                                            \
     case n:                                                                                             \
-        launch_k((ln_bf16_v4_kernel<n, RMS>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc, add);    \
+        if (with_slabs)                                                                                 \
+            launch_k((ln_bf16_v4_kernel<n, RMS, true>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc, add);  \
+        else                                                                                            \
+            launch_k((ln_bf16_v4_kernel<n, RMS, false>), grid, blk, 0, s, h, rows, g, b, eps, o, ldo, mc, add); \
         break;
         DD_NV_CASES(X)
 #undef X
