@@ -175,30 +175,31 @@ def test_fp32_forward_matches_oracle(case):
 
 
 LISTED_CASES = [
-    # overrides, B, L: the row counts on either side of the lines of the residual projections' split
+    # overrides, B, L, T: the row counts on either side of the lines of the residual projections' split
     # (128, 512, 1024 rows), and above 2048, where the layer is launched for many and for few listed rows
-    (dict(d_model=128, n_heads=2, vocab=12000), 1, 40),
-    (dict(d_model=128, n_heads=2, vocab=12000), 2, 64),
-    (dict(d_model=128, n_heads=2, vocab=12000), 3, 43),
-    (dict(d_model=128, n_heads=2, vocab=12000, d_mlp=128), 3, 50),    # no room for a slab beside the MLP rows
-    (dict(), 1, 150),
-    (dict(), 2, 256),
-    (dict(), 3, 200),
-    (dict(), 4, 275),
-    (dict(), 7, 300),
+    (dict(d_model=128, n_heads=2, vocab=12000), 1, 40, 3),
+    (dict(d_model=128, n_heads=2, vocab=12000), 2, 64, 3),
+    (dict(d_model=128, n_heads=2, vocab=12000), 3, 43, 3),
+    (dict(d_model=128, n_heads=2, vocab=12000, d_mlp=128), 3, 50, 3),    # no room for a slab beside the MLP rows
+    (dict(), 1, 150, 3),
+    (dict(), 2, 256, 3),
+    (dict(), 3, 200, 3),
+    (dict(), 4, 275, 3),
+    (dict(), 7, 300, 3),
+    (dict(), 7, 300, 1),      # every row listed: the 256-row tiles
 ]
 
 
-@pytest.mark.parametrize("case", LISTED_CASES, ids=lambda c: f"B{c[1]}-L{c[2]}-" + "-".join(f"{k}{v}" for k, v in c[0].items()))
+@pytest.mark.parametrize("case", LISTED_CASES, ids=lambda c: f"B{c[1]}-L{c[2]}-T{c[3]}-" + "-".join(f"{k}{v}" for k, v in c[0].items()))
 def test_listed_rows_have_the_full_path_logits(case):
     """The loop's last layer runs on the listed rows alone; their logits are those of
     dd_denoise_forward on every row, bit for bit.  Compared where the vocabulary projection sums K in
     the same order on both sides: list index and token row both in the first tile of 256 rows."""
     torch = torch_or_skip()
-    over, B, L = case
+    over, B, L, T = case
     say("listed rows", case)
     cfg = workloads.model_cfg(2, n_layers=2, max_len=L, **over)
-    V, M, T = cfg["vocab"], B * L, 3
+    V, M = cfg["vocab"], B * L
     buf = torch.zeros(dd.param_bytes(cfg), dtype=torch.uint8, device="cuda")
     dd.init_params(cfg, buf, seed=45)
     al = 1.0 - np.arange(T + 1) / T
